@@ -206,6 +206,7 @@ struct dda_target {
     double green_kd = -1.0;
     bool have64 = false, have32 = false;
     DevBuf gh64, gh32;
+    DevBuf gp64, gp32;                 // the same in the plane kernel's layout, where it takes this grid
     int lo[3] = {0, 0, 0};             // lattice coordinates of the bounding box's first point
     // near field: the last extended volume (every point a site), keyed by the
     // points added below and above the box on each axis
@@ -444,6 +445,9 @@ struct Work {
     int site_blocks = 1;
     int pass_blocks = 1;
     int var[3] = {0, 0, 0};   // strided-pass variants: y forward, z with tensor, y inverse
+    // the plane kernel takes the place of the strided passes of an FP64 / FP32
+    // product (set with the variants; not where the caller names a variant)
+    bool plane64 = false, plane32 = false;
     void* grid = nullptr;
     double* kh = nullptr;
     double2* e0 = nullptr;
@@ -595,6 +599,8 @@ struct Work {
     // near-ties resolve the same way from run to run.
     void autotune(bool enabled, int forced = 0) {
         const Geo& g = t->geo;
+        plane64 = forced <= 0 && plane_fits<double>(g, nrhs);
+        plane32 = forced <= 0 && plane_fits<float>(g, nrhs);
         if (forced > 0) {
             for (int slot = 0; slot < 3; ++slot) {
                 const int nv = strided_variants(g.M[slot == 1 ? 2 : 1], slot == 1);
@@ -610,7 +616,9 @@ struct Work {
             return;
         }
         std::array<int, 3> best{0, 0, 0};
-        if (enabled) {
+        if (fp32 ? plane32 : plane64) {   // no pass to tune: one plane kernel takes all three
+            if (enabled) c->tuned[key] = best;
+        } else if (enabled) {
             hipEvent_t e0 = take_event(c), e1 = take_event(c);
             for (int slot = 0; slot < 3; ++slot) {
                 const int L = g.M[slot == 1 ? 2 : 1];
@@ -692,17 +700,24 @@ struct Work {
             Timed tm(c, T_SCATTER, s);
             launch_scatter_x<T>(sc, chk_sc, g, a, gr, tw, s);
         }
-        {
-            Timed tm(c, T_FFTY_FWD, s);
-            strided_slot<T>(0, chk_rest, vars[0]);
-        }
-        {
+        if (sizeof(T) == 4 ? plane32 : plane64) {
             Timed tm(c, T_FFTZ_G, s);
-            strided_slot<T>(1, chk_rest, vars[1]);
-        }
-        {
-            Timed tm(c, T_FFTY_INV, s);
-            strided_slot<T>(2, chk_rest, vars[2]);
+            const dda_target* src = segs.empty() ? t : segs[0].t;
+            launch_plane<T>(chk_rest, g, nrhs, gr, tw, (const C*)(sizeof(T) == 4 ? src->gp32.p : src->gp64.p), a.st,
+                            s);
+        } else {
+            {
+                Timed tm(c, T_FFTY_FWD, s);
+                strided_slot<T>(0, chk_rest, vars[0]);
+            }
+            {
+                Timed tm(c, T_FFTZ_G, s);
+                strided_slot<T>(1, chk_rest, vars[1]);
+            }
+            {
+                Timed tm(c, T_FFTY_INV, s);
+                strided_slot<T>(2, chk_rest, vars[2]);
+            }
         }
         {
             Timed tm(c, T_GATHER, s);
@@ -740,6 +755,12 @@ void ensure_green(dda_ctx* c, dda_target* t, double kd, bool fp32, bool force) {
     double2* g64 = (double2*)t->gh64.ensure(nh * sizeof(double2));
     float2* g32 = fp32 ? (float2*)t->gh32.ensure(nh * sizeof(float2)) : nullptr;
     launch_green_octant(g, G, g64, g32, c->stream);
+    // the plane kernel's layout, where it takes this grid (with any number of
+    // right-hand sides; launch limits are checked with the product)
+    const bool p64 = plane_fits<double>(g, 1), p32 = fp32 && plane_fits<float>(g, 1);
+    if (p64 || p32)
+        launch_green_plane(g, g64, p64 ? (double2*)t->gp64.ensure(plane_values(g) * sizeof(double2)) : nullptr,
+                           p32 ? (float2*)t->gp32.ensure(plane_values(g) * sizeof(float2)) : nullptr, c->stream);
     HIPCHK(hipGetLastError());
     t->green_kd = kd;
     t->have64 = true;
@@ -866,7 +887,11 @@ void run_chunk(Work& w, int chunk) {
     key_bytes(key, w.t->gh64.p);
     key_bytes(key, w.t->gh32.p);
     key_bytes(key, w.t->tw.p);
+    key_bytes(key, w.t->gp64.p);
+    key_bytes(key, w.t->gp32.p);
     key_bytes(key, w.var);
+    key_bytes(key, w.plane64);
+    key_bytes(key, w.plane32);
     key_bytes(key, w.site_blocks);
     key_bytes(key, w.pass_blocks);
     const int flags[4] = {chunk, w.fp32 ? 1 : 0, w.qmr ? 1 : 0, w.b2 ? 1 : 0};
@@ -1285,6 +1310,8 @@ Job make_batch(dda_ctx* c, const std::vector<Job*>& mem) {
         r.kd = j->kd;
         r.ghat[0] = jt->gh64.p;
         r.ghat[1] = jt->gh32.p;
+        r.gplane[0] = jt->gp64.p;
+        r.gplane[1] = jt->gp32.p;
         for (int k = 0; k < count; ++k) b.host_rg.push_back(r);
         m.batch_site_blocks = std::max(m.batch_site_blocks, r.site_blocks);
         m.idx.insert(m.idx.end(), j->idx.begin(), j->idx.end());
@@ -1635,7 +1662,8 @@ void free_target(dda_target* t) {
     if (!t) return;
     free_target(t->nf);
     t->nf = nullptr;
-    for (DevBuf* b : {&t->map, &t->perm, &t->mat, &t->coords, &t->tw, &t->tw32, &t->mdev, &t->gh64, &t->gh32})
+    for (DevBuf* b : {&t->map, &t->perm, &t->mat, &t->coords, &t->tw, &t->tw32, &t->mdev, &t->gh64, &t->gh32, &t->gp64,
+                      &t->gp32})
         b->release();
     delete t;
 }

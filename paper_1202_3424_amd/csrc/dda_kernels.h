@@ -45,7 +45,8 @@ struct RhsGeo {
     int site_blocks;
     int pad;
     double kd;
-    const void* ghat[2];   // tensor FFT: FP64 (double2), FP32 (float2)
+    const void* ghat[2];     // tensor FFT: FP64 (double2), FP32 (float2)
+    const void* gplane[2];   // the same in the layout of the plane kernel (dda_plane.h), or null
 };
 
 // Geometry of one target's FFT grid.
@@ -177,6 +178,23 @@ inline int strided_variants(int L, bool gh) { return ct_length(L) ? (gh ? 28 : 1
 constexpr bool ragged_variant(int gh, int v) {
     return !gh || !(v == 0 || v == 1 || v == 2 || v == 7 || v == 8 || v == 9);
 }
+// Passes 2-4 as one kernel per kx plane (dda_plane.h), where plane_fits: the
+// y and z extents have compiled lengths whose plane fits the LDS.  gp: the
+// tensor octant in that kernel's layout (launch_green_plane; a ragged batch
+// takes each right-hand side's from g.rg).  Bitwise the results of the three
+// launch_strided passes, and faster wherever it fits, so it needs no tuning:
+// 33 us against 48 for 128 x 96 x 64 with two right-hand sides in FP64.
+template <typename T>
+void launch_plane(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, const double2* tw,
+                  const typename V2<T>::t* gp, const RhsState* st, hipStream_t s);
+template <typename T> bool plane_fits(const Geo& g, int nrhs);
+// stored ky of a tensor row in that layout: LY / 2 + 1 and padding up to a
+// 128-byte (FP64) or 64-byte (FP32) boundary
+constexpr int plane_row(int LY) { return (LY / 2 + 1 + 7) & ~7; }
+// values of that layout, [Hx][Hz][6][plane_row(My)]
+inline size_t plane_values(const Geo& g) { return (size_t)g.H[0] * g.H[2] * 6 * plane_row(g.M[1]); }
+// the octant in that layout from the octant itself (either output may be null)
+void launch_green_plane(const Geo& g, const double2* gh64, double2* gp64, float2* gp32, hipStream_t s);
 // The interaction tensor on the padded grid is held as two three-component
 // slabs [2][npts][3]: (xx, xy, xz) and (yy, yz, zz), so that its transforms
 // run as the three-component passes with two right-hand sides.

@@ -128,6 +128,22 @@ __global__ __launch_bounds__(NT) void k_green_octant(Geo g, const double2* G, do
     }
 }
 
+// The octant as [Hx][Hz][6][plane_row(My)] for the plane kernel, the padding
+// of a row zero.
+__global__ __launch_bounds__(NT) void k_green_plane(Geo g, const double2* gh64, double2* gp64, float2* gp32) {
+    const int hyp = plane_row(g.M[1]);
+    const long long i = (long long)blockIdx.x * NT + threadIdx.x;
+    if (i >= (long long)g.H[0] * g.H[2] * 6 * hyp) return;
+    const int hy = (int)(i % hyp);
+    const int c = (int)(i / hyp % 6);
+    const int hz = (int)(i / (6LL * hyp) % g.H[2]);
+    const int hx = (int)(i / (6LL * hyp * g.H[2]));
+    double2 v = {0.0, 0.0};
+    if (hy < g.H[1]) v = gh64[(((long long)hz * g.H[1] + hy) * g.H[0] + hx) * 6 + c];
+    if (gp64) gp64[i] = v;
+    if (gp32) gp32[i] = float2{(float)v.x, (float)v.y};
+}
+
 // 1/alpha (or its derivative with respect to eps, scheme + 2) per
 // (right-hand side, material): "Dipole Polarizabilities".
 //   LATTDR (Draine & Goodman 1993): 1/alpha = 1/alpha_CM
@@ -1169,6 +1185,11 @@ void launch_green_sample(const Geo& g, double kd, double2* G, hipStream_t s) {
 void launch_green_octant(const Geo& g, const double2* G, double2* gh64, float2* gh32, hipStream_t s) {
     const long long nh = (long long)g.H[0] * g.H[1] * g.H[2];
     hipLaunchKernelGGL(k_green_octant, dim3((unsigned)((nh + NT - 1) / NT)), dim3(NT), 0, s, g, G, gh64, gh32);
+}
+
+void launch_green_plane(const Geo& g, const double2* gh64, double2* gp64, float2* gp32, hipStream_t s) {
+    const long long n = (long long)plane_values(g);
+    hipLaunchKernelGGL(k_green_plane, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, s, g, gh64, gp64, gp32);
 }
 
 void launch_alpha(int nrhs, int nmat, const double2* mats, double m_medium, const double* khat, const double2* e0,

@@ -1,0 +1,413 @@
+// Passes 2-4 of the product (y forward, z with the tensor product, y
+// inverse; see dda_passes.h) as one kernel per kx plane, for grids whose
+// (y, z) plane fits one compute unit's LDS.
+//
+// What bounds it.  Run as three kernels, the passes write and read the padded
+// plane three times (ten line-grid volumes of traffic) and each waits for the
+// one before it; here the plane is read once, kept in LDS through all three
+// transforms and written once (two volumes).  What is left is the LDS traffic
+// of the exchanges and the arithmetic of the transforms.
+//
+// Layout.  A workgroup owns one kx of one right-hand side: three component
+// planes, element (ky, z) of component c at c * CS + ky * ZS + z, z < nz only
+// (the z padding lives in registers).
+// ZS is odd and CS = 3 mod 8 (FP64) or 5 mod 16 (FP32) in elements, so that
+// both the lines along y (lanes over z and c) and the columns along z
+// (lanes over ky) touch distinct banks.  Every line is handled by Q = L / P
+// lanes of one wavefront (the register-resident passes of dda_device.h, the
+// same butterflies and twiddles as every other form, so bitwise-identical
+// results), and a line's exchange goes through that line's own LDS words:
+// LDS instructions of one wavefront execute in order, so no exchange needs a
+// workgroup barrier, and the kernel has two in all.
+#pragma once
+
+#include "dda_passes.h"
+
+namespace dda {
+namespace plane {
+
+using passes::tw_table;
+
+// VGPRs of line data per thread in the z stage (three components of P values)
+template <typename T> constexpr int z_vgprs(int LZ) { return 3 * ct_split(LZ) * (int)(2 * sizeof(T) / 4); }
+
+// LDS words (elements) of one column's exchange: element (j, f) of the
+// first group's output, f < P, j < Q, at (f / FG) * CS + (f % FG) * Q + j:
+// a third of the f in each of the column's three component segments.
+constexpr int ex_group(int L) { return (ct_split(L) + 2) / 3; }
+constexpr int ex_words(int L) { return ex_group(L) * (L / ct_split(L)); }
+
+// z stride: odd, at least the occupied z extent and an exchange segment
+constexpr int z_stride(int LZ, int nz) {
+    return (nz > ex_words(LZ) ? nz : ex_words(LZ)) | 1;
+}
+// component stride: at least LY * ZS, = 3 mod 8 (FP64) or 5 mod 16 (FP32)
+constexpr int c_stride(int LY, int ZS, bool f32) {
+    return f32 ? LY * ZS + (5 + 16 - LY * ZS % 16) % 16 : LY * ZS + (3 + 8 - LY * ZS % 8) % 8;
+}
+constexpr size_t PLANE_LDS = 163840;   // 160 KB per compute unit
+
+constexpr size_t plane_bytes(int LY, int LZ, int nz, bool f32) {
+    return (size_t)3 * c_stride(LY, z_stride(LZ, nz), f32) * (f32 ? sizeof(float2) : sizeof(double2));
+}
+
+// Lengths with a plane kernel: their product at every occupied extent the
+// padding rule gives them (at most L / 2 on each axis).  z: three components of a column to a thread,
+// up to 144 VGPRs of data, which leaves two wavefronts per SIMD.
+constexpr bool plane_y(int L) { return L == 32 || L == 48 || L == 64 || L == 80 || L == 96 || L == 128; }
+template <typename T> constexpr bool plane_z(int LZ) { return plane_y(LZ) && z_vgprs<T>(LZ) <= 144; }
+// pairs whose plane fits with the largest occupied z extent, LZ / 2
+template <typename T> constexpr bool plane_pair(int LY, int LZ) {
+    return plane_y(LY) && plane_z<T>(LZ) && plane_bytes(LY, LZ, LZ / 2, sizeof(T) == 4) <= PLANE_LDS;
+}
+
+// Wavefronts per workgroup: one per group of z columns a wavefront takes at
+// once, at most eight (two per SIMD at the registers the z stage holds).
+// Measured exceptions, both sides in us per launch on this card: FP64 48 x
+// 32, whose 39 KB let four workgroups share a compute unit, two (308 against
+// 346 with three, 128 right-hand sides); FP32 96 x 64 and 96 x 128, twelve at
+// three per SIMD (25.1 against 26.0 and 44.6 against 49.2 with eight, two
+// right-hand sides); FP32 with LZ = 80, eight for the y lines (181 against
+// 193 with five, 80 x 80, twenty right-hand sides).
+template <typename T> constexpr int plane_waves(int LY, int LZ) {
+    const int nz = LY * (LZ / ct_split(LZ)) / 64;   // groups of z columns
+    if (sizeof(T) == 8) return (LZ == 32 && nz == 3) ? 2 : (nz < 8 ? nz : 8);
+    if (nz == 12) return 12;
+    if (LZ == 80) return 8;
+    return nz < 8 ? nz : 8;
+}
+// wavefronts per SIMD asked of the compiler: three where it needs no
+// spilling for them (FP32, at most 72 VGPRs of data)
+template <typename T> constexpr int plane_occ(int LY, int LZ) {
+    return sizeof(T) == 4 && (plane_waves<T>(LY, LZ) == 12 || (plane_waves<T>(LY, LZ) <= 4 && z_vgprs<T>(LZ) <= 72)) ? 3 : 2;
+}
+
+// Orders the LDS accesses of one wavefront for the compiler (the hardware
+// executes them in order).
+__device__ __forceinline__ void wave_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// One-dimensional launch: workgroup b runs on XCD b % 8 (round-robin), which
+// takes one run of kx and its mirror run (they share tensor rows), every
+// right-hand side in turn; neighbouring kx share cache lines of the grid,
+// which then meet in that XCD's L2.  Grids whose x extent does not split
+// that way give each XCD one contiguous run.
+__device__ __forceinline__ bool plane_tile(int Mx, int& kx, int& q) {
+    const int j = blockIdx.x % passes::N_XCD, local = blockIdx.x / passes::N_XCD;
+    if (Mx % (2 * passes::N_XCD) == 0) {
+        const int W = Mx / (2 * passes::N_XCD);
+        const int i = local % (2 * W);
+        q = local / (2 * W);
+        kx = i < W ? j * W + i : Mx - (j + 1) * W + (i - W);
+        return true;
+    }
+    const int nt = (Mx + passes::N_XCD - 1) / passes::N_XCD;
+    q = local / nt;
+    kx = j * nt + local % nt;
+    return kx < Mx;
+}
+inline unsigned plane_grid(int Mx, int nrhs) {
+    return (unsigned)(passes::N_XCD * ((Mx + passes::N_XCD - 1) / passes::N_XCD)) * (unsigned)nrhs;
+}
+
+// gp: the tensor octant as [Hx][Hz][6][plane_row(LY)] (lanes over ky read
+// consecutive values, rows on cache-line boundaries).
+template <typename T, int LY, int LZ, int NTHR, int WV>
+__global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(WV))) void k_plane(Geo g, typename V2<T>::t* grid, const double2* tw64,
+                                               const typename V2<T>::t* gp, const RhsState* st, int chk, int ZS,
+                                               int CS) {
+    using C = typename V2<T>::t;
+    constexpr int PY = ct_split(LY), QY = LY / PY;
+    constexpr int PZ = ct_split(LZ), QZ = LZ / PZ;
+    constexpr int LPW = 64 / QY;             // y lines per wavefront
+    constexpr int CPW = 64 / QZ;             // z columns per wavefront
+    constexpr int NW = NTHR / 64;
+    constexpr int FG = ex_group(LZ);
+    static_assert(LY % CPW == 0, "whole wavefronts of columns");
+    extern __shared__ __align__(16) unsigned char smem[];
+    C* lds = (C*)smem;
+    const int Mx = g.M[0];
+    int kx, q;
+    if (!plane_tile(Mx, kx, q)) return;
+    if (passes::skip_rhs(st + q, chk)) return;
+    int ny = g.n[1], nz = g.n[2];
+    if (g.rg) {   // ragged batch: this right-hand side's target
+        const RhsGeo& r = g.rg[q];
+        ny = r.n[1];
+        nz = r.n[2];
+        gp = (const C*)r.gplane[sizeof(C) == sizeof(float2) ? 1 : 0];
+    }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const auto* twy = tw_table<T>(g, tw64) + g.ax[1].tw;
+    const auto* twz = tw_table<T>(g, tw64) + g.ax[2].tw;
+    C* gq = grid + (long long)q * g.npts * 3 + (long long)kx * 3;
+    const int nlines = 3 * nz;
+    const int yt = lane / LPW;
+    const long long ys = (long long)Mx * 3;
+
+    // ---- y forward: line (z, c3), lanes yt = 0 .. QY-1
+    for (int l0 = wave * LPW; l0 < nlines; l0 += NW * LPW) {
+        const int ln = l0 + lane % LPW;
+        const int z = ln / 3, c3 = ln % 3;
+        const bool live = ln < nlines;
+        const C* src = gq + (long long)z * LY * ys + c3;
+        C v[1][PY];
+#pragma unroll
+        for (int m = 0; m < PY; ++m) {
+            const int e = yt + QY * m;
+            if (2 * m < PY && live && e < ny) {
+                v[0][m] = src[(long long)e * ys];
+            } else {
+                v[0][m].x = 0;
+                v[0][m].y = 0;
+            }
+        }
+        rf_group_a<T, -1, LY, true, 1>(v, twy);
+        C* row = lds + c3 * CS + z;
+        if (live) {
+#pragma unroll
+            for (int f = 0; f < PY; ++f) row[(yt * PY + f) * ZS] = v[0][f];
+        }
+        wave_fence();
+        if (live) {
+#pragma unroll
+            for (int c = 0; c < PY / QY; ++c) {
+#pragma unroll
+                for (int jj = 0; jj < QY; ++jj) v[0][c * QY + jj] = row[(jj * PY + yt + QY * c) * ZS];
+            }
+        }
+        wave_fence();
+        rf_group_b<T, -1, LY, false, 1>(v, yt, twy);
+        if (live) {
+#pragma unroll
+            for (int c = 0; c < PY / QY; ++c) {
+#pragma unroll
+                for (int gg = 0; gg < QY; ++gg) row[(yt + QY * c + PY * gg) * ZS] = v[0][c * QY + gg];
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- z forward, tensor product, z inverse: column ky, lanes zt
+    const int zt = lane / CPW;
+    // LDS offset of the values (j, f = zt + QZ c) this lane reads in an exchange
+    int rd[PZ / QZ];
+#pragma unroll
+    for (int c = 0; c < PZ / QZ; ++c) {
+        const int f = zt + QZ * c;
+        rd[c] = (f / FG) * CS + (f % FG) * QZ;
+    }
+    constexpr int HY = plane_row(LY), Hz = LZ / 2 + 1;
+    for (int c0 = wave * CPW; c0 < LY; c0 += NW * CPW) {
+        const int cy = c0 + lane % CPW;
+        // the upper half in mirrored order: its tensor rows then ascend with
+        // the lane, as the lower half's do
+        const bool uy = cy > LY / 2;
+        const int fy = uy ? cy - LY / 2 : cy;
+        const int ky = uy ? LY - fy : cy;
+        C* cb = lds + ky * ZS;
+        C v[3][PZ];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+#pragma unroll
+            for (int m = 0; m < PZ; ++m) {
+                const int e = zt + QZ * m;
+                if (2 * m < PZ && e < nz) {
+                    v[a][m] = cb[a * CS + e];
+                } else {
+                    v[a][m].x = 0;
+                    v[a][m].y = 0;
+                }
+            }
+        }
+        wave_fence();
+        auto exchange = [&]() {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+#pragma unroll
+                for (int f = 0; f < PZ; ++f) cb[(f / FG) * CS + (f % FG) * QZ + zt] = v[a][f];
+                wave_fence();
+#pragma unroll
+                for (int c = 0; c < PZ / QZ; ++c) {
+#pragma unroll
+                    for (int jj = 0; jj < QZ; ++jj) v[a][c * QZ + jj] = cb[rd[c] + jj];
+                }
+                wave_fence();
+            }
+        };
+        rf_group_a<T, -1, LZ, true, 3>(v, twz);
+        exchange();
+        rf_group_b<T, -1, LZ, false, 3>(v, zt, twz);
+        {
+            // y_a = sum_b Ghat_ab x_b at (kx, ky, kz = zt + QZ c + PZ gg): the
+            // stored octant and the parities (diagonal even, ab odd in a and b)
+            const bool ux = kx > Mx / 2;
+            const int fx = ux ? Mx - kx : kx;
+            const C* gx = gp + (long long)fx * Hz * 6 * HY + fy;
+            const bool f1 = ux != uy;
+#pragma unroll
+            for (int c = 0; c < PZ / QZ; ++c) {
+#pragma unroll
+                for (int gg = 0; gg < QZ; ++gg) {
+                    const int kz = zt + QZ * c + PZ * gg;
+                    const bool uz = kz > LZ / 2;
+                    const int fz = uz ? LZ - kz : kz;
+                    const C* Gp = gx + fz * 6 * HY;
+                    C G6[6];
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) G6[k] = Gp[k * HY];
+                    const bool f2 = ux != uz, f4 = uy != uz;
+                    G6[1].x = f1 ? -G6[1].x : G6[1].x;
+                    G6[1].y = f1 ? -G6[1].y : G6[1].y;
+                    G6[2].x = f2 ? -G6[2].x : G6[2].x;
+                    G6[2].y = f2 ? -G6[2].y : G6[2].y;
+                    G6[4].x = f4 ? -G6[4].x : G6[4].x;
+                    G6[4].y = f4 ? -G6[4].y : G6[4].y;
+                    const int sl = c * QZ + gg;
+                    const C X = v[0][sl], Y = v[1][sl], Z = v[2][sl];
+                    v[0][sl] = passes::trow(G6[0], G6[1], G6[2], X, Y, Z);
+                    v[1][sl] = passes::trow(G6[1], G6[3], G6[4], X, Y, Z);
+                    v[2][sl] = passes::trow(G6[2], G6[4], G6[5], X, Y, Z);
+                }
+            }
+        }
+        // back to subsequences: X[kappa_c + P g] = X[zt + Q m], m = c + (P / Q) g
+        {
+            C w[3][PZ];
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+#pragma unroll
+                for (int c = 0; c < PZ / QZ; ++c) {
+#pragma unroll
+                    for (int gg = 0; gg < QZ; ++gg) w[a][c + (PZ / QZ) * gg] = v[a][c * QZ + gg];
+                }
+            }
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+#pragma unroll
+                for (int m = 0; m < PZ; ++m) v[a][m] = w[a][m];
+            }
+        }
+        rf_group_a<T, 1, LZ, false, 3>(v, twz);
+        exchange();
+        rf_group_b<T, 1, LZ, true, 3>(v, zt, twz);
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+#pragma unroll
+            for (int c = 0; c < PZ / QZ; ++c) {
+#pragma unroll
+                for (int gg = 0; gg < QZ / 2; ++gg) {
+                    const int e = zt + QZ * c + PZ * gg;
+                    if (e < nz) cb[a * CS + e] = v[a][c * QZ + gg];
+                }
+            }
+        }
+        wave_fence();
+    }
+    __syncthreads();
+
+    // ---- y inverse, y < ny stored
+    for (int l0 = wave * LPW; l0 < nlines; l0 += NW * LPW) {
+        const int ln = l0 + lane % LPW;
+        const int z = ln / 3, c3 = ln % 3;
+        const bool live = ln < nlines;
+        C* row = lds + c3 * CS + z;
+        C v[1][PY];
+#pragma unroll
+        for (int m = 0; m < PY; ++m) {
+            if (live) {
+                v[0][m] = row[(yt + QY * m) * ZS];
+            } else {
+                v[0][m].x = 0;
+                v[0][m].y = 0;
+            }
+        }
+        wave_fence();
+        rf_group_a<T, 1, LY, false, 1>(v, twy);
+        if (live) {
+#pragma unroll
+            for (int f = 0; f < PY; ++f) row[(yt * PY + f) * ZS] = v[0][f];
+        }
+        wave_fence();
+        if (live) {
+#pragma unroll
+            for (int c = 0; c < PY / QY; ++c) {
+#pragma unroll
+                for (int jj = 0; jj < QY; ++jj) v[0][c * QY + jj] = row[(jj * PY + yt + QY * c) * ZS];
+            }
+        }
+        rf_group_b<T, 1, LY, true, 1>(v, yt, twy);
+        C* dst = gq + (long long)z * LY * ys + c3;
+        if (live) {
+#pragma unroll
+            for (int c = 0; c < PY / QY; ++c) {
+#pragma unroll
+                for (int gg = 0; gg < QY / 2; ++gg) {
+                    const int e = yt + QY * c + PY * gg;
+                    if (e < ny) dst[(long long)e * ys] = v[0][c * QY + gg];
+                }
+            }
+        }
+    }
+}
+
+// ------------------------------------------------------------------ launcher
+
+template <typename T, int LY, int LZ>
+bool plane_launch(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, const double2* tw,
+                  const typename V2<T>::t* gp, const RhsState* st, hipStream_t s) {
+    if constexpr (plane_pair<T>(LY, LZ)) {
+        constexpr int NTHR = 64 * plane_waves<T>(LY, LZ);
+        const int ZS = z_stride(LZ, g.n[2]), CS = c_stride(LY, ZS, sizeof(T) == 4);
+        DDA_LAUNCH((k_plane<T, LY, LZ, NTHR, plane_occ<T>(LY, LZ)>), dim3(plane_grid(g.M[0], nrhs)), dim3(NTHR),
+                   plane_bytes(LY, LZ, g.n[2], sizeof(T) == 4), s, g, grid, tw, gp, st, chk, ZS, CS);
+        return true;
+    }
+    return false;
+}
+
+template <typename T, int LY>
+bool plane_launch_z(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, const double2* tw,
+                    const typename V2<T>::t* gp, const RhsState* st, hipStream_t s) {
+    switch (g.M[2]) {
+#define DDA_Z(L) \
+    case L: return plane_launch<T, LY, L>(chk, g, nrhs, grid, tw, gp, st, s);
+        DDA_Z(32) DDA_Z(48) DDA_Z(64) DDA_Z(80) DDA_Z(96) DDA_Z(128)
+#undef DDA_Z
+        default: return false;
+    }
+}
+
+}  // namespace plane
+
+template <typename T>
+void launch_plane(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, const double2* tw,
+                  const typename V2<T>::t* gp, const RhsState* st, hipStream_t s) {
+    bool done = false;
+    switch (g.M[1]) {
+#define DDA_Y(L) \
+    case L: done = plane::plane_launch_z<T, L>(chk, g, nrhs, grid, tw, gp, st, s); break;
+        DDA_Y(32) DDA_Y(48) DDA_Y(64) DDA_Y(80) DDA_Y(96) DDA_Y(128)
+#undef DDA_Y
+        default: break;
+    }
+    if (!done) throw std::invalid_argument("no plane kernel for this grid");
+}
+
+// Whether launch_plane takes this grid: a compiled pair of lengths whose
+// plane, with the occupied z extent, fits the LDS, and a launch within the
+// grid limit.
+template <typename T> bool plane_fits(const Geo& g, int nrhs) {
+    if (!plane::plane_pair<T>(g.M[1], g.M[2]) || 2 * g.n[1] > g.M[1] || 2 * g.n[2] > g.M[2]) return false;
+    return (long long)(g.M[0] + passes::N_XCD) * nrhs * 768 < (1LL << 32);
+}
+
+#define DDA_INSTANTIATE_PLANE(T)                                                                                \
+    template void launch_plane<T>(int, const Geo&, int, V2<T>::t*, const double2*, const V2<T>::t*,              \
+                                  const RhsState*, hipStream_t);                                                \
+    template bool plane_fits<T>(const Geo&, int);
+
+}  // namespace dda

@@ -1,0 +1,6 @@
+// The plane kernel on FP64 grids (templates in dda_plane.h).
+#include "dda_plane.h"
+
+namespace dda {
+DDA_INSTANTIATE_PLANE(double)
+}

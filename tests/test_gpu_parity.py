@@ -1409,3 +1409,25 @@ def test_qmr_breakdown_is_reported(dda):
     assert r[0]["status"] == 0 and r[0]["restarts"] == 0
     ref = np.linalg.solve(A, b.reshape(-1)).reshape(-1, 3)
     assert np.abs(x.cpu().numpy()[0] - ref).max() <= 1e-8 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_matvec"])
+@pytest.mark.parametrize("ny", [11, 16, 17, 24, 25, 32, 33, 40, 41, 48, 49, 64])
+def test_plane_kernel_equals_the_three_passes(dda, precision, ny):
+    """Every pair of compiled (y, z) lengths at the smallest and largest box
+    extents that pad to it (and x extents with a runtime-planned and a
+    compile-time length): the product of the fused plane kernel is bitwise
+    that of the three separate passes, which a named variant selects."""
+    for nz in (11, 16, 17, 24, 25, 32, 33, 40, 41, 48, 49, 64):
+        nx = 3 if (ny + nz) % 2 else 19
+        rng = np.random.default_rng(1000 * ny + nz)
+        keep = rng.random((nx, ny, nz)) < 0.1
+        keep[0, 0, 0] = keep[-1, -1, -1] = True
+        ijk = np.argwhere(keep).astype(np.int32)
+        tgt = dda.Target(ijk, 1.4 + 0.1j)
+        assert tgt.box == (nx, ny, nz)
+        kh, e0 = w.along_x_yz()
+        xv = _cuda(w.random_vectors(31, (2, len(ijk), 3)))
+        y = dda.apply(tgt, dda.Options.for_size_parameter(2.0, precision=precision), kh, e0, xv)
+        ref = dda.apply(tgt, dda.Options.for_size_parameter(2.0, precision=precision, kernel_variant=4), kh, e0, xv)
+        assert torch.equal(y, ref), (nx, ny, nz)
