@@ -743,18 +743,14 @@ void ensure_green(dda_ctx* c, dda_target* t, double kd, bool fp32, bool force) {
     const bool fresh = force || t->green_kd != kd;
     if (!fresh && (fp32 ? t->have32 : t->have64)) return;
     const Geo& g = t->geo;
-    double2* G = (double2*)c->gtmp.ensure((size_t)g.npts * 6 * sizeof(double2));
     const double2* tw = (const double2*)t->tw.p;
     Timed tm(c, T_GREEN, c->stream);
-    launch_green_sample(g, kd, G, c->stream);
-    launch_xgrid3(g, G, tw, c->stream);
-    launch_strided<double>(1, -1, CHK_NONE, g, 2, 3, g.M[2], g.M[1], g.M[1], G, tw, nullptr, nullptr, c->stream);
-    launch_strided<double>(2, -1, CHK_NONE, g, 2, 3, g.M[1], g.M[2], g.M[2], G, tw, nullptr, nullptr, c->stream);
     const size_t nh = (size_t)g.H[0] * g.H[1] * g.H[2] * 6;
     if (fresh) t->have64 = t->have32 = false;
+    double2* work = (double2*)c->gtmp.ensure(green_work_values(g) * sizeof(double2));
     double2* g64 = (double2*)t->gh64.ensure(nh * sizeof(double2));
     float2* g32 = fp32 ? (float2*)t->gh32.ensure(nh * sizeof(float2)) : nullptr;
-    launch_green_octant(g, G, g64, g32, c->stream);
+    launch_green(g, kd, work, g64, g32, tw, c->stream);
     // the plane kernel's layout, where it takes this grid (with any number of
     // right-hand sides; launch limits are checked with the product)
     const bool p64 = plane_fits<double>(g, 1), p32 = fp32 && plane_fits<float>(g, 1);

@@ -195,13 +195,11 @@ constexpr int plane_row(int LY) { return (LY / 2 + 1 + 7) & ~7; }
 inline size_t plane_values(const Geo& g) { return (size_t)g.H[0] * g.H[2] * 6 * plane_row(g.M[1]); }
 // the octant in that layout from the octant itself (either output may be null)
 void launch_green_plane(const Geo& g, const double2* gh64, double2* gp64, float2* gp32, hipStream_t s);
-// The interaction tensor on the padded grid is held as two three-component
-// slabs [2][npts][3]: (xx, xy, xz) and (yy, yz, zz), so that its transforms
-// run as the three-component passes with two right-hand sides.
-void launch_xgrid3(const Geo& g, double2* grid, const double2* tw, hipStream_t s);
-
-void launch_green_sample(const Geo& g, double kd, double2* G, hipStream_t s);
-void launch_green_octant(const Geo& g, const double2* G, double2* gh64, float2* gh32, hipStream_t s);
+// The FFT octant of the interaction tensor at kd into gh64 and, where given,
+// gh32, [Hz][Hy][Hx][6] (dda_green.hip); work: green_work_values(g) values.
+size_t green_work_values(const Geo& g);
+void launch_green(const Geo& g, double kd, double2* work, double2* gh64, float2* gh32, const double2* tw,
+                  hipStream_t s);
 // 1/alpha (scheme + 2: its derivative in eps) per (right-hand side, material)
 // from the target's distinct refractive indices mats [nmat] and the ambient
 // medium's index

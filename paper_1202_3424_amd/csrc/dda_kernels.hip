@@ -1,5 +1,5 @@
 // HIP kernels of the DDA solve for gfx950, other than the matvec passes
-// (dda_passes.h): the interaction-tensor sampling and its FFT, 1/alpha,
+// (dda_passes.h) and the interaction tensor (dda_green.hip): 1/alpha,
 // E_inc, the BiCGSTAB updates and their reductions, the efficiency sums, the
 // adjoint right-hand side and gradient, and small utilities.
 #include <stdexcept>
@@ -24,125 +24,7 @@ template <typename C> __device__ __forceinline__ double2 to_d(C u) {
 __device__ __forceinline__ bool finite2(double2 a) { return isfinite(a.x) && isfinite(a.y); }
 
 
-__host__ __device__ inline int pad_len(int L) { return L | 1; }
-template <typename C> __host__ inline size_t fft_smem(int L, int nlines) {
-    return ((size_t)((L + 1) & ~1) + (size_t)nlines * pad_len(L)) * sizeof(C) + 8 * (NT / 64) * sizeof(double) + 64;
-}
-
-// Forward FFT along x of every line of a two-slab three-component FP64 grid
-// (the interaction tensor; slab = grid z).
-__global__ __launch_bounds__(NT) void k_xgrid3(Geo g, double2* grid, const double2* tw64, int XL) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int Mx = g.M[0], My = g.M[1];
-    const int z = blockIdx.y;
-    const int y0 = blockIdx.x * XL;
-    const int nl = min(XL, My - y0);
-    const int nlines = 3 * nl;
-    const int Lp = pad_len(Mx);
-    double2* tws = (double2*)smem;
-    double2* lds = tws + ((Mx + 1) & ~1);
-    load_twiddles<double>(tws, tw64, g.ax[0]);
-    double2* gq = grid + (long long)blockIdx.z * g.npts * 3 + ((long long)z * My + y0) * Mx * 3;
-    const int tot = nl * Mx * 3;
-    for (int idx = threadIdx.x; idx < tot; idx += NT) {
-        const int c = idx % 3;
-        const int rest = idx / 3;
-        const int e = rest % Mx;
-        const int yo = rest / Mx;
-        lds[(yo * 3 + c) * Lp + e] = gq[idx];
-    }
-    __syncthreads();
-    fft_lines<double, -1>(lds, tws, nlines, Lp, g.ax[0]);
-    for (int idx = threadIdx.x; idx < tot; idx += NT) {
-        const int c = idx % 3;
-        const int rest = idx / 3;
-        const int e = rest % Mx;
-        const int yo = rest / Mx;
-        gq[idx] = lds[(yo * 3 + c) * Lp + e];
-    }
-}
-
 // ------------------------------------------------------------------ setup
-
-// Signed lattice separation held by padded index m on an axis of box extent
-// n and padded extent M; false for the empty slots between +(n-1) and -(n-1).
-__device__ __forceinline__ bool sep(int m, int n, int M, int& d) {
-    if (m <= n - 1) { d = m; return true; }
-    if (m >= M - (n - 1)) { d = m - M; return true; }
-    return false;
-}
-
-// Off-diagonal interaction tensor (Draine 1988) sampled at every separation:
-// A_jl = exp(ikr)/r [k^2 (nn - I) + (ikr - 1)/r^2 (3nn - I)], stored as its six
-// distinct components xx, xy, xz, yy, yz, zz; zero at R = 0 and empty slots.
-__global__ __launch_bounds__(NT) void k_green_sample(Geo g, double kd, double2* G) {
-    const long long i = (long long)blockIdx.x * NT + threadIdx.x;
-    if (i >= g.npts) return;
-    const int Mx = g.M[0], My = g.M[1], Mz = g.M[2];
-    const int mx = (int)(i % Mx);
-    const int my = (int)((i / Mx) % My);
-    const int mz = (int)(i / ((long long)Mx * My));
-    int dx, dy, dz;
-    // component c in slab c / 3, position c % 3
-    double2* out0 = G + i * 3;
-    double2* out1 = G + (g.npts + i) * 3;
-    const bool ok = sep(mx, g.n[0], Mx, dx) && sep(my, g.n[1], My, dy) && sep(mz, g.n[2], Mz, dz);
-    if (!ok || (dx == 0 && dy == 0 && dz == 0)) {
-        for (int c = 0; c < 3; ++c) out0[c] = out1[c] = double2{0.0, 0.0};
-        return;
-    }
-    const double X = dx, Y = dy, Z = dz;
-    const double r2 = X * X + Y * Y + Z * Z;
-    const double r = sqrt(r2);
-    double sn, cs;
-    sincos(kd * r, &sn, &cs);
-    const double2 pref = {cs / r, sn / r};                       // exp(ikr)/r
-    const double2 ikr1 = {-1.0 / r2, kd * r / r2};               // (ikr - 1)/r^2
-    // A = pref [ (-k^2 - (ikr-1)/r^2) I + (k^2 + 3(ikr-1)/r^2) R R / r^2 ]
-    const double2 ciso = cmul(pref, double2{-kd * kd - ikr1.x, -ikr1.y});
-    const double2 cnn = cscale(cmul(pref, double2{kd * kd + 3.0 * ikr1.x, 3.0 * ikr1.y}), 1.0 / r2);
-    const double R[3] = {X, Y, Z};
-    const int ab[6][2] = {{0, 0}, {0, 1}, {0, 2}, {1, 1}, {1, 2}, {2, 2}};
-    for (int c = 0; c < 6; ++c) {
-        double2 v = cscale(cnn, R[ab[c][0]] * R[ab[c][1]]);
-        if (ab[c][0] == ab[c][1]) v = cadd(v, ciso);
-        (c < 3 ? out0 : out1)[c % 3] = v;
-    }
-}
-
-// Keep the octant 0..M/2 of the tensor FFT, scaled by 1/M so that the
-// inverse transforms of the product need no further normalisation.
-__global__ __launch_bounds__(NT) void k_green_octant(Geo g, const double2* G, double2* gh64, float2* gh32) {
-    const long long nh = (long long)g.H[0] * g.H[1] * g.H[2];
-    const long long i = (long long)blockIdx.x * NT + threadIdx.x;
-    if (i >= nh) return;
-    const int hx = (int)(i % g.H[0]);
-    const int hy = (int)((i / g.H[0]) % g.H[1]);
-    const int hz = (int)(i / ((long long)g.H[0] * g.H[1]));
-    const long long src = (((long long)hz * g.M[1] + hy) * g.M[0] + hx) * 3;
-    const double sc = 1.0 / (double)g.npts;
-    for (int c = 0; c < 6; ++c) {
-        const double2 v = cscale(G[(c < 3 ? 0 : g.npts * 3) + src + c % 3], sc);
-        if (gh64) gh64[i * 6 + c] = v;
-        if (gh32) gh32[i * 6 + c] = float2{(float)v.x, (float)v.y};
-    }
-}
-
-// The octant as [Hx][Hz][6][plane_row(My)] for the plane kernel, the padding
-// of a row zero.
-__global__ __launch_bounds__(NT) void k_green_plane(Geo g, const double2* gh64, double2* gp64, float2* gp32) {
-    const int hyp = plane_row(g.M[1]);
-    const long long i = (long long)blockIdx.x * NT + threadIdx.x;
-    if (i >= (long long)g.H[0] * g.H[2] * 6 * hyp) return;
-    const int hy = (int)(i % hyp);
-    const int c = (int)(i / hyp % 6);
-    const int hz = (int)(i / (6LL * hyp) % g.H[2]);
-    const int hx = (int)(i / (6LL * hyp * g.H[2]));
-    double2 v = {0.0, 0.0};
-    if (hy < g.H[1]) v = gh64[(((long long)hz * g.H[1] + hy) * g.H[0] + hx) * 6 + c];
-    if (gp64) gp64[i] = v;
-    if (gp32) gp32[i] = float2{(float)v.x, (float)v.y};
-}
 
 // 1/alpha (or its derivative with respect to eps, scheme + 2) per
 // (right-hand side, material): "Dipole Polarizabilities".
@@ -1169,27 +1051,6 @@ int strided_cols_per_tile(int L, int nc, bool fp32) {
     int p = 1;
     while (p * 2 <= tx && p * 2 <= 16) p *= 2;
     return p;
-}
-
-void launch_xgrid3(const Geo& g, double2* grid, const double2* tw, hipStream_t s) {
-    int XL = Tile<double>::EMAX / (3 * g.M[0]);
-    if (XL < 1) throw std::invalid_argument("x extent above the LDS line tile");
-    dim3 grd((g.M[1] + XL - 1) / XL, g.M[2], 2);
-    hipLaunchKernelGGL(k_xgrid3, grd, dim3(NT), fft_smem<double2>(g.M[0], 3 * XL), s, g, grid, tw, XL);
-}
-
-void launch_green_sample(const Geo& g, double kd, double2* G, hipStream_t s) {
-    hipLaunchKernelGGL(k_green_sample, dim3((unsigned)((g.npts + NT - 1) / NT)), dim3(NT), 0, s, g, kd, G);
-}
-
-void launch_green_octant(const Geo& g, const double2* G, double2* gh64, float2* gh32, hipStream_t s) {
-    const long long nh = (long long)g.H[0] * g.H[1] * g.H[2];
-    hipLaunchKernelGGL(k_green_octant, dim3((unsigned)((nh + NT - 1) / NT)), dim3(NT), 0, s, g, G, gh64, gh32);
-}
-
-void launch_green_plane(const Geo& g, const double2* gh64, double2* gp64, float2* gp32, hipStream_t s) {
-    const long long n = (long long)plane_values(g);
-    hipLaunchKernelGGL(k_green_plane, dim3((unsigned)((n + NT - 1) / NT)), dim3(NT), 0, s, g, gh64, gp64, gp32);
 }
 
 void launch_alpha(int nrhs, int nmat, const double2* mats, double m_medium, const double* khat, const double2* e0,

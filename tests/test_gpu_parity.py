@@ -1431,3 +1431,25 @@ def test_plane_kernel_equals_the_three_passes(dda, precision, ny):
         y = dda.apply(tgt, dda.Options.for_size_parameter(2.0, precision=precision), kh, e0, xv)
         ref = dda.apply(tgt, dda.Options.for_size_parameter(2.0, precision=precision, kernel_variant=4), kh, e0, xv)
         assert torch.equal(y, ref), (nx, ny, nz)
+
+
+@pytest.mark.parametrize("box", [(1, 1, 2), (1, 7, 13), (13, 1, 9), (2, 3, 1), (10, 5, 33), (11, 24, 3), (49, 2, 17),
+                                 (3, 65, 4)])
+def test_tensor_octant_over_odd_and_padded_extents(dda, box):
+    """The tensor FFT at extents of one site, odd (M = 2n - 1), even and
+    over-padded grid extents on each axis: the product of a scattered handful
+    of sites against the dense matrix (1e-12)."""
+    rng = np.random.default_rng(sum(box))
+    keep = rng.random(box) < min(1.0, 60.0 / np.prod(box))
+    keep[0, 0, 0] = keep[-1, -1, -1] = True
+    ijk = np.argwhere(keep).astype(np.int32)
+    n = len(ijk)
+    m = np.full(n, 1.5 + 0.2j)
+    tgt = dda.Target(ijk, m)
+    assert tgt.box == box
+    kh, e0 = w.along_x_yz()
+    xv = w.random_vectors(8, (2, n, 3))
+    y = dda.apply(tgt, dda.Options.for_size_parameter(0.8), kh, e0, _cuda(xv)).cpu().numpy()
+    for q in range(2):
+        ref = (_dense_A(ijk, m, 0.8, kh[q], e0[q], "LATTDR") @ xv[q].reshape(-1)).reshape(n, 3)
+        assert np.abs(y[q] - ref).max() <= 1e-12 * np.abs(ref).max()
