@@ -1744,7 +1744,7 @@ dda_status dda_ctx_destroy(dda_ctx* c) {
                 delete ws;
             }
             c->main.release();
-            for (DevBuf* b : {&c->dainv, &c->aux, &c->gtmp}) b->release();
+            for (DevBuf* b : {&c->dainv, &c->aux, &c->gtmp, &c->ffbuf}) b->release();
             for (const auto& p : c->pending) {
                 (void)hipEventDestroy(p.a);
                 (void)hipEventDestroy(p.b);
@@ -2016,6 +2016,34 @@ dda_status dda_ctx_tuned_variants(dda_ctx* c, const dda_target* t, int32_t n_rhs
     });
 }
 
+}  // extern "C"
+
+namespace {
+// Work memory and launches of the far field of nrhs solutions P (caller
+// order) over nd directions: one list for all (dstride 0) or a set for each
+// (dstride nd).
+size_t far_bytes(const dda_target* t, int nrhs, int nd) {
+    return far_lines(t->nsites, t->geo.n) ? far_lines_bytes(t->geo.n, nrhs, nd)
+                                          : (size_t)nrhs * 3 * t->nsites * sizeof(double2);
+}
+void far_launch(const dda_target* t, int nrhs, const dda_c64* P, const double* dirs, int nd, int dstride, double kd,
+                void* work, double2* f, double* dcs, hipStream_t s) {
+    if (far_lines(t->nsites, t->geo.n)) {
+        launch_far_lines((const int*)t->map.p, (const int*)t->perm.p, (const double2*)P, 3LL * t->nsites, nrhs, dirs,
+                         nd, dstride, kd, t->lo, t->geo.n, work, f, dcs, s);
+        return;
+    }
+    double2* Ps = (double2*)work;
+    launch_permute(nrhs, t->nsites, 3, (const int*)t->perm.p, (const double2*)P, Ps, true, s);
+    if (dstride)
+        launch_farfield_sets(t->nsites, (const int*)t->coords.p, Ps, nrhs, dirs, nd, kd, t->lo, t->geo.n, f, dcs, s);
+    else
+        launch_farfield(t->nsites, (const int*)t->coords.p, Ps, nrhs, dirs, nd, kd, t->lo, t->geo.n, f, dcs, s);
+}
+}  // namespace
+
+extern "C" {
+
 dda_status dda_far_field(dda_ctx* c, dda_target* t, const dda_opts* o, int32_t n_rhs, const dda_c64* P,
                          int32_t n_dir, const double* n_hat, const double* theta_hat, const double* phi_hat,
                          dda_c64* f, double* dcs) {
@@ -2044,18 +2072,14 @@ dda_status dda_far_field(dda_ctx* c, dda_target* t, const dda_opts* o, int32_t n
         }
         Scope sc(c);
         const double kd = kd_of(o, t->nsites);
-        const size_t n3 = 3 * (size_t)t->nsites;
-        const size_t pb = (size_t)n_rhs * n3 * sizeof(double2), db = dirs.size() * sizeof(double);
+        const size_t pb = (far_bytes(t, n_rhs, n_dir) + 15) & ~(size_t)15, db = dirs.size() * sizeof(double);
         const size_t fb = (size_t)n_rhs * n_dir * 2 * sizeof(double2), cb = (size_t)n_rhs * n_dir * sizeof(double);
         char* buf = (char*)c->ffbuf.ensure(pb + db + fb + cb + 256);
-        double2* Ps = (double2*)buf;
-        double* ddev = (double*)(buf + pb);
-        double2* fdev = (double2*)(buf + pb + db);
-        double* cdev = (double*)(buf + pb + db + fb);
+        double2* fdev = (double2*)(buf + pb);
+        double* ddev = (double*)(buf + pb + fb);
+        double* cdev = (double*)(buf + pb + fb + db);
         HIPCHK(hipMemcpyAsync(ddev, dirs.data(), db, hipMemcpyHostToDevice, c->stream));
-        launch_permute(n_rhs, t->nsites, 3, (const int*)t->perm.p, (const double2*)P, Ps, true, c->stream);
-        launch_farfield(t->nsites, (const int*)t->coords.p, Ps, n_rhs, ddev, n_dir, kd, t->lo, t->geo.n, fdev, cdev,
-                        c->stream);
+        far_launch(t, n_rhs, P, ddev, n_dir, 0, kd, buf, fdev, cdev, c->stream);
         HIPCHK(hipGetLastError());
         if (f) HIPCHK(hipMemcpyAsync(f, fdev, fb, hipMemcpyDeviceToHost, c->stream));
         if (dcs) HIPCHK(hipMemcpyAsync(dcs, cdev, cb, hipMemcpyDeviceToHost, c->stream));
@@ -2118,17 +2142,15 @@ dda_status dda_scattering_averages(dda_ctx* c, dda_target* t, const dda_opts* o,
         const int qg = std::max(1, std::min(n_rhs, (1 << 22) / nd));
         const long long ndt = (long long)nd * qg;
         const size_t n3 = 3 * (size_t)t->nsites;
-        const size_t pb = (size_t)n_rhs * n3 * sizeof(double2), db = (size_t)ndt * 9 * sizeof(double);
+        const size_t pb = (far_bytes(t, qg, nd) + 15) & ~(size_t)15, db = (size_t)ndt * 9 * sizeof(double);
         const size_t fb = (size_t)ndt * 2 * sizeof(double2), cb = (size_t)ndt * sizeof(double);
         const size_t kb = (size_t)n_rhs * 3 * sizeof(double), mb = (size_t)n_theta * sizeof(double);
         char* buf = (char*)c->ffbuf.ensure(pb + db + fb + cb + kb + mb + 256);
-        double2* Ps = (double2*)buf;
-        double* ddev = (double*)(buf + pb);
-        double2* fdev = (double2*)(buf + pb + db);
+        double2* fdev = (double2*)(buf + pb);
+        double* ddev = (double*)(buf + pb + fb);
         double* cdev = (double*)(buf + pb + db + fb);
         double* kdev = (double*)(buf + pb + db + fb + cb);
         double* mdev = (double*)(buf + pb + db + fb + cb + kb);
-        launch_permute(n_rhs, t->nsites, 3, (const int*)t->perm.p, (const double2*)P, Ps, true, c->stream);
         HIPCHK(hipMemcpyAsync(kdev, kh.data(), kb, hipMemcpyHostToDevice, c->stream));
         HIPCHK(hipMemcpyAsync(mdev, mu.data(), mb, hipMemcpyHostToDevice, c->stream));
         std::vector<double> dcs((size_t)ndt);
@@ -2137,8 +2159,7 @@ dda_status dda_scattering_averages(dda_ctx* c, dda_target* t, const dda_opts* o,
             // the directions about each right-hand side's incidence direction,
             // formed on the device
             launch_avg_dirs(ng, kdev + 3 * (size_t)g0, mdev, n_theta, n_phi, ddev, c->stream);
-            launch_farfield_sets(t->nsites, (const int*)t->coords.p, Ps + (size_t)g0 * n3, ng, ddev, nd, kd, t->lo,
-                                 t->geo.n, fdev, cdev, c->stream);
+            far_launch(t, ng, P + (size_t)g0 * n3, ddev, nd, nd, kd, buf, fdev, cdev, c->stream);
             HIPCHK(hipGetLastError());
             HIPCHK(hipMemcpyAsync(dcs.data(), cdev, (size_t)ng * nd * sizeof(double), hipMemcpyDeviceToHost, c->stream));
             HIPCHK(hipStreamSynchronize(c->stream));

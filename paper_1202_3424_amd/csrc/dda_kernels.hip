@@ -329,151 +329,6 @@ __global__ __launch_bounds__(NT) void k_b2_update(SiteArgs a) {
     publish_partial<3>(acc, a.partials + (long long)q * a.maxblk * PSTRIDE, blockIdx.x, a.maxblk, sh);
 }
 
-// ------------------------------------------------------------------ far field
-// Scattering amplitudes ("Scattering by Finite Targets: The Mueller Matrix";
-// Draine 1988): per direction n and right-hand side, A = k^3 sum_j P_j
-// exp(-i k n . r_j), then f_1 = theta . A, f_2 = phi . A and the differential
-// cross section (|f_1|^2 + |f_2|^2) / k^2.  dirs holds n, theta, phi per
-// direction.  On the lattice the phase factor separates by axis,
-// exp(-i k n . r) = w_x(x) w_y(y) w_z(z), so one workgroup per direction
-// tabulates the n_x + n_y + n_z factors of its direction in LDS and every
-// term costs two complex products instead of a sine and cosine; the
-// right-hand sides are taken FR at a time over the same factors, and DW
-// directions at a time over the same loaded sites (each site's P is read
-// once for all DW).  per > 0: direction d belongs to right-hand side d / per
-// alone (every right-hand side with its own direction set in one launch;
-// DW divides per) and its results go to entry d; there FR is 1.  Each term
-// is accumulated as four fused multiply-adds in a fixed order.
-// Deterministic sums (each direction: fixed per-thread order, then the
-// workgroup reduction; the same for every DW and FR).
-template <int DW, int FR>
-__global__ __launch_bounds__(NT) void k_farfield(int nsites, const int* coords, const double2* P, long long n3,
-                                                 int nrhs, const double* dirs, double k, int lox, int loy, int loz,
-                                                 int nx, int ny, int nz, double2* f, double* dcs, int ndir,
-                                                 int per) {
-    extern __shared__ double2 wtab[];     // [DW][nx + ny + nz] phase factors of the group's directions
-    __shared__ double sh[6 * FR * NT / 64];   // block_sum scratch: one value per wave and sum
-    const int d0 = blockIdx.x * DW;
-    const int nt = nx + ny + nz;
-    for (int i = threadIdx.x; i < DW * nt; i += NT) {
-        const int j = i / nt, ii = i % nt;
-        const int d = min(d0 + j, ndir - 1);   // past the end: a copy of the last direction, not stored
-        const double* dv = dirs + (long long)d * 9;
-        const int a = ii < nx ? 0 : (ii < nx + ny ? 1 : 2);
-        const int c = a == 0 ? lox + ii : (a == 1 ? loy + (ii - nx) : loz + (ii - nx - ny));
-        double sn, cs;
-        sincos(-k * dv[a] * c, &sn, &cs);
-        wtab[i] = double2{cs, sn};
-    }
-    __syncthreads();
-    const double k3 = k * k * k;
-    // per = 0: the right-hand sides FR at a time along the grid's y
-    const int qa = per > 0 ? d0 / per : (int)blockIdx.y * FR;
-    const int qb = per > 0 ? qa + 1 : min(nrhs, qa + FR);
-    for (int q0 = qa; q0 < qb; q0 += FR) {
-        double acc[DW][6 * FR];
-#pragma unroll
-        for (int j = 0; j < DW; ++j)
-#pragma unroll
-            for (int i = 0; i < 6 * FR; ++i) acc[j][i] = 0.0;
-        // a thread's sites s, s + NT, s + 2 NT, ... in that order, two per
-        // iteration with both sites' loads issued first
-        for (int s0 = threadIdx.x; s0 < nsites; s0 += 2 * NT) {
-            int cc[2][3];
-            double2 pv[2][FR][3];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int s = min(s0 + h * NT, nsites - 1);   // past the end: loaded, not added
-                cc[h][0] = coords[s * 3 + 0] - lox;
-                cc[h][1] = nx + coords[s * 3 + 1] - loy;
-                cc[h][2] = nx + ny + coords[s * 3 + 2] - loz;
-#pragma unroll
-                for (int r = 0; r < FR; ++r) {
-                    const double2* Pq = P + (long long)(q0 + r) * n3 + (long long)s * 3;
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) pv[h][r][c] = q0 + r < qb ? Pq[c] : double2{0.0, 0.0};
-                }
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (h == 1 && s0 + NT >= nsites) break;
-#pragma unroll
-                for (int j = 0; j < DW; ++j) {
-                    const double2* wt = wtab + j * nt;
-                    const double2 w = cmul(cmul(wt[cc[h][0]], wt[cc[h][1]]), wt[cc[h][2]]);
-#pragma unroll
-                    for (int r = 0; r < FR; ++r) {
-#pragma unroll
-                        for (int c = 0; c < 3; ++c) {
-                            double& ar = acc[j][6 * r + 2 * c];
-                            double& ai = acc[j][6 * r + 2 * c + 1];
-                            ar = fma(pv[h][r][c].x, w.x, ar);
-                            ar = fma(-pv[h][r][c].y, w.y, ar);
-                            ai = fma(pv[h][r][c].x, w.y, ai);
-                            ai = fma(pv[h][r][c].y, w.x, ai);
-                        }
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < DW; ++j) {
-            block_sum<6 * FR>(acc[j], sh);
-            const int d = d0 + j;
-            if (threadIdx.x == 0 && d < ndir) {
-                const double* dv = dirs + (long long)d * 9;
-                for (int r = 0; r < FR && q0 + r < qb; ++r) {
-                    double2 f1 = {0.0, 0.0}, f2 = {0.0, 0.0};
-                    for (int c = 0; c < 3; ++c) {
-                        const double2 A = {k3 * acc[j][6 * r + 2 * c], k3 * acc[j][6 * r + 2 * c + 1]};
-                        f1 = cadd(f1, double2{dv[3 + c] * A.x, dv[3 + c] * A.y});
-                        f2 = cadd(f2, double2{dv[6 + c] * A.x, dv[6 + c] * A.y});
-                    }
-                    const long long o = per > 0 ? (long long)d : (long long)(q0 + r) * ndir + d;
-                    f[o * 2 + 0] = f1;
-                    f[o * 2 + 1] = f2;
-                    dcs[o] = (f1.x * f1.x + f1.y * f1.y + f2.x * f2.x + f2.y * f2.y) / (k * k);
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-// Direction sets of the angular averages ("Averaging over Scattering
-// Directions"): for right-hand side q with incidence direction k, the frame
-// (k, u, v), u the unit vector along k x e (e the x axis, or y where k is
-// near x) and v = k x u, and the directions n = mu_i k + sqrt(1 - mu_i^2)
-// (cos p_j u + sin p_j v), p_j = 2 pi j / n_phi, with their theta and phi
-// unit vectors: dirs [ng][n_theta][n_phi][9] (n, theta, phi).
-__global__ __launch_bounds__(NT) void k_avg_dirs(int ng, const double* kh, const double* mu, int n_theta, int n_phi,
-                                                 double* dirs) {
-    const long long nd = (long long)n_theta * n_phi;
-    const long long idx = (long long)blockIdx.x * NT + threadIdx.x;
-    if (idx >= (long long)ng * nd) return;
-    const int q = (int)(idx / nd);
-    const int i = (int)((idx % nd) / n_phi);
-    const int j = (int)(idx % n_phi);
-    const double* k = kh + 3 * q;
-    const bool nx = fabs(k[0]) < 0.9;
-    const double e[3] = {nx ? 1.0 : 0.0, nx ? 0.0 : 1.0, 0.0};
-    double u[3] = {k[1] * e[2] - k[2] * e[1], k[2] * e[0] - k[0] * e[2], k[0] * e[1] - k[1] * e[0]};
-    const double un = sqrt(u[0] * u[0] + u[1] * u[1] + u[2] * u[2]);
-    for (double& x : u) x /= un;
-    const double v[3] = {k[1] * u[2] - k[2] * u[1], k[2] * u[0] - k[0] * u[2], k[0] * u[1] - k[1] * u[0]};
-    const double ct = mu[i], st = sqrt(fmax(0.0, 1.0 - ct * ct));
-    const double p = 2.0 * M_PI * j / n_phi;
-    double sp, cp;
-    sincos(p, &sp, &cp);
-    double* D = dirs + idx * 9;
-    for (int m = 0; m < 3; ++m) {
-        const double t = cp * u[m] + sp * v[m];
-        D[m] = ct * k[m] + st * t;
-        D[3 + m] = ct * t - st * k[m];
-        D[6 + m] = -sp * u[m] + cp * v[m];
-    }
-}
-
 // ------------------------------------------------------------------ near field
 // ("Near-Field Calculations".)  The extended volume is a lattice box of
 // dims[0] x dims[1] x dims[2] points starting at lattice point org, every
@@ -1087,43 +942,6 @@ void launch_b2_update(const SiteArgs& a, int site_blocks, hipStream_t s) {
 }
 void launch_qmr_final(const SiteArgs& a, int site_blocks, hipStream_t s) {
     hipLaunchKernelGGL(k_qmr_final, dim3(site_blocks, a.nrhs), dim3(NT), 0, s, a);
-}
-// directions per workgroup of the far field: four where the direction sets
-// allow it and the launch still has at least FF_MIN_WG workgroups (each
-// site's P then serves four directions), else one
-constexpr int FF_DW = 4;
-constexpr int FF_MIN_WG = 512;
-void launch_farfield(int nsites, const int* coords, const double2* P, int nrhs, const double* dirs, int ndir,
-                     double k, const int lo[3], const int n[3], double2* f, double* dcs, hipStream_t s) {
-    const size_t nt = (size_t)(n[0] + n[1] + n[2]);
-    const int npair = (nrhs + 1) / 2;   // grid y: the right-hand sides two at a time
-    if ((long long)((ndir + FF_DW - 1) / FF_DW) * npair >= FF_MIN_WG) {
-        hipLaunchKernelGGL((k_farfield<FF_DW, 2>), dim3((ndir + FF_DW - 1) / FF_DW, npair), dim3(NT),
-                           FF_DW * nt * sizeof(double2), s, nsites, coords, P, 3LL * nsites, nrhs, dirs, k, lo[0],
-                           lo[1], lo[2], n[0], n[1], n[2], f, dcs, ndir, 0);
-    } else {
-        hipLaunchKernelGGL((k_farfield<1, 2>), dim3(ndir, npair), dim3(NT), nt * sizeof(double2), s, nsites, coords,
-                           P, 3LL * nsites, nrhs, dirs, k, lo[0], lo[1], lo[2], n[0], n[1], n[2], f, dcs, ndir, 0);
-    }
-}
-void launch_avg_dirs(int ng, const double* kh, const double* mu, int n_theta, int n_phi, double* dirs,
-                     hipStream_t s) {
-    const long long tot = (long long)ng * n_theta * n_phi;
-    hipLaunchKernelGGL(k_avg_dirs, dim3((unsigned)((tot + NT - 1) / NT)), dim3(NT), 0, s, ng, kh, mu, n_theta, n_phi,
-                       dirs);
-}
-void launch_farfield_sets(int nsites, const int* coords, const double2* P, int nrhs, const double* dirs, int per,
-                          double k, const int lo[3], const int n[3], double2* f, double* dcs, hipStream_t s) {
-    const size_t nt = (size_t)(n[0] + n[1] + n[2]);
-    const int ndt = per * nrhs;
-    if (per % FF_DW == 0 && ndt >= FF_DW * FF_MIN_WG) {
-        hipLaunchKernelGGL((k_farfield<FF_DW, 1>), dim3(ndt / FF_DW), dim3(NT), FF_DW * nt * sizeof(double2), s, nsites,
-                           coords, P, 3LL * nsites, nrhs, dirs, k, lo[0], lo[1], lo[2], n[0], n[1], n[2], f, dcs,
-                           ndt, per);
-    } else {
-        hipLaunchKernelGGL((k_farfield<1, 1>), dim3(ndt), dim3(NT), nt * sizeof(double2), s, nsites, coords, P,
-                           3LL * nsites, nrhs, dirs, k, lo[0], lo[1], lo[2], n[0], n[1], n[2], f, dcs, ndt, per);
-    }
 }
 void launch_nf_place(int nsites, const int* perm, const int* coords, const double2* P, int nrhs, const int org[3],
                      const int dims[3], double2* x, hipStream_t s) {

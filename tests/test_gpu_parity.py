@@ -1453,3 +1453,46 @@ def test_tensor_octant_over_odd_and_padded_extents(dda, box):
     for q in range(2):
         ref = (_dense_A(ijk, m, 0.8, kh[q], e0[q], "LATTDR") @ xv[q].reshape(-1)).reshape(n, 3)
         assert np.abs(y[q] - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("box,n_dir", [((21, 21, 21), 1), ((8, 48, 33), 15), ((33, 17, 16), 17), ((256, 6, 6), 70),
+                                       ((255, 6, 7), 64), ((16, 48, 12), 130)])
+def test_far_field_by_lines_matches_the_oracle(dda, box, n_dir):
+    """Dense boxes of at least 8,192 sites (odd and even lines, partial tiles
+    of lines, planes and directions): the amplitudes by contractions along x
+    against the oracle's direct sum (1e-12)."""
+    from oracle import farfield
+    rng = np.random.default_rng(n_dir)
+    keep = rng.random(box) < 0.93
+    keep[0, 0, 0] = keep[-1, -1, -1] = True
+    ijk = (np.argwhere(keep) - [3, -2, 40]).astype(np.int32)
+    n = len(ijk)
+    assert n >= 8192
+    tgt = dda.Target(ijk, 1.5 + 0.1j)
+    P = w.random_vectors(12, (3, n, 3))
+    nh, th, ph = w.lab_directions(rng.uniform(0, 180, n_dir), rng.uniform(0, 360, n_dir))
+    opts = dda.Options.for_size_parameter(4.0)
+    f, dcs = dda.far_field(tgt, opts, _cuda(P), nh, th, ph)
+    k = dense.kd_from_size_parameter(4.0, n)
+    for q in range(3):
+        A = farfield.amplitude_vectors(ijk, P[q], k, nh)
+        ref = np.stack([np.sum(th * A, axis=1), np.sum(ph * A, axis=1)], axis=1)
+        assert np.abs(f[q] - ref).max() <= 1e-12 * np.abs(P[q]).sum() * k ** 3 / np.sqrt(n)
+        assert np.allclose(dcs[q], (np.abs(f[q]) ** 2).sum(axis=1) / k ** 2, rtol=1e-13, atol=0)
+
+
+def test_far_field_by_lines_in_groups_of_right_hand_sides(dda):
+    """More right-hand sides than one launch's operands hold (512 MiB): each
+    one's amplitudes equal those of a call of its own, bitwise."""
+    ijk = w.brick(256, 6, 6)
+    n, q = len(ijk), 470
+    tgt = dda.Target(ijk, 1.5 + 0.1j)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    P = torch.randn((q, n, 3), generator=g, dtype=torch.complex128, device="cuda")
+    nh, th, ph = w.lab_directions([10.0, 75.0], [0.0, 40.0])
+    opts = dda.Options.for_size_parameter(4.0)
+    f, _ = dda.far_field(tgt, opts, P, nh, th, ph)
+    for i in (0, 1, 300, 433, q - 1):
+        fi, _ = dda.far_field(tgt, opts, P[i:i + 1], nh, th, ph)
+        assert np.array_equal(f[i], fi[0])
