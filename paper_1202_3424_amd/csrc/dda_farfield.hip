@@ -165,7 +165,7 @@ __global__ __launch_bounds__(NT) void k_avg_dirs(int ng, const double* kh, const
 // per direction, right-hand side and point of the box (rounded up to 8 in x
 // and 16 in y, a tile of 16 lines only as far from the centre as it has
 // sites), 71 us of matrix instructions for the 51,488-site ellipsoid and 2 x
-// 3,072 directions: 129 us and 24 for its three small kernels, 353 by the sum
+// 3,072 directions: 129 us and 14 for its two small kernels, 353 by the sum
 // over sites.
 
 constexpr int FF_LINES = 16;   // lines (along y) of a tile
@@ -174,16 +174,51 @@ constexpr int FF_DIRS = 16;    // directions of a wavefront
 // the directions nor the right-hand sides of the call
 constexpr int FF_Z = 2;
 
+// Phase factors of a tile of 16 directions: tab[q][tile] holds, in the order
+// the lanes of k_ff_lines read them, (cos, sin)(t h) of lane (direction
+// lane & 15, h = 4 ks + (lane >> 4)) as [KS][64], then exp(-i k n_y y) as
+// [ny][16] and exp(-i k n_z z) as [nz][16].  Directions past the end copy the
+// last one.  i: value of this thread; dirs, tab: of this right-hand side.
+__device__ __forceinline__ void ff_factor(int i, int tile, int nx, int ny, int nz, int KS, const double* dirs, int nd,
+                                          double k, int loy, int loz, double2* tab) {
+    const int n = KS * 64 + (ny + nz) * FF_DIRS;
+    if (i >= n) return;
+    const int j = i - KS * 64;
+    const double* dv = dirs + (long long)min(tile * FF_DIRS + (i & 15), nd - 1) * 9;
+    double ph;
+    if (j < 0) ph = k * dv[0] * (4 * (i >> 6) + ((i & 63) >> 4) + (nx & 1 ? 0.0 : 0.5));
+    else if (j < ny * FF_DIRS) ph = -k * dv[1] * (loy + j / FF_DIRS);
+    else ph = -k * dv[2] * (loz + j / FF_DIRS - ny);
+    double2 w;
+    sincos(ph, &w.y, &w.x);
+    tab[(long long)tile * n + i] = w;
+}
+
+// The operands of k_ff_lines for right-hand side blockIdx.y: the first nfold
+// workgroups fold P, the others form the phase factors (one launch: each part
+// alone is mostly launch and load latency).
+//
 // The folded operands of every tile (16 lines of one z, one component), in
 // the order in which a wavefront's lanes read them: value [q][tile][c][ks][p]
 // of lane (k, l) is h = 4 ks + k of line y = 16 yb + l, {Re E, Im O} (p = 0)
-// or {Im E, -Re O} (p = 1).  A workgroup forms four steps ks of one component of a tile;
-// kt[tile][ks / 4]: steps of the tile up to its last one there with a site.
-__global__ __launch_bounds__(NT) void k_ff_fold(const int* map, const int* perm, const double2* P, long long n3,
-                                                int nx, int ny, int nz, int KS, double2* fold, int* kt) {
+// or {Im E, -Re O} (p = 1).  A workgroup forms four steps ks of one component
+// of a tile; kt[tile][ks / 4]: steps of the tile up to its last one there with
+// a site.
+__global__ __launch_bounds__(NT) void k_ff_operands(const int* map, const int* perm, const double2* P, long long n3,
+                                                    int nx, int ny, int nz, int KS, double2* fold, int* kt,
+                                                    int nfold, const double* dirs, int nd, int dstride, double k,
+                                                    int loy, int loz, double2* tab) {
+    if ((int)blockIdx.x >= nfold) {
+        const int per = (KS * 64 + (ny + nz) * FF_DIRS + NT - 1) / NT;   // workgroups of a tile of directions
+        const int b = blockIdx.x - nfold, q = blockIdx.y;
+        const int tiles = (nd + FF_DIRS - 1) / FF_DIRS;
+        ff_factor(b % per * NT + threadIdx.x, b / per, nx, ny, nz, KS, dirs + (long long)q * dstride * 9, nd, k, loy,
+                  loz, tab + (long long)q * tiles * (KS * 64 + (ny + nz) * FF_DIRS));
+        return;
+    }
     __shared__ int most;
     const int nyb = (ny + FF_LINES - 1) / FF_LINES, nkg = (KS + 3) / 4;
-    const int tile = blockIdx.x / nkg, kg = blockIdx.x % nkg, q = blockIdx.y, c = blockIdx.z;
+    const int tile = blockIdx.x / (3 * nkg), kg = blockIdx.x % nkg, q = blockIdx.y, c = blockIdx.x / nkg % 3;
     const int z = tile / nyb, yb = tile % nyb;
     const double2* Pq = P + (long long)q * n3;
     double2* out = fold + ((long long)q * nz * nyb + tile) * 3 * KS * 2 * 64;
@@ -212,29 +247,7 @@ __global__ __launch_bounds__(NT) void k_ff_fold(const int* map, const int* perm,
         o[64] = double2{E.y, -O.x};
     }
     __syncthreads();
-    if (q == 0 && c == 0 && threadIdx.x == 0) kt[blockIdx.x] = most;
-}
-
-// Phase factors of every tile of 16 directions: tab[q][tile] holds, in the
-// order the lanes of k_ff_lines read them, (cos, sin)(t h) of lane (direction
-// lane & 15, h = 4 ks + (lane >> 4)) as [KS][64], then exp(-i k n_y y) as
-// [ny][16] and exp(-i k n_z z) as [nz][16].  Directions past the end copy the
-// last one.
-__global__ __launch_bounds__(NT) void k_ff_factors(int nx, int ny, int nz, int KS, const double* dirs, int nd,
-                                                  int dstride, double k, int loy, int loz, double2* tab) {
-    const int n = KS * 64 + (ny + nz) * FF_DIRS;
-    const int i = blockIdx.x * NT + threadIdx.x;
-    if (i >= n) return;
-    const int tile = blockIdx.y, q = blockIdx.z;
-    const int j = i - KS * 64;
-    const double* dv = dirs + ((long long)q * dstride + min(tile * FF_DIRS + (i & 15), nd - 1)) * 9;
-    double ph;
-    if (j < 0) ph = k * dv[0] * (4 * (i >> 6) + ((i & 63) >> 4) + (nx & 1 ? 0.0 : 0.5));
-    else if (j < ny * FF_DIRS) ph = -k * dv[1] * (loy + j / FF_DIRS);
-    else ph = -k * dv[2] * (loz + j / FF_DIRS - ny);
-    double2 w;
-    sincos(ph, &w.y, &w.x);
-    tab[((long long)q * gridDim.y + tile) * n + i] = w;
+    if (q == 0 && c == 0 && threadIdx.x == 0) kt[tile * nkg + kg] = most;
 }
 
 // Sums over the planes z of chunk blockIdx.y for 16 directions per
@@ -340,7 +353,8 @@ __global__ __launch_bounds__(NT) void k_ff_project(const double* part, int nchun
     if (d >= nd) return;
     const double* dv = dirs + ((long long)q * dstride + d) * 9;
     double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int h = 0; h < nchunk; ++h) {
+#pragma unroll 8
+    for (int h = 0; h < nchunk; ++h) {   // (unrolled: the loads do not wait for one another)
         const double* p = part + (((long long)q * nchunk + h) * nd + d) * 6;
         for (int i = 0; i < 6; ++i) s[i] += p[i];
     }
@@ -403,11 +417,11 @@ void launch_farfield_sets(int nsites, const int* coords, const double2* P, int n
 // directions or right-hand sides of the call).  The line form's work grows
 // with the rounded box, the sum's with the sites: for 48^3 boxes, 2 x 3,072
 // directions, 297 against 453 us a call at two points a site, 297 against 265
-// at four.  Below about 8,000 sites its three small kernels cost more than
-// they save: 141 against 127 us at 16^3, 178 against 196 at 24^3 sites.
+// at four.  At 4,096 sites (16^3) the two meet: 87 against 96 us for 3,072
+// directions, 59 against 56 for 74.
 bool far_lines(int nsites, const int n[3]) {
     const long long v = 8LL * ((n[0] + 7) / 8) * FF_LINES * ((n[1] + FF_LINES - 1) / FF_LINES) * n[2];
-    return nsites >= 8192 && v <= 3LL * nsites;
+    return nsites >= 4096 && v <= 3LL * nsites;
 }
 namespace {
 struct LineSizes {
@@ -445,14 +459,13 @@ void launch_far_lines(const int* map, const int* perm, const double2* P, long lo
     double* part = (double*)((char*)tab + (size_t)grp * z.tab);
     const size_t sm = (size_t)(NT / 64) * z.KS * 64 * sizeof(double2);
     const int nf = z.KS * 64 + (n[1] + n[2]) * FF_DIRS;
-    const int per_wg = FF_DIRS * (NT / 64);
+    const int per_wg = FF_DIRS * (NT / 64), nfold = z.tiles * z.nkg * 3;
     for (int q0 = 0; q0 < nrhs; q0 += grp) {
         const int nq = nrhs - q0 < grp ? nrhs - q0 : grp;
         const double* dq = dirs + (size_t)q0 * dstride * 9;
-        hipLaunchKernelGGL(k_ff_fold, dim3(z.tiles * z.nkg, nq, 3), dim3(NT), 0, s, map, perm, P + (size_t)q0 * n3, n3, n[0],
-                           n[1], n[2], z.KS, fold, kt);
-        hipLaunchKernelGGL(k_ff_factors, dim3((nf + NT - 1) / NT, (nd + FF_DIRS - 1) / FF_DIRS, nq), dim3(NT), 0, s,
-                           n[0], n[1], n[2], z.KS, dq, nd, dstride, k, lo[1], lo[2], tab);
+        hipLaunchKernelGGL(k_ff_operands, dim3(nfold + ((nf + NT - 1) / NT) * ((nd + FF_DIRS - 1) / FF_DIRS), nq),
+                           dim3(NT), 0, s, map, perm, P + (size_t)q0 * n3, n3, n[0], n[1], n[2], z.KS, fold, kt,
+                           nfold, dq, nd, dstride, k, lo[1], lo[2], tab);
         hipLaunchKernelGGL(k_ff_lines, dim3((nd + per_wg - 1) / per_wg, z.nchunk, nq), dim3(NT), sm, s, fold, kt,
                            n[0], n[1], n[2], z.KS, tab, nd, part);
         hipLaunchKernelGGL(k_ff_project, dim3((nd + NT - 1) / NT, nq), dim3(NT), 0, s, part, z.nchunk, dq, nd, dstride,

@@ -1458,7 +1458,7 @@ def test_tensor_octant_over_odd_and_padded_extents(dda, box):
 @pytest.mark.parametrize("box,n_dir", [((21, 21, 21), 1), ((8, 48, 33), 15), ((33, 17, 16), 17), ((256, 6, 6), 70),
                                        ((255, 6, 7), 64), ((16, 48, 12), 130)])
 def test_far_field_by_lines_matches_the_oracle(dda, box, n_dir):
-    """Dense boxes of at least 8,192 sites (odd and even lines, partial tiles
+    """Dense boxes (odd and even lines, partial tiles
     of lines, planes and directions): the amplitudes by contractions along x
     against the oracle's direct sum (1e-12)."""
     from oracle import farfield
