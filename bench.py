@@ -93,7 +93,7 @@ def log(*a):
 def kernel_source_digest() -> str:
     """Digest of the sources that define the FFT pass kernels."""
     h = hashlib.sha256()
-    for f in ("dda_device.h", "dda_passes.h"):
+    for f in ("dda_device.h", "dda_passcommon.h", "dda_passes.h", "dda_xpass.h", "dda_plane.h"):
         with open(os.path.join(ROOT, "paper_1202_3424_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()

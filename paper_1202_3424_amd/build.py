@@ -14,8 +14,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libdda.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
-SOURCES = ["dda_kernels.hip", "dda_green.hip", "dda_farfield.hip", "dda_passes_f64.hip", "dda_passes_f32.hip", "dda_plane_f64.hip", "dda_plane_f32.hip",
-           "dda_api.hip"]
+SOURCES = ["dda_kernels.hip", "dda_green.hip", "dda_farfield.hip", "dda_passes_f32.hip", "dda_passes_f64.hip",
+           "dda_xpass_f64.hip", "dda_xpass_f32.hip", "dda_plane_f64.hip", "dda_plane_f32.hip", "dda_api.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

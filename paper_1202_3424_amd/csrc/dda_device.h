@@ -560,16 +560,49 @@ __device__ __forceinline__ void load_twiddles(typename V2<T>::t* dst, const doub
 
 // ---------------------------------------------------------------- reductions
 
+// v + (v of lane ^ OFF): one step of a wavefront's xor butterfly.  On the
+// vector unit (permlane swaps across rows, DPP within one) instead of
+// through LDS permutes, whose latency a small kernel's tail waits for six
+// times; the same additions.
+template <int OFF> __device__ __forceinline__ double xor_add(double v) {
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    if constexpr (OFF == 32) {
+        const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+        const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+        return __hiloint2double(b[0], a[0]) + __hiloint2double(b[1], a[1]);
+    } else if constexpr (OFF == 16) {
+        const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+        const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+        return __hiloint2double(b[0], a[0]) + __hiloint2double(b[1], a[1]);
+    } else {
+        // lane ^ 8: rotate the 16-lane row by 8; ^ 4: mirror each 8 lanes,
+        // then each 4; ^ 2, ^ 1: quad permutations
+        int l, h;
+        if constexpr (OFF == 8) {
+            l = __builtin_amdgcn_mov_dpp(lo, 0x128, 0xf, 0xf, true);
+            h = __builtin_amdgcn_mov_dpp(hi, 0x128, 0xf, 0xf, true);
+        } else if constexpr (OFF == 4) {
+            l = __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(lo, 0x141, 0xf, 0xf, true), 0x1B, 0xf, 0xf, true);
+            h = __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(hi, 0x141, 0xf, 0xf, true), 0x1B, 0xf, 0xf, true);
+        } else if constexpr (OFF == 2) {
+            l = __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xf, 0xf, true);
+            h = __builtin_amdgcn_mov_dpp(hi, 0x4E, 0xf, 0xf, true);
+        } else {
+            l = __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xf, 0xf, true);
+            h = __builtin_amdgcn_mov_dpp(hi, 0xB1, 0xf, 0xf, true);
+        }
+        return v + __hiloint2double(h, l);
+    }
+}
+
 // Sum NV doubles over the workgroup; the result is valid in thread 0.
 // Fixed order: xor-butterfly inside each 64-lane wavefront, then the four
 // wavefront sums in index order.
 template <int NV, int NTHR = NT>
 __device__ __forceinline__ void block_sum(double (&v)[NV], double* sh) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-#pragma unroll
-        for (int i = 0; i < NV; ++i) v[i] += __shfl_xor(v[i], off, 64);
-    }
+    for (int i = 0; i < NV; ++i)
+        v[i] = xor_add<1>(xor_add<2>(xor_add<4>(xor_add<8>(xor_add<16>(xor_add<32>(v[i]))))));
     if constexpr (NTHR == 64) return;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     if (lane == 0) {

@@ -1,6 +1,6 @@
 // The five passes of the FFT matrix-vector product y = A x, as kernel
-// templates instantiated per grid precision (dda_passes_f64.hip,
-// dda_passes_f32.hip).
+// templates instantiated per grid precision: passes 2-4 here
+// (dda_passes_f64.hip, dda_passes_f32.hip), passes 1 and 5 in dda_xpass.h.
 //
 // A = the interaction matrix of Draine (1988) plus the diagonal 1/alpha
 // ("Dipole Polarizabilities"); the product is a convolution on a zero-padded
@@ -22,16 +22,10 @@
 // runtime plan with twiddles staged in LDS.
 #pragma once
 
-#include <stdexcept>
-#include <type_traits>
-
-#include "dda_kernels.h"
+#include "dda_passcommon.h"
 
 namespace dda {
 namespace passes {
-
-// lengths with compile-time kernels
-#define DDA_CT_LENGTHS(X) X(32) X(48) X(64) X(80) X(96) X(128) X(160) X(192) X(256) X(384) X(512)
 
 // x columns per workgroup of a compile-time strided pass: a tile of about
 // 1536 complex values (three components per column)
@@ -42,539 +36,6 @@ constexpr int ct_cols(int L) {
     while (p * 2 <= tx && p * 2 <= 16) p *= 2;
     return p;
 }
-// threads of a compile-time x-pass workgroup: one wavefront up to length
-// 128, two beyond (a line of 3 x 256 values gives one wavefront 12 elements
-// per thread, which serialises its dependent map and site loads)
-constexpr int xthr(int L) { return L > 128 ? 128 : 64; }
-
-template <typename C> __device__ __forceinline__ C to_c(double2 u) {
-    C c;
-    c.x = u.x;
-    c.y = u.y;
-    return c;
-}
-template <typename C> __device__ __forceinline__ double2 to_d(C u) {
-    double2 c;
-    c.x = (double)u.x;
-    c.y = (double)u.y;
-    return c;
-}
-
-__device__ __forceinline__ bool skip_rhs(const RhsState* st, int chk) {
-    return chk != CHK_NONE && st->status != ST_ACTIVE;
-}
-
-// g_a X + g_b Y + g_c Z for one row of the symmetric tensor product, each
-// part one expression so that it contracts to a multiply and five fused
-// multiply-adds (every pass-3 form uses this, so all stay bitwise identical)
-template <typename C>
-__device__ __forceinline__ C trow(const C& ga, const C& gb, const C& gc, const C& X, const C& Y, const C& Z) {
-    C r;
-    r.x = ga.x * X.x - ga.y * X.y + gb.x * Y.x - gb.y * Y.y + gc.x * Z.x - gc.y * Z.y;
-    r.y = ga.x * X.y + ga.y * X.x + gb.x * Y.y + gb.y * Y.x + gc.x * Z.y + gc.y * Z.x;
-    return r;
-}
-
-inline __host__ __device__ int pad_len(int L) { return L | 1; }
-inline __host__ __device__ int even_up(int L) { return (L + 1) & ~1; }
-
-// LDS of a runtime-length kernel: [twiddles (L)][tile (nlines * Lp)][scratch];
-// of a compile-time kernel: [tile][scratch].
-template <typename C> inline size_t smem_rt(int L, int nlines) {
-    return ((size_t)even_up(L) + (size_t)nlines * pad_len(L)) * sizeof(C) + 8 * (NT / 64) * sizeof(double) + 64;
-}
-template <typename C> inline size_t smem_ct(int L, int nlines) {
-    return (size_t)nlines * pad_len(L) * sizeof(C) + 8 * (NT / 64) * sizeof(double) + 64;
-}
-
-// ------------------------------------------------------------------ pass 1
-
-template <typename T, int MODE, int LC, int NTHR>
-__global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename V2<T>::t* grid, const double2* tw64,
-                                                   int XLrt, int chk) {
-    using C = typename V2<T>::t;
-    constexpr bool CT = LC > 0;
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int q = blockIdx.z;
-    const RhsState* st = a.st + q;
-    if (skip_rhs(st, chk)) return;
-    int nx = g.n[0], ny = g.n[1];
-    const int* map = a.map;
-    const int Mx = CT ? LC : g.M[0];
-    const int My = g.M[1];
-    const int XL = CT ? 1 : XLrt;
-    const int z = blockIdx.y;
-    const int y0 = blockIdx.x * XL;
-    // the workgroups of one right-hand side along y, and its partial-sum index
-    int bx = gridDim.x;
-    if (a.rg) {   // ragged batch: this right-hand side's target
-        const RhsGeo& r = a.rg[q];
-        if (z >= r.n[2] || y0 >= r.n[1]) return;
-        nx = r.n[0];
-        ny = r.n[1];
-        map += r.map_off;
-        bx = (ny + XL - 1) / XL;
-    }
-    const int nl = CT ? 1 : min(XL, ny - y0);
-    const int nlines = 3 * nl;
-    const int Lp = pad_len(Mx);
-    C* lds;
-    C* tws = nullptr;
-    if constexpr (CT) {
-        lds = (C*)smem;
-    } else {
-        tws = (C*)smem;
-        lds = tws + even_up(Mx);
-        load_twiddles<T, NTHR>(tws, tw64, g.ax[0]);
-    }
-    double2 beta = {0, 0}, omega = {0, 0}, alpha = {0, 0};
-    double w_old = 0.0, w_new = 0.0;
-    int pend = 0;
-    if (MODE == SC_P) { beta = st->beta; omega = st->omega; alpha = st->alpha; pend = st->pend; }
-    if (MODE == SC_S) alpha = st->alpha;
-    if (MODE == SC_Q) { beta = st->beta; w_old = st->w_old; w_new = st->w_new; }
-    if (MODE == SC_B0 || MODE == SC_B2) beta = st->beta;
-    if (MODE == SC_B1 || MODE == SC_B3) alpha = st->alpha;
-    const long long vb = (long long)q * a.n3;
-    const int* mrow = map + ((long long)z * ny + y0) * nx;
-    double ss[3] = {0.0, 0.0, 0.0};
-    // forward transform of a line that is zero beyond nx: with 2 nx <= Mx the
-    // first radix pass never reads the upper half, which is then not filled
-    // (always so at the compile-time lengths, which are even and >= 2 nx - 1)
-    bool hin = false;
-    if constexpr (CT) hin = ct_half_in_ok(LC) && 2 * nx <= Mx;
-    const int ext = hin ? Mx / 2 : Mx;
-    const int tin = nl * ext * 3;
-    // the site-vector values this mode reads at element i (all of them are
-    // loaded before any update is stored, so that the loads of every element
-    // a thread fills are in flight together)
-    struct Ops {
-        double2 o[6];
-    };
-    auto load_ops = [&](long long i) {
-        Ops v;
-        if (MODE == SC_PLAIN || MODE == SC_CONJ) {
-            v.o[0] = a.in[i];
-        } else if (MODE == SC_P) {
-            v.o[0] = a.r[i]; v.o[1] = a.p[i]; v.o[2] = a.v[i]; v.o[3] = a.x[i]; v.o[4] = a.t[i];
-        } else if (MODE == SC_B0) {
-            v.o[0] = a.r[i]; v.o[1] = a.p[i];
-        } else if (MODE == SC_B1) {
-            v.o[0] = a.r[i]; v.o[1] = a.v[i]; v.o[2] = a.x[i]; v.o[3] = a.p[i];
-        } else if (MODE == SC_B2) {
-            v.o[0] = a.r[i]; v.o[1] = a.p[i]; v.o[2] = a.t[i]; v.o[3] = a.v[i];
-        } else if (MODE == SC_B3) {
-            v.o[0] = a.r[i]; v.o[1] = a.v[i]; v.o[2] = a.t[i]; v.o[3] = a.u2[i]; v.o[4] = a.x[i]; v.o[5] = a.p[i];
-        } else if (MODE == SC_Q) {
-            v.o[0] = a.r[i]; v.o[1] = a.p[i]; v.o[2] = a.rhat[i]; v.o[3] = a.t[i]; v.o[4] = a.x[i];
-        } else {   // SC_S
-            v.o[0] = a.r[i]; v.o[1] = a.v[i]; v.o[2] = a.rhat[i];
-        }
-        return v;
-    };
-    // the product's input at element i after this mode's vector update from
-    // the loaded values v, the update stored back (and summed) only where
-    // `live` (a site of this line; elsewhere the value is unused)
-    auto update = [&](long long i, const Ops& v, bool live) -> double2 {
-        double2 u;
-        if (MODE == SC_PLAIN) {
-            u = v.o[0];
-        } else if (MODE == SC_CONJ) {
-            u = cconj(v.o[0]);
-        } else if (MODE == SC_P) {
-            // the previous iteration's end, if pending: x += alpha p + omega
-            // s, r = s - omega t (s is held in r); then p = r + beta (p -
-            // omega v)
-            double2 rr = v.o[0];
-            const double2 pp = v.o[1];
-            if (pend) {
-                const double2 xx = cadd(cadd(v.o[3], cmul(alpha, pp)), cmul(omega, rr));
-                rr = csub(rr, cmul(omega, v.o[4]));
-                if (live) {
-                    a.x[i] = xx;
-                    a.r[i] = rr;
-                }
-            }
-            u = cadd(rr, cmul(beta, csub(pp, cmul(omega, v.o[2]))));
-            if (live) a.p[i] = u;
-        } else if (MODE == SC_B0) {
-            // BiCGstab(2), first BiCG step: u_0 = r_0 - beta u_0
-            u = csub(v.o[0], cmul(beta, v.o[1]));
-            if (live) a.p[i] = u;
-        } else if (MODE == SC_B1) {
-            // r_0 -= alpha u_1, x += alpha u_0; product of r_0
-            u = csub(v.o[0], cmul(alpha, v.o[1]));
-            if (live) {
-                a.r[i] = u;
-                a.x[i] = cadd(v.o[2], cmul(alpha, v.o[3]));
-            }
-        } else if (MODE == SC_B2) {
-            // second BiCG step: u_0 = r_0 - beta u_0, u_1 = r_1 - beta u_1; product of u_1
-            u = csub(v.o[2], cmul(beta, v.o[3]));
-            if (live) {
-                a.p[i] = csub(v.o[0], cmul(beta, v.o[1]));
-                a.v[i] = u;
-            }
-        } else if (MODE == SC_B3) {
-            // r_0 -= alpha u_1, r_1 -= alpha u_2, x += alpha u_0; product of r_1
-            u = csub(v.o[2], cmul(alpha, v.o[3]));
-            if (live) {
-                a.r[i] = csub(v.o[0], cmul(alpha, v.o[1]));
-                a.t[i] = u;
-                a.x[i] = cadd(v.o[4], cmul(alpha, v.o[5]));
-            }
-        } else if (MODE == SC_Q) {
-            // QMR: p = r + beta p, and the pending smoothing step
-            // (y, s) <- w_old (y, s) + w_new (x, r)
-            const double2 rr = v.o[0];
-            u = cadd(rr, cmul(beta, v.o[1]));
-            if (live) {
-                const double2 sm = v.o[2], ym = v.o[3], xx = v.o[4];
-                a.p[i] = u;
-                a.rhat[i] = double2{w_old * sm.x + w_new * rr.x, w_old * sm.y + w_new * rr.y};
-                a.t[i] = double2{w_old * ym.x + w_new * xx.x, w_old * ym.y + w_new * xx.y};
-            }
-        } else {
-            // s = r - alpha v, stored over r; |s|^2 and <rhat, s>
-            u = csub(v.o[0], cmul(alpha, v.o[1]));
-            if (live) {
-                const double2 w = cdotc(v.o[2], u);
-                a.r[i] = u;
-                ss[0] += u.x * u.x + u.y * u.y;
-                ss[1] += w.x;
-                ss[2] += w.y;
-            }
-        }
-        return u;
-    };
-    if constexpr (CT) {
-        // one line: the site indices of every element this thread fills are
-        // loaded first, then every operand (clamped to site 0 where there is
-        // no site), so that the loads of all elements are in flight together
-        constexpr int EXT = ct_half_in_ok(LC) ? LC / 2 : LC;
-        constexpr int NPT = (3 * EXT + NTHR - 1) / NTHR;
-        int sk[NPT];
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            const int e = idx / 3;
-            sk[k] = (idx < tin && e < nx) ? mrow[e] : -1;
-        }
-        Ops ok[NPT];
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            ok[k] = load_ops(vb + (long long)(sk[k] >= 0 ? sk[k] : 0) * 3 + idx % 3);
-        }
-        double2 uk[NPT];
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            const bool live = sk[k] >= 0;
-            uk[k] = update(vb + (long long)(live ? sk[k] : 0) * 3 + idx % 3, ok[k], live);
-        }
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            if (idx < tin) {
-                C val;
-                val.x = 0;
-                val.y = 0;
-                if (sk[k] >= 0) val = to_c<C>(uk[k]);
-                lds[(idx % 3) * Lp + idx / 3] = val;
-            }
-        }
-        // (a full-length input, never the case at these even lengths: zeros
-        // beyond the half)
-        for (int idx = 3 * EXT + threadIdx.x; idx < tin; idx += NTHR) {
-            C val;
-            val.x = 0;
-            val.y = 0;
-            lds[(idx % 3) * Lp + idx / 3] = val;
-        }
-    } else {
-        for (int idx = threadIdx.x; idx < tin; idx += NTHR) {
-            const int c = idx % 3;
-            const int rest = idx / 3;
-            const int e = rest % ext;
-            const int yo = rest / ext;
-            C val;
-            val.x = 0;
-            val.y = 0;
-            if (e < nx) {
-                const int s = mrow[yo * nx + e];
-                if (s >= 0) {
-                    const long long i = vb + (long long)s * 3 + c;
-                    val = to_c<C>(update(i, load_ops(i), true));
-                }
-            }
-            lds[(yo * 3 + c) * Lp + e] = val;
-        }
-    }
-    __syncthreads();
-    if constexpr (CT) {
-        if (hin) fft_lines_ct<T, -1, LC, 3, NTHR, true, false>(lds, tw64 + g.ax[0].tw);
-        else fft_lines_ct<T, -1, LC, 3, NTHR>(lds, tw64 + g.ax[0].tw);
-    } else {
-        fft_lines<T, -1, NTHR>(lds, tws, nlines, Lp, g.ax[0]);
-    }
-    C* gq = grid + ((long long)q * g.npts + ((long long)z * My + y0) * Mx) * 3;
-    if constexpr (CT) {
-        constexpr int NPT = (3 * LC + NTHR - 1) / NTHR;
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            if ((3 * LC) % NTHR == 0 || idx < 3 * LC) gq[idx] = lds[(idx % 3) * Lp + idx / 3];
-        }
-    } else {
-        const int tot = nl * Mx * 3;
-        for (int idx = threadIdx.x; idx < tot; idx += NTHR) {
-            const int c = idx % 3;
-            const int rest = idx / 3;
-            const int e = rest % Mx;
-            const int yo = rest / Mx;
-            gq[idx] = lds[(yo * 3 + c) * Lp + e];
-        }
-    }
-    if (MODE == SC_S) {
-        // slots 5-7 of the block's entry; the gather of t (same grid) fills
-        // slots 0-4 and one finalize reads both
-        double* sh = (double*)(lds + nlines * Lp);
-        const int blk = blockIdx.y * bx + blockIdx.x;
-        publish_partial<3, NTHR, 5>(ss, a.partials + (long long)q * a.maxblk * PSTRIDE, blk, a.maxblk, sh);
-    }
-}
-
-// ------------------------------------------------------------------ pass 5
-
-// PRE (compile-time lengths): each element's site operands are loaded
-// before the inverse transform, so their latency overlaps it, at the price
-// of the registers that hold them (fewer waves per SIMD); else after it.
-template <typename T, int MODE, int LC, int NTHR, bool PRE = false>
-__global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const typename V2<T>::t* grid,
-                                                  const double2* tw64, int XLrt, int chk) {
-    using C = typename V2<T>::t;
-    constexpr bool CT = LC > 0;
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int q = blockIdx.z;
-    const RhsState* st = a.st + q;
-    if (skip_rhs(st, chk)) return;
-    int nx = g.n[0], ny = g.n[1];
-    const int* map = a.map;
-    const int* mat = a.mat;
-    const int Mx = CT ? LC : g.M[0];
-    const int My = g.M[1];
-    const int XL = CT ? 1 : XLrt;
-    const int z = blockIdx.y;
-    const int y0 = blockIdx.x * XL;
-    int bx = gridDim.x;
-    if (a.rg) {   // ragged batch: this right-hand side's target
-        const RhsGeo& r = a.rg[q];
-        if (z >= r.n[2] || y0 >= r.n[1]) return;
-        nx = r.n[0];
-        ny = r.n[1];
-        map += r.map_off;
-        mat += r.site_off;
-        bx = (ny + XL - 1) / XL;
-    }
-    const int nl = CT ? 1 : min(XL, ny - y0);
-    const int nlines = 3 * nl;
-    const int Lp = pad_len(Mx);
-    C* lds;
-    C* tws = nullptr;
-    if constexpr (CT) {
-        lds = (C*)smem;
-    } else {
-        tws = (C*)smem;
-        lds = tws + even_up(Mx);
-        load_twiddles<T, NTHR>(tws, tw64, g.ax[0]);
-    }
-    const int* mrow = map + ((long long)z * ny + y0) * nx;
-    const int tout = nl * nx * 3;
-    // compile-time lengths (one line per workgroup): the site index and
-    // material of each element this thread gathers are loaded before the
-    // transform, so only the operand loads follow it (e < nx <= (L + 1) / 2
-    // since L >= 2 nx - 1)
-    constexpr int PF = CT ? (3 * ((LC + 1) / 2) + NTHR - 1) / NTHR : 1;
-    int ps[PF], pm[PF];
-    if constexpr (CT) {
-#pragma unroll
-        for (int k = 0; k < PF; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            ps[k] = idx < tout ? mrow[idx / 3] : -1;
-        }
-    }
-    const C* gq = grid + ((long long)q * g.npts + ((long long)z * My + y0) * Mx) * 3;
-    if constexpr (CT) {
-        // the line's 3 LC values: every load in flight before the LDS stores
-        // (unrolled: the loads need not wait for one another)
-        constexpr int NPT = (3 * LC + NTHR - 1) / NTHR;
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            if ((3 * LC) % NTHR == 0 || idx < 3 * LC) lds[(idx % 3) * Lp + idx / 3] = gq[idx];
-        }
-    } else {
-        const int tot = nl * Mx * 3;
-        for (int idx = threadIdx.x; idx < tot; idx += NTHR) {
-            const int c = idx % 3;
-            const int rest = idx / 3;
-            const int e = rest % Mx;
-            const int yo = rest / Mx;
-            lds[(yo * 3 + c) * Lp + e] = gq[idx];
-        }
-    }
-    // the site operands of the gathered elements (what each mode reads
-    // besides the product), loaded before the transform so that their
-    // latency overlaps it
-    const long long vb = (long long)q * a.n3;
-    auto operand = [&](long long i) -> double2 {
-        if (MODE == GA_PLAIN || MODE == GA_CONJ) return a.in[i];
-        if (MODE == GA_V || MODE == GA_Q) return a.p[i];
-        if (MODE == GA_T || MODE == GA_B1) return a.r[i];
-        if (MODE == GA_RES) return a.x[i];
-        if (MODE == GA_B2) return a.v[i];
-        return a.t[i];   // GA_B3
-    };
-    constexpr bool HAS_AUX = MODE == GA_V || MODE == GA_T || MODE == GA_B1 || MODE == GA_B2 || MODE == GA_B3 ||
-                             MODE == GA_RES;
-    auto auxiliary = [&](long long i) -> double2 {
-        if (MODE == GA_RES) return a.b[i];
-        if (MODE == GA_B3) return a.r[i];
-        return a.rhat[i];
-    };
-    double2 px[PF], pa[PF];
-    if constexpr (CT && PRE) {
-        // (clamped to site 0 where there is no site: the value is unused)
-#pragma unroll
-        for (int k = 0; k < PF; ++k) pm[k] = mat[ps[k] >= 0 ? ps[k] : 0];
-#pragma unroll
-        for (int k = 0; k < PF; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            const long long i = vb + (long long)(ps[k] >= 0 ? ps[k] : 0) * 3 + idx % 3;
-            px[k] = operand(i);
-            pa[k] = HAS_AUX ? auxiliary(i) : double2{0.0, 0.0};
-        }
-    }
-    __syncthreads();
-    if constexpr (CT) {
-        // only e < nx is gathered: with 2 nx <= Mx the last pass skips the upper half
-        if (ct_half_out_ok(LC) && 2 * nx <= Mx) fft_lines_ct<T, 1, LC, 3, NTHR, false, true>(lds, tw64 + g.ax[0].tw);
-        else fft_lines_ct<T, 1, LC, 3, NTHR>(lds, tw64 + g.ax[0].tw);
-    } else {
-        fft_lines<T, 1, NTHR>(lds, tws, nlines, Lp, g.ax[0]);
-    }
-
-    const double2* ai = a.ainv + (long long)q * a.nmat * 3;
-    double acc[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    // element (line yo, point e, component c) at site s of material mt, with
-    // its operand xo and auxiliary vector value xa (as loaded)
-    auto site = [&](int c, int e, int yo, int s, int mt, double2 xo, double2 xa) {
-        const long long i = vb + (long long)s * 3 + c;
-        const double2 gv = to_d(lds[(yo * 3 + c) * Lp + e]);
-        const double2 d = ai[mt * 3 + c];
-        const double2 xin = MODE == GA_CONJ ? cconj(xo) : xo;
-        const double2 y = cadd(gv, cmul(d, xin));
-        if (MODE == GA_PLAIN) {
-            a.out[i] = y;
-        } else if (MODE == GA_CONJ) {
-            const double2 yc = cconj(y);
-            a.out[i] = yc;
-            acc[0] += yc.x * yc.x + yc.y * yc.y;
-        } else if (MODE == GA_V) {
-            a.v[i] = y;
-            const double2 w = cdotc(xa, y);
-            acc[0] += w.x;
-            acc[1] += w.y;
-            acc[2] += y.x * y.x + y.y * y.y;   // |v|^2: bounds <rhat, v> with |rhat|
-        } else if (MODE == GA_T) {
-            a.t[i] = y;
-            const double2 w = cdotc(y, xin);    // <t, s>
-            const double2 wr = cdotc(xa, y);    // <rhat, t>
-            acc[0] += w.x;
-            acc[1] += w.y;
-            acc[2] += y.x * y.x + y.y * y.y;
-            acc[3] += wr.x;
-            acc[4] += wr.y;
-        } else if (MODE == GA_Q) {
-            a.v[i] = y;
-            acc[0] += xin.x * y.x - xin.y * y.y;   // p^T v (bilinear)
-            acc[1] += xin.x * y.y + xin.y * y.x;
-            acc[2] += y.x * y.x + y.y * y.y;       // |v|^2 and |p|^2 bound |p^T v|
-            acc[3] += xin.x * xin.x + xin.y * xin.y;
-        } else if (MODE == GA_B1 || MODE == GA_B2) {
-            // r_1 = A r_0 or u_2 = A u_1, and <rhat, .>
-            if (MODE == GA_B1) a.t[i] = y;
-            else a.u2[i] = y;
-            const double2 w = cdotc(xa, y);
-            acc[0] += w.x;
-            acc[1] += w.y;
-            acc[2] += y.x * y.x + y.y * y.y;
-        } else if (MODE == GA_B3) {
-            // r_2 = A r_1 and the minimal-residual sums |r_1|^2, <r_1, r_2>,
-            // |r_2|^2, <r_1, r_0>, <r_2, r_0>
-            a.r2[i] = y;
-            const double2 r0 = xa;
-            const double2 w12 = cdotc(xin, y), w10 = cdotc(xin, r0), w20 = cdotc(y, r0);
-            acc[0] += xin.x * xin.x + xin.y * xin.y;
-            acc[1] += w12.x;
-            acc[2] += w12.y;
-            acc[3] += y.x * y.x + y.y * y.y;
-            acc[4] += w10.x;
-            acc[5] += w10.y;
-            acc[6] += w20.x;
-            acc[7] += w20.y;
-        } else {
-            const double2 rr = csub(xa, y);
-            a.r[i] = rr;
-            acc[0] += rr.x * rr.x + rr.y * rr.y;
-        }
-    };
-    if constexpr (CT) {
-#pragma unroll
-        for (int k = 0; k < PF; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            if (idx < tout && ps[k] >= 0) {
-                if constexpr (PRE) {
-                    site(idx % 3, idx / 3, 0, ps[k], pm[k], px[k], pa[k]);
-                } else {
-                    const long long i = vb + (long long)ps[k] * 3 + idx % 3;
-                    site(idx % 3, idx / 3, 0, ps[k], pm[k], operand(i),
-                         HAS_AUX ? auxiliary(i) : double2{0.0, 0.0});
-                }
-            }
-        }
-    } else {
-        for (int idx = threadIdx.x; idx < tout; idx += NTHR) {
-            const int c = idx % 3;
-            const int rest = idx / 3;
-            const int e = rest % nx;
-            const int yo = rest / nx;
-            const int s = mrow[yo * nx + e];
-            if (s >= 0) {
-                const long long i = vb + (long long)s * 3 + c;
-                site(c, e, yo, s, mat[s], operand(i), HAS_AUX ? auxiliary(i) : double2{0.0, 0.0});
-            }
-        }
-    }
-    if (MODE != GA_PLAIN) {
-        double* sh = (double*)(lds + nlines * Lp);
-        const int blk = blockIdx.y * bx + blockIdx.x;
-        if constexpr (MODE == GA_B3) {
-            publish_partial<8, NTHR>(acc, a.partials + (long long)q * a.maxblk * PSTRIDE, blk, a.maxblk, sh);
-        } else if constexpr (MODE == GA_T) {
-            double a5[5] = {acc[0], acc[1], acc[2], acc[3], acc[4]};
-            publish_partial<5, NTHR>(a5, a.partials + (long long)q * a.maxblk * PSTRIDE, blk, a.maxblk, sh);
-        } else if constexpr (MODE == GA_Q) {
-            double a4[4] = {acc[0], acc[1], acc[2], acc[3]};
-            publish_partial<4, NTHR>(a4, a.partials + (long long)q * a.maxblk * PSTRIDE, blk, a.maxblk, sh);
-        } else {
-            double a3[3] = {acc[0], acc[1], acc[2]};
-            publish_partial<3, NTHR>(a3, a.partials + (long long)q * a.maxblk * PSTRIDE, blk, a.maxblk, sh);
-        }
-    }
-}
-
 // ------------------------------------------------------------------ passes 2-4
 
 // Right-hand side q of a strided pass in a ragged batch (g.rg): the y passes
@@ -1343,57 +804,6 @@ void k_zsq(Geo g, typename V2<T>::t* grid, const double2* tw64, const typename V
 
 // ------------------------------------------------------------------ launchers
 
-template <typename T, int MODE>
-void scatter_dispatch(int chk, const Geo& g, const SiteArgs& a, typename V2<T>::t* grid, const double2* tw,
-                      hipStream_t s) {
-    using C = typename V2<T>::t;
-    const int L = g.M[0];
-    const int XL = x_lines_per_tile(g, a.nrhs, sizeof(T) == 4);
-    dim3 grd((g.n[1] + XL - 1) / XL, g.n[2], a.nrhs);
-    switch (L) {
-#define DDA_CASE(LL)                                                                                            \
-    case LL:                                                                                                   \
-        DDA_LAUNCH((k_scatter_x<T, MODE, LL, xthr(LL)>), grd, dim3(xthr(LL)), smem_ct<C>(LL, 3), s, g, a, grid, \
-                           tw, 1, chk);                                                                        \
-        return;
-        DDA_CT_LENGTHS(DDA_CASE)
-#undef DDA_CASE
-        default:
-            DDA_LAUNCH((k_scatter_x<T, MODE, 0, NT>), grd, dim3(NT), smem_rt<C>(L, 3 * XL), s, g, a, grid,
-                               tw, XL, chk);
-    }
-}
-
-template <typename T, int MODE>
-void gather_dispatch(int chk, const Geo& g, const SiteArgs& a, const typename V2<T>::t* grid, const double2* tw,
-                     hipStream_t s) {
-    using C = typename V2<T>::t;
-    const int L = g.M[0];
-    const int XL = x_lines_per_tile(g, a.nrhs, sizeof(T) == 4);
-    dim3 grd((g.n[1] + XL - 1) / XL, g.n[2], a.nrhs);
-    // operands before the transform pay in launches of few right-hand sides
-    // (latency-bound workgroups); with many, the launch is bandwidth-bound
-    // and the registers they take cost more occupancy than they save
-    // (measured: 2-RHS solves gain, the 128-RHS brick loses 10%)
-    const bool pre = a.nrhs <= 16;
-    switch (L) {
-#define DDA_CASE(LL)                                                                                            \
-    case LL:                                                                                                   \
-        if (pre)                                                                                               \
-            DDA_LAUNCH((k_gather_x<T, MODE, LL, xthr(LL), true>), grd, dim3(xthr(LL)), smem_ct<C>(LL, 3), s, g, \
-                       a, grid, tw, 1, chk);                                                                   \
-        else                                                                                                   \
-            DDA_LAUNCH((k_gather_x<T, MODE, LL, xthr(LL), false>), grd, dim3(xthr(LL)), smem_ct<C>(LL, 3), s,   \
-                       g, a, grid, tw, 1, chk);                                                                \
-        return;
-        DDA_CT_LENGTHS(DDA_CASE)
-#undef DDA_CASE
-        default:
-            DDA_LAUNCH((k_gather_x<T, MODE, 0, NT>), grd, dim3(NT), smem_rt<C>(L, 3 * XL), s, g, a, grid,
-                               tw, XL, chk);
-    }
-}
-
 // Compile-time variants of a strided pass.  LDS form (k_strided, k_zfold):
 // (tile width, VAR, XCD order), indices 0 .. n_lds_variants - 1, index 0 the
 // default.
@@ -1620,40 +1030,6 @@ void strided_dispatch(int variant, int axis, int chk, const Geo& g, int nrhs, in
 // ------------------------------------------------------------------ entry points
 
 template <typename T>
-void launch_scatter_x(int mode, int chk, const Geo& g, const SiteArgs& a, typename V2<T>::t* grid, const double2* tw,
-                      hipStream_t s) {
-    using namespace passes;
-    switch (mode) {
-        case SC_PLAIN: scatter_dispatch<T, SC_PLAIN>(chk, g, a, grid, tw, s); break;
-        case SC_CONJ: scatter_dispatch<T, SC_CONJ>(chk, g, a, grid, tw, s); break;
-        case SC_P: scatter_dispatch<T, SC_P>(chk, g, a, grid, tw, s); break;
-        case SC_Q: scatter_dispatch<T, SC_Q>(chk, g, a, grid, tw, s); break;
-        case SC_B0: scatter_dispatch<T, SC_B0>(chk, g, a, grid, tw, s); break;
-        case SC_B1: scatter_dispatch<T, SC_B1>(chk, g, a, grid, tw, s); break;
-        case SC_B2: scatter_dispatch<T, SC_B2>(chk, g, a, grid, tw, s); break;
-        case SC_B3: scatter_dispatch<T, SC_B3>(chk, g, a, grid, tw, s); break;
-        default: scatter_dispatch<T, SC_S>(chk, g, a, grid, tw, s); break;
-    }
-}
-
-template <typename T>
-void launch_gather_x(int mode, int chk, const Geo& g, const SiteArgs& a, const typename V2<T>::t* grid,
-                     const double2* tw, hipStream_t s) {
-    using namespace passes;
-    switch (mode) {
-        case GA_PLAIN: gather_dispatch<T, GA_PLAIN>(chk, g, a, grid, tw, s); break;
-        case GA_CONJ: gather_dispatch<T, GA_CONJ>(chk, g, a, grid, tw, s); break;
-        case GA_V: gather_dispatch<T, GA_V>(chk, g, a, grid, tw, s); break;
-        case GA_T: gather_dispatch<T, GA_T>(chk, g, a, grid, tw, s); break;
-        case GA_Q: gather_dispatch<T, GA_Q>(chk, g, a, grid, tw, s); break;
-        case GA_B1: gather_dispatch<T, GA_B1>(chk, g, a, grid, tw, s); break;
-        case GA_B2: gather_dispatch<T, GA_B2>(chk, g, a, grid, tw, s); break;
-        case GA_B3: gather_dispatch<T, GA_B3>(chk, g, a, grid, tw, s); break;
-        default: gather_dispatch<T, GA_RES>(chk, g, a, grid, tw, s); break;
-    }
-}
-
-template <typename T>
 void launch_strided(int axis, int dir, int chk, const Geo& g, int nrhs, int nc, int n_outer, int lin, int lout,
                     typename V2<T>::t* grid, const double2* tw, const typename V2<T>::t* ghat, const RhsState* st,
                     hipStream_t s, int variant) {
@@ -1672,10 +1048,6 @@ static_assert(passes::n_strided_variants(1) == 28 && passes::n_strided_variants(
               "strided_variants() in dda_kernels.h counts these variants");
 
 #define DDA_INSTANTIATE_PASSES(T)                                                                                 \
-    template void launch_scatter_x<T>(int, int, const Geo&, const SiteArgs&, V2<T>::t*, const double2*,           \
-                                      hipStream_t);                                                              \
-    template void launch_gather_x<T>(int, int, const Geo&, const SiteArgs&, const V2<T>::t*, const double2*,      \
-                                     hipStream_t);                                                               \
     template void launch_strided<T>(int, int, int, const Geo&, int, int, int, int, int, V2<T>::t*, const double2*, \
                                     const V2<T>::t*, const RhsState*, hipStream_t, int);
 
