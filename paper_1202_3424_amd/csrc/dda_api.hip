@@ -1706,6 +1706,27 @@ dda_target* nf_target(dda_ctx* c, dda_target* t, const int e[6], const int org[3
     return t->nf;
 }
 
+// y = A x for the caller's vectors.  The x passes take them in caller order
+// themselves; where x and y overlap in part, through sorted copies in the
+// work vectors (a site's output could overwrite another's input).
+void plain_product(Work& w, const dda_c64* x, dda_c64* y) {
+    const size_t n = (size_t)w.nrhs * w.a.n3;
+    const int* perm = (const int*)w.t->perm.p;
+    const bool apart = x + n <= y || y + n <= x;
+    if (apart) {
+        w.a.perm = perm;
+        w.a.in = (const double2*)x;
+        w.a.out = (double2*)y;
+    } else {
+        launch_permute(w.nrhs, w.t->nsites, 3, perm, (const double2*)x, w.a.p, true, w.s);
+        w.a.in = w.a.p;
+        w.a.out = w.a.v;
+    }
+    w.matvec(SC_PLAIN, GA_PLAIN, CHK_NONE, CHK_NONE);
+    if (!apart) launch_permute(w.nrhs, w.t->nsites, 3, perm, w.a.v, (double2*)y, false, w.s);
+    HIPCHK(hipGetLastError());
+}
+
 }  // namespace
 
 // ====================================================================== ABI
@@ -1811,12 +1832,7 @@ dda_status dda_apply(dda_ctx* c, dda_target* t, const dda_opts* o, int32_t n_rhs
         w.autotune((o->flags & DDA_FLAG_NO_AUTOTUNE) == 0, o->kernel_variant);
         w.upload_incidence(kh, e0);
         w.alpha_table(o->polarizability, o->m_medium, (double2*)w.a.ainv);
-        launch_permute(n_rhs, t->nsites, 3, (const int*)t->perm.p, (const double2*)x, w.a.p, true, c->stream);
-        w.a.in = w.a.p;
-        w.a.out = w.a.v;
-        w.matvec(SC_PLAIN, GA_PLAIN, CHK_NONE, CHK_NONE);
-        launch_permute(n_rhs, t->nsites, 3, (const int*)t->perm.p, w.a.v, (double2*)y, false, c->stream);
-        HIPCHK(hipGetLastError());
+        plain_product(w, x, y);
         return DDA_OK;
     });
 }
@@ -1854,12 +1870,7 @@ dda_status dda_apply_noalloc(dda_ctx* c, dda_target* t, const dda_opts* o, int32
         w.autotune(false, o->kernel_variant);   // the tiling tuned for this shape, else the default
         w.upload_incidence(khv, e0v);
         w.alpha_table(o->polarizability, o->m_medium, (double2*)w.a.ainv);
-        launch_permute(n_rhs, t->nsites, 3, (const int*)t->perm.p, (const double2*)x, w.a.p, true, w.s);
-        w.a.in = w.a.p;
-        w.a.out = w.a.v;
-        w.matvec(SC_PLAIN, GA_PLAIN, CHK_NONE, CHK_NONE);
-        launch_permute(n_rhs, t->nsites, 3, (const int*)t->perm.p, w.a.v, (double2*)y, false, w.s);
-        HIPCHK(hipGetLastError());
+        plain_product(w, x, y);
         return DDA_OK;
     });
 }

@@ -89,6 +89,7 @@ struct SiteArgs {
     double2* r2;           // BiCGstab(2): third residual
     const double2* in;     // input of the plain / conjugated product
     double2* out;          // output of the plain / conjugated product
+    const int* perm;       // plain product: in and out are in caller order, site s at perm[s]; else null
     RhsState* st;          // [nrhs]
     double* partials;      // [nrhs][PSTRIDE][maxblk] per-workgroup sums of the last reducing kernel
     double* chains;        // [nrhs][PSTRIDE][NT] k_finalize's per-thread sums of them, or null

@@ -77,6 +77,12 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
     struct Ops {
         double2 o[6];
     };
+    // element (site s, component c) of this mode's vectors: the plain
+    // product may take its input in the caller's site order
+    auto elem = [&](int s, int c) -> long long {
+        if (MODE == SC_PLAIN && a.perm) s = a.perm[s];
+        return vb + (long long)s * 3 + c;
+    };
     auto load_ops = [&](long long i) {
         Ops v;
         if (MODE == SC_PLAIN || MODE == SC_CONJ) {
@@ -190,14 +196,14 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
             const int idx = threadIdx.x + k * NTHR;
-            ok[k] = load_ops(vb + (long long)(sk[k] >= 0 ? sk[k] : 0) * 3 + idx % 3);
+            ok[k] = load_ops(elem(sk[k] >= 0 ? sk[k] : 0, idx % 3));
         }
         double2 uk[NPT];
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
             const int idx = threadIdx.x + k * NTHR;
             const bool live = sk[k] >= 0;
-            uk[k] = update(vb + (long long)(live ? sk[k] : 0) * 3 + idx % 3, ok[k], live);
+            uk[k] = update(MODE == SC_PLAIN ? 0 : elem(live ? sk[k] : 0, idx % 3), ok[k], live);
         }
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
@@ -230,7 +236,7 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
             if (e < nx) {
                 const int s = mrow[yo * nx + e];
                 if (s >= 0) {
-                    const long long i = vb + (long long)s * 3 + c;
+                    const long long i = elem(s, c);
                     val = to_c<C>(update(i, load_ops(i), true));
                 }
             }
@@ -354,6 +360,10 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
     // besides the product), loaded before the transform so that their
     // latency overlaps it
     const long long vb = (long long)q * a.n3;
+    auto elem = [&](int s, int c) -> long long {   // (see k_scatter_x)
+        if (MODE == GA_PLAIN && a.perm) s = a.perm[s];
+        return vb + (long long)s * 3 + c;
+    };
     auto operand = [&](long long i) -> double2 {
         if (MODE == GA_PLAIN || MODE == GA_CONJ) return a.in[i];
         if (MODE == GA_V || MODE == GA_Q) return a.p[i];
@@ -377,7 +387,7 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
 #pragma unroll
         for (int k = 0; k < PF; ++k) {
             const int idx = threadIdx.x + k * NTHR;
-            const long long i = vb + (long long)(ps[k] >= 0 ? ps[k] : 0) * 3 + idx % 3;
+            const long long i = elem(ps[k] >= 0 ? ps[k] : 0, idx % 3);
             px[k] = operand(i);
             pa[k] = HAS_AUX ? auxiliary(i) : double2{0.0, 0.0};
         }
@@ -396,7 +406,7 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
     // element (line yo, point e, component c) at site s of material mt, with
     // its operand xo and auxiliary vector value xa (as loaded)
     auto site = [&](int c, int e, int yo, int s, int mt, double2 xo, double2 xa) {
-        const long long i = vb + (long long)s * 3 + c;
+        const long long i = elem(s, c);
         const double2 gv = to_d(lds[(yo * 3 + c) * Lp + e]);
         const double2 d = ai[mt * 3 + c];
         const double2 xin = MODE == GA_CONJ ? cconj(xo) : xo;
@@ -464,7 +474,7 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
                 if constexpr (PRE) {
                     site(idx % 3, idx / 3, 0, ps[k], pm[k], px[k], pa[k]);
                 } else {
-                    const long long i = vb + (long long)ps[k] * 3 + idx % 3;
+                    const long long i = elem(ps[k], idx % 3);
                     site(idx % 3, idx / 3, 0, ps[k], pm[k], operand(i),
                          HAS_AUX ? auxiliary(i) : double2{0.0, 0.0});
                 }
@@ -478,7 +488,7 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
             const int yo = rest / nx;
             const int s = mrow[yo * nx + e];
             if (s >= 0) {
-                const long long i = vb + (long long)s * 3 + c;
+                const long long i = elem(s, c);
                 site(c, e, yo, s, mat[s], operand(i), HAS_AUX ? auxiliary(i) : double2{0.0, 0.0});
             }
         }
