@@ -105,11 +105,11 @@ def kernel_source_digest() -> str:
 # x += alpha p + omega s, r = s - omega t, then p = r + beta(p - omega v));
 # the scatter of s = r - alpha v reads r, v, rhat and writes r; each gather
 # reads its input and rhat and writes its output.  QMR: the scatter reads r,
-# p and the smoothed pair (s, y) and x, and writes p, s, y; the gather reads
+# p and the smoothed pair (s, y) and x, and writes p, s, y, x; the gather reads
 # p and writes v.  BiCGstab(2): 3, 6, 6 and 9 vectors in the four scatters,
 # 3 in every gather.  The plain product (near field): its input, and input
 # plus output.
-SITE_VECTORS = {"bicgstab": (6, 3), "qmr": (8, 2), "bicgstab2": (6, 3), "plain": (1, 2)}
+SITE_VECTORS = {"bicgstab": (6, 3), "qmr": (9, 2), "bicgstab2": (6, 3), "plain": (1, 2)}
 
 
 def pass_bytes(tgt, n_sites: int, csize: int, solver: str = "bicgstab", plane: bool = False) -> dict:

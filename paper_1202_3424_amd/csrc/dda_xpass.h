@@ -58,7 +58,7 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
     int pend = 0;
     if (MODE == SC_P) { beta = st->beta; omega = st->omega; alpha = st->alpha; pend = st->pend; }
     if (MODE == SC_S) alpha = st->alpha;
-    if (MODE == SC_Q) { beta = st->beta; w_old = st->w_old; w_new = st->w_new; }
+    if (MODE == SC_Q) { alpha = st->alpha; beta = st->beta; w_old = st->w_old; w_new = st->w_new; }
     if (MODE == SC_B0 || MODE == SC_B2) beta = st->beta;
     if (MODE == SC_B1 || MODE == SC_B3) alpha = st->alpha;
     const long long vb = (long long)q * a.n3;
@@ -156,12 +156,15 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
                 a.x[i] = cadd(v.o[4], cmul(alpha, v.o[5]));
             }
         } else if (MODE == SC_Q) {
-            // QMR: p = r + beta p, and the pending smoothing step
-            // (y, s) <- w_old (y, s) + w_new (x, r)
+            // QMR: the previous iteration's x += alpha p (p = 0 after a
+            // start), the pending smoothing step (y, s) <- w_old (y, s) +
+            // w_new (x, r), and p = r + beta p
             const double2 rr = v.o[0];
             u = cadd(rr, cmul(beta, v.o[1]));
             if (live) {
-                const double2 sm = v.o[2], ym = v.o[3], xx = v.o[4];
+                const double2 sm = v.o[2], ym = v.o[3];
+                const double2 xx = cadd(v.o[4], cmul(alpha, v.o[1]));
+                a.x[i] = xx;
                 a.p[i] = u;
                 a.rhat[i] = double2{w_old * sm.x + w_new * rr.x, w_old * sm.y + w_new * rr.y};
                 a.t[i] = double2{w_old * ym.x + w_new * xx.x, w_old * ym.y + w_new * xx.y};
