@@ -703,8 +703,8 @@ struct Work {
         if (sizeof(T) == 4 ? plane32 : plane64) {
             Timed tm(c, T_FFTZ_G, s);
             const dda_target* src = segs.empty() ? t : segs[0].t;
-            launch_plane<T>(chk_rest, g, nrhs, gr, tw, (const C*)(sizeof(T) == 4 ? src->gp32.p : src->gp64.p), a.st,
-                            s);
+            const void* gp = plane_short<T>(g) ? ghat(sizeof(T) == 4) : sizeof(T) == 4 ? src->gp32.p : src->gp64.p;
+            launch_plane<T>(chk_rest, g, nrhs, gr, tw, (const C*)gp, a.st, s);
         } else {
             {
                 Timed tm(c, T_FFTY_FWD, s);
@@ -731,9 +731,13 @@ struct Work {
     }
     // fp64: force an FP64 product in the FP32-matvec mode (refinement, checks)
     void matvec(int sc, int ga, int chk_sc, int chk_rest, bool fp64 = false) {
-        static const int defaults[3] = {0, 0, 0};
-        if (fp32 && !fp64) matvec_t<float>(sc, ga, chk_sc, chk_rest, var);
-        else matvec_t<double>(sc, ga, chk_sc, chk_rest, fp32 ? defaults : var);
+        if (fp32 && !fp64) {
+            matvec_t<float>(sc, ga, chk_sc, chk_rest, var);
+        } else {
+            const int* M = t->geo.M;
+            const int check[3] = {check_variant(M[1], 0), check_variant(M[2], 1), check_variant(M[1], 2)};
+            matvec_t<double>(sc, ga, chk_sc, chk_rest, fp32 ? check : var);
+        }
         HIPCHK(hipGetLastError());
     }
 };
@@ -753,7 +757,8 @@ void ensure_green(dda_ctx* c, dda_target* t, double kd, bool fp32, bool force) {
     launch_green(g, kd, work, g64, g32, tw, c->stream);
     // the plane kernel's layout, where it takes this grid (with any number of
     // right-hand sides; launch limits are checked with the product)
-    const bool p64 = plane_fits<double>(g, 1), p32 = fp32 && plane_fits<float>(g, 1);
+    const bool p64 = plane_fits<double>(g, 1) && !plane_short<double>(g);
+    const bool p32 = fp32 && plane_fits<float>(g, 1) && !plane_short<float>(g);
     if (p64 || p32)
         launch_green_plane(g, g64, p64 ? (double2*)t->gp64.ensure(plane_values(g) * sizeof(double2)) : nullptr,
                            p32 ? (float2*)t->gp32.ensure(plane_values(g) * sizeof(float2)) : nullptr, c->stream);

@@ -173,6 +173,17 @@ void launch_strided(int axis, int dir, int chk, const Geo& g, int nrhs, int nc, 
                     typename V2<T>::t* grid, const double2* tw, const typename V2<T>::t* ghat, const RhsState* st,
                     hipStream_t s, int variant = 0);
 inline int strided_variants(int L, bool gh) { return ct_length(L) ? (gh ? 28 : 12) : 1; }
+// Fixed choices for FP64 products beside an FP32-matvec solve (residual
+// checks; too few to tune for): slot 0 y forward, 1 z with tensor, 2 y
+// inverse.  Measured on cubes, two right-hand sides, us per launch against
+// variant 0: 128 25, 82, 26 (34, 105, 39); 160 59, 192, 71 (73, 233, 81); 192
+// 97, 422, 96 (153, 532, 173); 256 239, 787, 235 (395, 1276, 400); 384 976,
+// 4483, 1004 (1490, 5297, 1802).
+constexpr int check_variant(int L, int slot) {
+    if (L < 128) return 0;
+    if (slot == 1) return L == 256 ? 25 : 10;
+    return (L == 192 || L > 256) ? 10 : 11;
+}
 // the variants a ragged batch runs: every y-pass variant, and the pass-3
 // variants that take one right-hand side per workgroup (each right-hand side
 // reads its own tensor and extent); the others run as variant 3 there
@@ -189,6 +200,8 @@ template <typename T>
 void launch_plane(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, const double2* tw,
                   const typename V2<T>::t* gp, const RhsState* st, hipStream_t s);
 template <typename T> bool plane_fits(const Geo& g, int nrhs);
+// whether that is the short-length kernel, which reads the octant itself
+template <typename T> bool plane_short(const Geo& g);
 // stored ky of a tensor row in that layout: LY / 2 + 1 and padding up to a
 // 128-byte (FP64) or 64-byte (FP32) boundary
 constexpr int plane_row(int LY) { return (LY / 2 + 1 + 7) & ~7; }

@@ -354,6 +354,98 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(WV))) void
     }
 }
 
+// ------------------------------------------------------------------ short lengths
+// The same fusion for grids with y and z extents of at most 20, which have no
+// compile-time kernels (targets of up to about ten sites across): the
+// plane of one kx in LDS as y lines (z, c) and as z lines (ky, c), the
+// runtime-planned transforms on each.  Bounded by latency: launches and
+// barriers (18^3, two right-hand sides, FP64: 15 us against 33 as three
+// kernels).
+
+// LDS values of the two forms of the plane and the twiddles of both axes
+constexpr size_t rt_values(int LY, int LZ, int nz) {
+    return (size_t)3 * nz * (LY | 1) + (size_t)3 * LY * (LZ | 1) + ((LY + 1) & ~1) + ((LZ + 1) & ~1);
+}
+
+template <typename T>
+__global__ __launch_bounds__(NT) void k_plane_rt(Geo g, AxisPlan py, AxisPlan pz, typename V2<T>::t* grid,
+                                                const double2* tw64, const typename V2<T>::t* ghat,
+                                                const RhsState* st, int chk) {
+    using C = typename V2<T>::t;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int kx = blockIdx.x, q = blockIdx.y;
+    if (passes::skip_rhs(st + q, chk)) return;
+    const int Mx = g.M[0], My = py.L, Mz = pz.L, ny = g.n[1], nz = g.n[2];
+    const int Ly = My | 1, Lz = Mz | 1;
+    C* twy = (C*)smem;
+    C* twz = twy + ((My + 1) & ~1);
+    C* A = twz + ((Mz + 1) & ~1);   // [z][c][Ly]
+    C* B = A + 3 * nz * Ly;         // [ky][c][Lz]
+    load_twiddles<T>(twy, tw64, py);
+    load_twiddles<T>(twz, tw64, pz);
+    C* gq = grid + (long long)q * g.npts * 3 + (long long)kx * 3;
+    // lines per call of the runtime transform (its tile bound)
+    const int by = Tile<T>::EMAX / My, bz = Tile<T>::EMAX / Mz;
+    C zero;
+    zero.x = 0;
+    zero.y = 0;
+    for (int i = threadIdx.x; i < 3 * nz * My; i += NT) {
+        const int c = i % 3, y = i / 3 % My, z = i / (3 * My);
+        A[(z * 3 + c) * Ly + y] = y < ny ? gq[((long long)z * My + y) * Mx * 3 + c] : zero;
+    }
+    __syncthreads();
+    for (int l = 0; l < 3 * nz; l += by) fft_lines<T, -1>(A + l * Ly, twy, min(by, 3 * nz - l), Ly, py);
+    for (int i = threadIdx.x; i < 3 * My * Mz; i += NT) {
+        const int ky = i % My, z = i / My % Mz, c = i / (My * Mz);
+        B[(ky * 3 + c) * Lz + z] = z < nz ? A[(z * 3 + c) * Ly + ky] : zero;
+    }
+    __syncthreads();
+    for (int l = 0; l < 3 * My; l += bz) fft_lines<T, -1>(B + l * Lz, twz, min(bz, 3 * My - l), Lz, pz);
+    const bool ux = kx > Mx / 2;
+    const int fx = ux ? Mx - kx : kx;
+    for (int i = threadIdx.x; i < My * Mz; i += NT) {
+        const int ky = i % My, kz = i / My;
+        const bool uy = ky > My / 2, uz = kz > Mz / 2;
+        const int fy = uy ? My - ky : ky, fz = uz ? Mz - kz : kz;
+        const C* Gp = ghat + (((long long)fz * g.H[1] + fy) * g.H[0] + fx) * 6;
+        C G[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) G[k] = Gp[k];
+        // diagonal components are even in every index, ab is odd in a and b
+        if (ux != uy) { G[1].x = -G[1].x; G[1].y = -G[1].y; }
+        if (ux != uz) { G[2].x = -G[2].x; G[2].y = -G[2].y; }
+        if (uy != uz) { G[4].x = -G[4].x; G[4].y = -G[4].y; }
+        C* p = B + ky * 3 * Lz + kz;
+        const C X = p[0], Y = p[Lz], Z = p[2 * Lz];
+        p[0] = passes::trow(G[0], G[1], G[2], X, Y, Z);
+        p[Lz] = passes::trow(G[1], G[3], G[4], X, Y, Z);
+        p[2 * Lz] = passes::trow(G[2], G[4], G[5], X, Y, Z);
+    }
+    __syncthreads();
+    for (int l = 0; l < 3 * My; l += bz) fft_lines<T, 1>(B + l * Lz, twz, min(bz, 3 * My - l), Lz, pz);
+    for (int i = threadIdx.x; i < 3 * My * nz; i += NT) {
+        const int z = i % nz, ky = i / nz % My, c = i / (nz * My);
+        A[(z * 3 + c) * Ly + ky] = B[(ky * 3 + c) * Lz + z];
+    }
+    __syncthreads();
+    for (int l = 0; l < 3 * nz; l += by) fft_lines<T, 1>(A + l * Ly, twy, min(by, 3 * nz - l), Ly, py);
+    for (int i = threadIdx.x; i < 3 * nz * ny; i += NT) {
+        const int c = i % 3, y = i / 3 % ny, z = i / (3 * ny);
+        gq[((long long)z * My + y) * Mx * 3 + c] = A[(z * 3 + c) * Ly + y];
+    }
+}
+
+// The radix sequence the strided passes use on an axis: a compile-time
+// length's, or the runtime plan's.
+inline AxisPlan strided_plan(const AxisPlan& ax) {
+    AxisPlan p = ax;
+    if (ct_plan(ax.L, -1) > 0) {
+        p.nst = ct_plan(ax.L, -1);
+        for (int i = 0; i < p.nst; ++i) p.R[i] = ct_plan(ax.L, i);
+    }
+    return p;
+}
+
 // ------------------------------------------------------------------ launcher
 
 template <typename T, int LY, int LZ>
@@ -383,10 +475,27 @@ bool plane_launch_z(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, co
 
 }  // namespace plane
 
+// The short-length kernel takes grids of one target with at most 20 points
+// along y and z, the lengths below the shortest compile-time one.  Measured,
+// us for passes 2-4 here and as three kernels: 18 x 18, two right-hand sides
+// 15 and 33, thirty-two 24 and 235; but 20 x 48, whose z pass has a
+// compile-time kernel, 28 and 19.
+template <typename T> bool plane_short(const Geo& g) {
+    return !g.rg && g.M[1] <= 20 && g.M[2] <= 20 &&
+           plane::rt_values(g.M[1], g.M[2], g.n[2]) * sizeof(typename V2<T>::t) <= plane::PLANE_LDS;
+}
+
 template <typename T>
 void launch_plane(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, const double2* tw,
                   const typename V2<T>::t* gp, const RhsState* st, hipStream_t s) {
     bool done = false;
+    if (plane_short<T>(g)) {
+        hipStream_t stream = s;
+        DDA_LAUNCH((plane::k_plane_rt<T>), dim3(g.M[0], nrhs), dim3(NT),
+                   plane::rt_values(g.M[1], g.M[2], g.n[2]) * sizeof(typename V2<T>::t), stream, g,
+                   plane::strided_plan(g.ax[1]), plane::strided_plan(g.ax[2]), grid, tw, gp, st, chk);
+        return;
+    }
     switch (g.M[1]) {
 #define DDA_Y(L) \
     case L: done = plane::plane_launch_z<T, L>(chk, g, nrhs, grid, tw, gp, st, s); break;
@@ -401,6 +510,7 @@ void launch_plane(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, cons
 // plane, with the occupied z extent, fits the LDS, and a launch within the
 // grid limit.
 template <typename T> bool plane_fits(const Geo& g, int nrhs) {
+    if (plane_short<T>(g)) return nrhs <= 65535;
     if (!plane::plane_pair<T>(g.M[1], g.M[2]) || 2 * g.n[1] > g.M[1] || 2 * g.n[2] > g.M[2]) return false;
     return (long long)(g.M[0] + passes::N_XCD) * nrhs * 768 < (1LL << 32);
 }
@@ -408,6 +518,7 @@ template <typename T> bool plane_fits(const Geo& g, int nrhs) {
 #define DDA_INSTANTIATE_PLANE(T)                                                                                \
     template void launch_plane<T>(int, const Geo&, int, V2<T>::t*, const double2*, const V2<T>::t*,              \
                                   const RhsState*, hipStream_t);                                                \
-    template bool plane_fits<T>(const Geo&, int);
+    template bool plane_fits<T>(const Geo&, int);                                                               \
+    template bool plane_short<T>(const Geo&);
 
 }  // namespace dda

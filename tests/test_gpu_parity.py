@@ -1496,3 +1496,46 @@ def test_far_field_by_lines_in_groups_of_right_hand_sides(dda):
     for i in (0, 1, 300, 433, q - 1):
         fi, _ = dda.far_field(tgt, opts, P[i:i + 1], nh, th, ph)
         assert np.array_equal(f[i], fi[0])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_matvec"])
+@pytest.mark.parametrize("short", [1, 3, 7, 9, 10])
+def test_short_plane_kernel_equals_the_three_passes(dda, precision, short):
+    """Grids with a y or z extent of at most 20 (runtime-planned), the other
+    short too (the short-length plane kernel) or compile-time: the product is
+    bitwise that of the three separate passes, which a named variant selects."""
+    for other in (1, 2, 8, 10, 11, 16, 24, 32, 40, 48, 50):
+        for ny, nz in ((short, other), (other, short)):
+            rng = np.random.default_rng(100 * ny + nz)
+            keep = rng.random((5, ny, nz)) < 0.3
+            keep[0, 0, 0] = keep[-1, -1, -1] = True
+            ijk = np.argwhere(keep).astype(np.int32)
+            tgt = dda.Target(ijk, 1.4 + 0.1j)
+            kh, e0 = w.along_x_yz()
+            xv = _cuda(w.random_vectors(32, (2, len(ijk), 3)))
+            y = dda.apply(tgt, dda.Options.for_size_parameter(1.0, precision=precision), kh, e0, xv)
+            ref = dda.apply(tgt, dda.Options.for_size_parameter(1.0, precision=precision, kernel_variant=1), kh, e0,
+                            xv)
+            assert torch.equal(y, ref), (ny, nz)
+
+
+def test_apply_with_overlapping_vectors(dda):
+    """x and y of a product that overlap in part (one buffer, y a right-hand
+    side further on): the same result as with separate buffers, the caller's
+    order being taken through sorted copies then."""
+    import ctypes
+    from paper_1202_3424_amd import _abi, api
+    ijk = w.sphere_integer(4.5)
+    n = len(ijk)
+    tgt = dda.Target(ijk, 1.4 + 0.1j)
+    kh, e0 = w.along_x_yz()
+    opts = dda.Options.for_size_parameter(1.0)
+    xv = _cuda(w.random_vectors(33, (2, n, 3)))
+    ref = dda.apply(tgt, opts, kh, e0, xv)
+    buf = torch.zeros((3, n, 3), dtype=torch.complex128, device="cuda")
+    buf[:2] = xv
+    o, inc = opts.c(), api._incidences(kh, e0)
+    st = _abi.load().dda_apply(tgt.ctx, tgt.handle, ctypes.byref(o), 2, inc, buf[0].data_ptr(), buf[1].data_ptr())
+    assert st == 0
+    torch.cuda.synchronize()
+    assert torch.equal(buf[1:], ref)
