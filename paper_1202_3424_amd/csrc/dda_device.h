@@ -336,8 +336,20 @@ static_assert(ct_plan_ok(32) && ct_plan_ok(48) && ct_plan_ok(64) && ct_plan_ok(8
 // transform of zero-padded data; R even), so inputs r >= R/2 are not read.
 // HALF_OUT: only the lower half of every line is wanted (the last pass of an
 // inverse transform; R even), so outputs q >= R/2 are not written.
-template <typename T, int R, int DIR, int L, int NL, int NS, int NTHR, bool HALF_IN = false, bool HALF_OUT = false>
-__device__ __forceinline__ void fft_pass_ct(typename V2<T>::t* lds, const double2* tw) {
+// LD / ST: the inputs come from ld(line, e) instead of the tile (which the
+// caller knows to be free) / the outputs go to st(line, e, value).
+constexpr int FFT_TW_VGPRS = 48;
+struct NoIO { static constexpr bool on = false; };
+template <typename F> struct LineIO : F {
+    static constexpr bool on = true;
+    __device__ __forceinline__ LineIO(const F& f) : F(f) {}
+};
+template <typename F> __device__ __forceinline__ LineIO<F> line_io(const F& f) { return LineIO<F>(f); }
+
+template <typename T, int R, int DIR, int L, int NL, int NS, int NTHR, bool HALF_IN = false, bool HALF_OUT = false,
+          typename LD = NoIO, typename ST = NoIO>
+__device__ __forceinline__ void fft_pass_ct(typename V2<T>::t* lds, const double2* tw, const LD& ld = LD(),
+                                            const ST& st = ST()) {
     static_assert(!(HALF_IN || HALF_OUT) || R % 2 == 0, "half-line pruning needs an even radix");
     constexpr int RIN = HALF_IN ? R / 2 : R;
     constexpr int ROUT = HALF_OUT ? R / 2 : R;
@@ -349,67 +361,103 @@ __device__ __forceinline__ void fft_pass_ct(typename V2<T>::t* lds, const double
     constexpr int TSTEP = L / (NS * R);
     C v[MAXB][R];
     C w[MAXB][R];
+    auto inputs = [&](int i, int b) {
+        const int line = b % NL;
+        const int j = b / NL;
+        const C* src = lds + line * LP + j;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r < RIN) {
+                if constexpr (LD::on) v[i][r] = ld(line, j + r * LR);
+                else v[i][r] = src[r * LR];
+            } else {
+                v[i][r].x = 0;
+                v[i][r].y = 0;
+            }
+        }
+    };
+    auto twiddles = [&](int i, int b) {
+        if (NS > 1) {
+            const int k = b / NL % NS;
+#pragma unroll
+            for (int r = 1; r < R; ++r) {
+                const double2 t = tw[r * k * TSTEP];
+                w[i][r].x = (decltype(w[i][r].x))t.x;
+                w[i][r].y = (decltype(w[i][r].y))(DIR > 0 ? -t.y : t.y);
+            }
+        }
+    };
+    auto butterfly = [&](int i, int b) {
+        const int line = b % NL;
+        const int j = b / NL;
+        const int k = j % NS;
+        if (NS > 1) {
+#pragma unroll
+            for (int r = 1; r < R; ++r) v[i][r] = cmul(v[i][r], w[i][r]);
+        }
+        Dft<R, DIR, C>::run(v[i]);
+        C* dst = lds + line * LP + (j - k) * R + k;
+#pragma unroll
+        for (int q = 0; q < ROUT; ++q) {
+            if constexpr (ST::on) st(line, (j - k) * R + k + q * NS, v[i][q]);
+            else dst[q * NS] = v[i][q];
+        }
+    };
+    // twiddles are loaded before the barrier, unless the registers they would
+    // hold through it cost occupancy; a last pass that stores to the grid then
+    // takes one butterfly at a time
+    constexpr bool LATE = MAXB * R * (int)(sizeof(C) / 4) > FFT_TW_VGPRS;
+    if constexpr (ST::on && LATE) {
+#pragma unroll
+        for (int i = 0; i < MAXB; ++i) {
+            const int b = threadIdx.x + i * NTHR;
+            if ((B % NTHR) == 0 || b < B) {
+                inputs(i, b);
+                twiddles(i, b);
+                butterfly(i, b);
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < MAXB; ++i) {
         const int b = threadIdx.x + i * NTHR;
         if ((B % NTHR) == 0 || b < B) {
-            const int line = b % NL;
-            const int j = b / NL;
-            const C* src = lds + line * LP + j;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                if (r < RIN) {
-                    v[i][r] = src[r * LR];
-                } else {
-                    v[i][r].x = 0;
-                    v[i][r].y = 0;
-                }
-            }
-            if (NS > 1) {
-                const int k = j % NS;
-#pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    const double2 t = tw[r * k * TSTEP];
-                    w[i][r].x = (decltype(w[i][r].x))t.x;
-                    w[i][r].y = (decltype(w[i][r].y))(DIR > 0 ? -t.y : t.y);
-                }
-            }
+            inputs(i, b);
+            if (!LATE) twiddles(i, b);
         }
     }
-    __syncthreads();
+    if constexpr (!LD::on && !ST::on) __syncthreads();
 #pragma unroll
     for (int i = 0; i < MAXB; ++i) {
         const int b = threadIdx.x + i * NTHR;
         if ((B % NTHR) == 0 || b < B) {
-            const int line = b % NL;
-            const int j = b / NL;
-            const int k = j % NS;
-            if (NS > 1) {
-#pragma unroll
-                for (int r = 1; r < R; ++r) v[i][r] = cmul(v[i][r], w[i][r]);
-            }
-            Dft<R, DIR, C>::run(v[i]);
-            C* dst = lds + line * LP + (j - k) * R + k;
-#pragma unroll
-            for (int q = 0; q < ROUT; ++q) dst[q * NS] = v[i][q];
+            if (LATE) twiddles(i, b);
+            butterfly(i, b);
         }
     }
-    __syncthreads();
+    if constexpr (!ST::on) __syncthreads();
 }
 
 // Every pass of a compile-time length.  HALF_IN / HALF_OUT (see fft_pass_ct)
 // apply to the first / last pass; the caller sets them only when the data
-// allow it (inputs e >= L/2 zero, outputs e >= L/2 unused).
+// allow it (inputs e >= L/2 zero, outputs e >= L/2 unused).  LD feeds the
+// first pass and ST takes the results of the last, each saving a round trip
+// through the tile and a barrier.
 template <typename T, int DIR, int L, int NL, int NTHR, bool HALF_IN = false, bool HALF_OUT = false, int S = 0,
-          int NS = 1>
-__device__ __forceinline__ void fft_lines_ct(typename V2<T>::t* lds, const double2* tw) {
+          int NS = 1, typename LD = NoIO, typename ST = NoIO>
+__device__ __forceinline__ void fft_lines_ct(typename V2<T>::t* lds, const double2* tw, const LD& ld = LD(),
+                                             const ST& st = ST()) {
     constexpr int NST = ct_plan(L, -1);
+    static_assert(NST >= 2, "the first and the last pass differ");
     if constexpr (S < NST) {
         constexpr int R = ct_plan(L, S);
         constexpr bool HI = HALF_IN && S == 0 && R % 2 == 0;
         constexpr bool HO = HALF_OUT && S == NST - 1 && R % 2 == 0;
-        fft_pass_ct<T, R, DIR, L, NL, NS, NTHR, HI, HO>(lds, tw);
-        fft_lines_ct<T, DIR, L, NL, NTHR, HALF_IN, HALF_OUT, S + 1, NS * R>(lds, tw);
+        if constexpr (S == 0) fft_pass_ct<T, R, DIR, L, NL, NS, NTHR, HI, HO>(lds, tw, ld, NoIO());
+        else if constexpr (S == NST - 1) fft_pass_ct<T, R, DIR, L, NL, NS, NTHR, HI, HO>(lds, tw, NoIO(), st);
+        else fft_pass_ct<T, R, DIR, L, NL, NS, NTHR, HI, HO>(lds, tw);
+        fft_lines_ct<T, DIR, L, NL, NTHR, HALF_IN, HALF_OUT, S + 1, NS * R>(lds, tw, ld, st);
     }
 }
 

@@ -196,24 +196,31 @@ __global__ __launch_bounds__(NT) void k_strided(Geo g, typename V2<T>::t* grid, 
     for (int q = q0; q < q1; ++q) {
         if (skip_rhs(st + q, chk)) continue;
         C* gq = grid + (long long)q * g.npts * NC + obase + (long long)x0 * NC;
-        const int tin = nlines * (hin ? L / 2 : L);
-        for (int idx = threadIdx.x; idx < tin; idx += NT) {
-            const int inner = idx % nlines;
-            const int e = idx / nlines;
+        // compile-time lengths: the first pass reads the grid and the last
+        // one writes it, without a round trip through the tile
+        auto load = line_io([&](int line, int e) {
             C v;
-            if (e < lin && inner < nval) {
-                v = gq[e * estride + inner];
-            } else {
-                v.x = 0;
-                v.y = 0;
+            v.x = 0;
+            v.y = 0;
+            if (e < lin && line < nval) v = gq[e * estride + line];
+            return v;
+        });
+        auto store = line_io([&](int line, int e, const C& v) {
+            if (e < lout && line < nval) gq[e * estride + line] = v;
+        });
+        if constexpr (!CT) {
+            const int tin = nlines * L;
+            for (int idx = threadIdx.x; idx < tin; idx += NT) {
+                const int inner = idx % nlines;
+                const int e = idx / nlines;
+                lds[inner * Lp + e] = load(inner, e);
             }
-            lds[inner * Lp + e] = v;
+            __syncthreads();
         }
-        __syncthreads();
         if constexpr (GH) {
             if constexpr (CT) {
-                if (hin) fft_lines_ct<T, -1, LC, NC * TXC, NT, true, false>(lds, tw64 + pl.tw);
-                else fft_lines_ct<T, -1, LC, NC * TXC, NT>(lds, tw64 + pl.tw);
+                if (hin) fft_lines_ct<T, -1, LC, NC * TXC, NT, true, false>(lds, tw64 + pl.tw, load);
+                else fft_lines_ct<T, -1, LC, NC * TXC, NT>(lds, tw64 + pl.tw, load);
             } else {
                 fft_lines<T, -1>(lds, tws, nlines, Lp, pl);
             }
@@ -293,25 +300,27 @@ __global__ __launch_bounds__(NT) void k_strided(Geo g, typename V2<T>::t* grid, 
             }
             __syncthreads();
             if constexpr (CT) {
-                if (hout) fft_lines_ct<T, 1, LC, NC * TXC, NT, false, true>(lds, tw64 + pl.tw);
-                else fft_lines_ct<T, 1, LC, NC * TXC, NT>(lds, tw64 + pl.tw);
+                if (hout) fft_lines_ct<T, 1, LC, NC * TXC, NT, false, true>(lds, tw64 + pl.tw, NoIO(), store);
+                else fft_lines_ct<T, 1, LC, NC * TXC, NT>(lds, tw64 + pl.tw, NoIO(), store);
             } else {
                 fft_lines<T, 1>(lds, tws, nlines, Lp, pl);
             }
         } else {
             if constexpr (CT) {
-                if (hin) fft_lines_ct<T, DIR, LC, NC * TXC, NT, true, false>(lds, tw64 + pl.tw);
-                else if (hout) fft_lines_ct<T, DIR, LC, NC * TXC, NT, false, true>(lds, tw64 + pl.tw);
-                else fft_lines_ct<T, DIR, LC, NC * TXC, NT>(lds, tw64 + pl.tw);
+                if (hin) fft_lines_ct<T, DIR, LC, NC * TXC, NT, true, false>(lds, tw64 + pl.tw, load, store);
+                else if (hout) fft_lines_ct<T, DIR, LC, NC * TXC, NT, false, true>(lds, tw64 + pl.tw, load, store);
+                else fft_lines_ct<T, DIR, LC, NC * TXC, NT>(lds, tw64 + pl.tw, load, store);
             } else {
                 fft_lines<T, DIR>(lds, tws, nlines, Lp, pl);
             }
         }
-        const int tout = nlines * lout;
-        for (int idx = threadIdx.x; idx < tout; idx += NT) {
-            const int inner = idx % nlines;
-            const int e = idx / nlines;
-            if (inner < nval) gq[e * estride + inner] = lds[inner * Lp + e];
+        if constexpr (!CT) {
+            const int tout = nlines * lout;
+            for (int idx = threadIdx.x; idx < tout; idx += NT) {
+                const int inner = idx % nlines;
+                const int e = idx / nlines;
+                store(inner, e, lds[inner * Lp + e]);
+            }
         }
         if (RHS_LOOP) __syncthreads();   // the next right-hand side refills the tile
     }
@@ -378,23 +387,20 @@ __global__ __launch_bounds__(NT) void k_zfold(Geo g, typename V2<T>::t* grid, co
         for (int q = 0; q < nrhs; ++q) {
             if (skip_rhs(st + q, chk)) continue;
             C* gq = grid + (long long)q * g.npts * 3 + (long long)ky * Mx * 3;
-            const int tin = NL * (hin ? L / 2 : L);
-            for (int idx = threadIdx.x; idx < tin; idx += NT) {
-                const int inner = idx % NL;
-                const int e = idx / NL;
-                const int xo = inner / 3, c = inner % 3;
+            auto load = line_io([&](int line, int e) {
+                const int xo = line / 3, c = line % 3;
                 C v;
-                if (e < lin && col_ok(xo)) {
-                    v = gq[e * plane + (long long)kx_of(xo) * 3 + c];
-                } else {
-                    v.x = 0;
-                    v.y = 0;
-                }
-                lds[inner * LP + e] = v;
-            }
-            __syncthreads();
-            if (hin) fft_lines_ct<T, -1, LC, NL, NT, true, false>(lds, tw);
-            else fft_lines_ct<T, -1, LC, NL, NT>(lds, tw);
+                v.x = 0;
+                v.y = 0;
+                if (e < lin && col_ok(xo)) v = gq[e * plane + (long long)kx_of(xo) * 3 + c];
+                return v;
+            });
+            auto store = line_io([&](int line, int e, const C& v) {
+                const int xo = line / 3, c = line % 3;
+                if (e < lout && col_ok(xo)) gq[e * plane + (long long)kx_of(xo) * 3 + c] = v;
+            });
+            if (hin) fft_lines_ct<T, -1, LC, NL, NT, true, false>(lds, tw, load);
+            else fft_lines_ct<T, -1, LC, NL, NT>(lds, tw, load);
 #pragma unroll
             for (int i = 0; i < MAXP; ++i) {
                 const int p = threadIdx.x + i * NT;
@@ -417,15 +423,8 @@ __global__ __launch_bounds__(NT) void k_zfold(Geo g, typename V2<T>::t* grid, co
                 }
             }
             __syncthreads();
-            if (hout) fft_lines_ct<T, 1, LC, NL, NT, false, true>(lds, tw);
-            else fft_lines_ct<T, 1, LC, NL, NT>(lds, tw);
-            const int tout = NL * lout;
-            for (int idx = threadIdx.x; idx < tout; idx += NT) {
-                const int inner = idx % NL;
-                const int e = idx / NL;
-                const int xo = inner / 3, c = inner % 3;
-                if (col_ok(xo)) gq[e * plane + (long long)kx_of(xo) * 3 + c] = lds[inner * LP + e];
-            }
+            if (hout) fft_lines_ct<T, 1, LC, NL, NT, false, true>(lds, tw, NoIO(), store);
+            else fft_lines_ct<T, 1, LC, NL, NT>(lds, tw, NoIO(), store);
             __syncthreads();
         }
     }

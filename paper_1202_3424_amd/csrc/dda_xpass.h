@@ -247,21 +247,14 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
         }
     }
     __syncthreads();
-    if constexpr (CT) {
-        if (hin) fft_lines_ct<T, -1, LC, 3, NTHR, true, false>(lds, tw64 + g.ax[0].tw);
-        else fft_lines_ct<T, -1, LC, 3, NTHR>(lds, tw64 + g.ax[0].tw);
-    } else {
-        fft_lines<T, -1, NTHR>(lds, tws, nlines, Lp, g.ax[0]);
-    }
     C* gq = grid + ((long long)q * g.npts + ((long long)z * My + y0) * Mx) * 3;
     if constexpr (CT) {
-        constexpr int NPT = (3 * LC + NTHR - 1) / NTHR;
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            if ((3 * LC) % NTHR == 0 || idx < 3 * LC) gq[idx] = lds[(idx % 3) * Lp + idx / 3];
-        }
+        // the last pass writes the grid itself
+        auto store = line_io([&](int line, int e, const C& v) { gq[e * 3 + line] = v; });
+        if (hin) fft_lines_ct<T, -1, LC, 3, NTHR, true, false>(lds, tw64 + g.ax[0].tw, NoIO(), store);
+        else fft_lines_ct<T, -1, LC, 3, NTHR>(lds, tw64 + g.ax[0].tw, NoIO(), store);
     } else {
+        fft_lines<T, -1, NTHR>(lds, tws, nlines, Lp, g.ax[0]);
         const int tot = nl * Mx * 3;
         for (int idx = threadIdx.x; idx < tot; idx += NTHR) {
             const int c = idx % 3;
@@ -340,16 +333,8 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
         }
     }
     const C* gq = grid + ((long long)q * g.npts + ((long long)z * My + y0) * Mx) * 3;
-    if constexpr (CT) {
-        // the line's 3 LC values: every load in flight before the LDS stores
-        // (unrolled: the loads need not wait for one another)
-        constexpr int NPT = (3 * LC + NTHR - 1) / NTHR;
-#pragma unroll
-        for (int k = 0; k < NPT; ++k) {
-            const int idx = threadIdx.x + k * NTHR;
-            if ((3 * LC) % NTHR == 0 || idx < 3 * LC) lds[(idx % 3) * Lp + idx / 3] = gq[idx];
-        }
-    } else {
+    // (compile-time lengths: the first pass reads the grid itself)
+    if constexpr (!CT) {
         const int tot = nl * Mx * 3;
         for (int idx = threadIdx.x; idx < tot; idx += NTHR) {
             const int c = idx % 3;
@@ -395,12 +380,15 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
             pa[k] = HAS_AUX ? auxiliary(i) : double2{0.0, 0.0};
         }
     }
-    __syncthreads();
     if constexpr (CT) {
+        auto load = line_io([&](int line, int e) { return gq[e * 3 + line]; });
         // only e < nx is gathered: with 2 nx <= Mx the last pass skips the upper half
-        if (ct_half_out_ok(LC) && 2 * nx <= Mx) fft_lines_ct<T, 1, LC, 3, NTHR, false, true>(lds, tw64 + g.ax[0].tw);
-        else fft_lines_ct<T, 1, LC, 3, NTHR>(lds, tw64 + g.ax[0].tw);
+        if (ct_half_out_ok(LC) && 2 * nx <= Mx)
+            fft_lines_ct<T, 1, LC, 3, NTHR, false, true>(lds, tw64 + g.ax[0].tw, load);
+        else
+            fft_lines_ct<T, 1, LC, 3, NTHR>(lds, tw64 + g.ax[0].tw, load);
     } else {
+        __syncthreads();
         fft_lines<T, 1, NTHR>(lds, tws, nlines, Lp, g.ax[0]);
     }
 
