@@ -90,35 +90,43 @@ __device__ __forceinline__ void wave_fence() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One-dimensional launch: workgroup b runs on XCD b % 8 (round-robin), which
-// takes one run of kx and its mirror run (they share tensor rows), every
-// right-hand side in turn; neighbouring kx share cache lines of the grid,
-// which then meet in that XCD's L2.  Grids whose x extent does not split
-// that way give each XCD one contiguous run.
-__device__ __forceinline__ bool plane_tile(int Mx, int& kx, int& q) {
+// One-dimensional launch: workgroup b runs on XCD b % 8 (round-robin).
+// Neighbouring kx share cache lines of the grid, which should meet in one
+// XCD's L2.  Where a sixteenth of the row, W = Mx / 16 points, is a run of at
+// least 192 bytes, an XCD takes one such run of kx and its mirror run (they
+// share tensor rows), every right-hand side in turn; with shorter runs (and
+// extents that do not split so) it takes a contiguous part of the
+// (right-hand side, kx) order.  Measured, us the first way and the second:
+// FP64 Mx 32 39.5 and 34.0, 48 42.6 and 40.2, 64 94.6 and 95.7, 96 305 and
+// 312, 128 32.0 and 35.8 (two right-hand sides); FP32 Mx 96 178 and 168.
+template <typename T> __host__ __device__ constexpr bool plane_runs(int Mx) {
+    return Mx % (2 * passes::N_XCD) == 0 && Mx / (2 * passes::N_XCD) * 3 * 2 * (int)sizeof(T) >= 192;
+}
+template <typename T> __device__ __forceinline__ bool plane_tile(int Mx, int nrhs, int& kx, int& q) {
     const int j = blockIdx.x % passes::N_XCD, local = blockIdx.x / passes::N_XCD;
-    if (Mx % (2 * passes::N_XCD) == 0) {
+    if (plane_runs<T>(Mx)) {
         const int W = Mx / (2 * passes::N_XCD);
         const int i = local % (2 * W);
         q = local / (2 * W);
         kx = i < W ? j * W + i : Mx - (j + 1) * W + (i - W);
         return true;
     }
-    const int nt = (Mx + passes::N_XCD - 1) / passes::N_XCD;
-    q = local / nt;
-    kx = j * nt + local % nt;
-    return kx < Mx;
+    const int t = j * (gridDim.x / passes::N_XCD) + local;
+    q = t / Mx;
+    kx = t % Mx;
+    return q < nrhs;
 }
 inline unsigned plane_grid(int Mx, int nrhs) {
-    return (unsigned)(passes::N_XCD * ((Mx + passes::N_XCD - 1) / passes::N_XCD)) * (unsigned)nrhs;
+    const long long n = (long long)Mx * nrhs;
+    return (unsigned)((n + passes::N_XCD - 1) / passes::N_XCD * passes::N_XCD);
 }
 
 // gp: the tensor octant as [Hx][Hz][6][plane_row(LY)] (lanes over ky read
 // consecutive values, rows on cache-line boundaries).
 template <typename T, int LY, int LZ, int NTHR, int WV>
 __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(WV))) void k_plane(Geo g, typename V2<T>::t* grid, const double2* tw64,
-                                               const typename V2<T>::t* gp, const RhsState* st, int chk, int ZS,
-                                               int CS) {
+                                               const typename V2<T>::t* gp, const RhsState* st, int chk, int nrhs,
+                                               int ZS, int CS) {
     using C = typename V2<T>::t;
     constexpr int PY = ct_split(LY), QY = LY / PY;
     constexpr int PZ = ct_split(LZ), QZ = LZ / PZ;
@@ -131,7 +139,7 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(WV))) void
     C* lds = (C*)smem;
     const int Mx = g.M[0];
     int kx, q;
-    if (!plane_tile(Mx, kx, q)) return;
+    if (!plane_tile<T>(Mx, nrhs, kx, q)) return;
     if (passes::skip_rhs(st + q, chk)) return;
     int ny = g.n[1], nz = g.n[2];
     if (g.rg) {   // ragged batch: this right-hand side's target
@@ -455,7 +463,7 @@ bool plane_launch(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, cons
         constexpr int NTHR = 64 * plane_waves<T>(LY, LZ);
         const int ZS = z_stride(LZ, g.n[2]), CS = c_stride(LY, ZS, sizeof(T) == 4);
         DDA_LAUNCH((k_plane<T, LY, LZ, NTHR, plane_occ<T>(LY, LZ)>), dim3(plane_grid(g.M[0], nrhs)), dim3(NTHR),
-                   plane_bytes(LY, LZ, g.n[2], sizeof(T) == 4), s, g, grid, tw, gp, st, chk, ZS, CS);
+                   plane_bytes(LY, LZ, g.n[2], sizeof(T) == 4), s, g, grid, tw, gp, st, chk, nrhs, ZS, CS);
         return true;
     }
     return false;

@@ -1519,6 +1519,26 @@ def test_short_plane_kernel_equals_the_three_passes(dda, precision, short):
             assert torch.equal(y, ref), (ny, nz)
 
 
+@pytest.mark.parametrize("nx", [1, 2, 3, 5, 8, 13, 16, 24, 25, 32, 33, 48, 50, 64, 65])
+def test_plane_kernel_order_of_workgroups(dda, nx):
+    """Every plane of every right-hand side is done once, whatever order the
+    x extent (a whole number of mirrored runs per XCD, a contiguous part, or
+    neither) and the count of right-hand sides give: bitwise the three passes."""
+    rng = np.random.default_rng(nx)
+    keep = rng.random((nx, 12, 16)) < 0.1
+    keep[0, 0, 0] = keep[-1, -1, -1] = True
+    ijk = np.argwhere(keep).astype(np.int32)
+    tgt = dda.Target(ijk, 1.4 + 0.1j)
+    for q in (1, 3):
+        kh, e0 = np.tile([1.0, 0, 0], (q, 1)), np.tile(np.array([0, 1, 0], complex), (q, 1))
+        xv = _cuda(w.random_vectors(34, (q, len(ijk), 3)))
+        for precision in ("fp64", "fp32_matvec"):
+            y = dda.apply(tgt, dda.Options.for_size_parameter(1.0, precision=precision), kh, e0, xv)
+            ref = dda.apply(tgt, dda.Options.for_size_parameter(1.0, precision=precision, kernel_variant=4), kh, e0,
+                            xv)
+            assert torch.equal(y, ref), (q, precision)
+
+
 def test_apply_with_overlapping_vectors(dda):
     """x and y of a product that overlap in part (one buffer, y a right-hand
     side further on): the same result as with separate buffers, the caller's
