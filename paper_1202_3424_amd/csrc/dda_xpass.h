@@ -23,7 +23,9 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
     extern __shared__ __align__(16) unsigned char smem[];
     const int q = blockIdx.z;
     const RhsState* st = a.st + q;
-    if (skip_rhs(st, chk)) return;
+    if constexpr (!CT) {
+        if (skip_rhs(st, chk)) return;
+    }
     int nx = g.n[0], ny = g.n[1];
     const int* map = a.map;
     const int Mx = CT ? LC : g.M[0];
@@ -195,6 +197,9 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
             const int e = idx / 3;
             sk[k] = (idx < tin && e < nx) ? mrow[e] : -1;
         }
+        // (the status and the map are loaded together: a small launch is a
+        // chain of load latencies)
+        if (skip_rhs(st, chk)) return;
         Ops ok[NPT];
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
@@ -286,7 +291,9 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
     extern __shared__ __align__(16) unsigned char smem[];
     const int q = blockIdx.z;
     const RhsState* st = a.st + q;
-    if (skip_rhs(st, chk)) return;
+    if constexpr (!CT) {
+        if (skip_rhs(st, chk)) return;
+    }
     int nx = g.n[0], ny = g.n[1];
     const int* map = a.map;
     const int* mat = a.mat;
@@ -331,6 +338,7 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
             const int idx = threadIdx.x + k * NTHR;
             ps[k] = idx < tout ? mrow[idx / 3] : -1;
         }
+        if (skip_rhs(st, chk)) return;   // (as in k_scatter_x)
     }
     const C* gq = grid + ((long long)q * g.npts + ((long long)z * My + y0) * Mx) * 3;
     // (compile-time lengths: the first pass reads the grid itself)
