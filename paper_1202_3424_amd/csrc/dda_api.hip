@@ -694,10 +694,6 @@ struct Work {
     void matvec_t(int sc, int ga, int chk_sc, int chk_rest, const int* vars) {
         using C = typename V2<T>::t;
         const Geo& g = t->geo;
-        // small launches are chains of load latencies: there passes 2-4 do
-        // not wait for a status first (their grid is scratch, so running them
-        // on a stopped right-hand side changes nothing)
-        const int chk_pass = nrhs * g.npts <= (1LL << 21) ? CHK_NONE : chk_rest;
         C* gr = (C*)grid;
         const double2* tw = (const double2*)t->tw.p;
         {
@@ -708,19 +704,19 @@ struct Work {
             Timed tm(c, T_FFTZ_G, s);
             const dda_target* src = segs.empty() ? t : segs[0].t;
             const void* gp = plane_short<T>(g) ? ghat(sizeof(T) == 4) : sizeof(T) == 4 ? src->gp32.p : src->gp64.p;
-            launch_plane<T>(chk_pass, g, nrhs, gr, tw, (const C*)gp, a.st, s);
+            launch_plane<T>(chk_rest, g, nrhs, gr, tw, (const C*)gp, a.st, s);
         } else {
             {
                 Timed tm(c, T_FFTY_FWD, s);
-                strided_slot<T>(0, chk_pass, vars[0]);
+                strided_slot<T>(0, chk_rest, vars[0]);
             }
             {
                 Timed tm(c, T_FFTZ_G, s);
-                strided_slot<T>(1, chk_pass, vars[1]);
+                strided_slot<T>(1, chk_rest, vars[1]);
             }
             {
                 Timed tm(c, T_FFTY_INV, s);
-                strided_slot<T>(2, chk_pass, vars[2]);
+                strided_slot<T>(2, chk_rest, vars[2]);
             }
         }
         {
