@@ -56,12 +56,17 @@ struct RhsGeo {
 //   H[a]  M[a]/2 + 1: extent of the stored octant of the tensor FFT
 // Grids hold NC complex components interleaved per point, point index
 // (z * My + y) * Mx + x, right-hand side outermost.
+//   i0, i1  the part of the box that holds inputs, [i0, i1) on each axis (all
+//           of it, [0, n), but for a near-field volume, whose only sources are
+//           the target's sites)
 //   tw32  the twiddle tables W_L^t rounded to FP32 (the FP64 tables' offsets)
 //   rg    per right-hand side geometry of a ragged batch, or null (one target)
 struct Geo {
     int n[3];
     int M[3];
     int H[3];
+    int i0[3];
+    int i1[3];
     long long npts;
     AxisPlan ax[3];
     const float2* tw32;
@@ -117,7 +122,8 @@ __device__ __forceinline__ int rhs_site_blocks(const SiteArgs& a, int q) {
 // of a BiCGstab(2) iteration (vectors: r_0 = r, r_1 = t, r_2 = r2, u_0 = p,
 // u_1 = v, u_2 = u2, shadow residual rhat; GA_V serves the first product).
 enum ScatterMode { SC_PLAIN = 0, SC_CONJ = 1, SC_P = 2, SC_S = 3, SC_Q = 4, SC_B0 = 5, SC_B1 = 6, SC_B2 = 7, SC_B3 = 8 };
-enum GatherMode { GA_PLAIN = 0, GA_CONJ = 1, GA_V = 2, GA_T = 3, GA_RES = 4, GA_Q = 5, GA_B1 = 6, GA_B2 = 7, GA_B3 = 8 };
+enum GatherMode { GA_PLAIN = 0, GA_CONJ = 1, GA_V = 2, GA_T = 3, GA_RES = 4, GA_Q = 5, GA_B1 = 6, GA_B2 = 7, GA_B3 = 8,
+                  GA_FIELD = 9 };
 // which right-hand sides a pass skips
 enum Check { CHK_NONE = 0, CHK_ACTIVE = 1 };
 // what k_finalize makes of the partial sums of the kernel before it
@@ -260,10 +266,8 @@ void launch_far_lines(const int* map, const int* perm, const double2* P, long lo
 // P (caller order) into the box-scan site vector x at the target's sites;
 // E_sca = -v and E_inc at every point (either output may be null); the
 // trilinear line a..b of n points through E [nrhs][box][3]
-void launch_nf_place(int nsites, const int* perm, const int* coords, const double2* P, int nrhs, const int org[3],
-                     const int dims[3], double2* x, hipStream_t s);
-void launch_nf_out(int nrhs, const int org[3], const int dims[3], const double* khat, const double2* e0, double kd,
-                   const double2* v, double2* einc, double2* esca, hipStream_t s);
+void launch_nf_inc(int nrhs, const int org[3], const int dims[3], const double* khat, const double2* e0, double kd,
+                   double2* einc, hipStream_t s);
 void launch_field_line(int nrhs, const int org[3], const int dims[3], const double2* E, const double a[3],
                        const double b[3], int n, double2* out, hipStream_t s);
 // nblk: the producer's workgroups per right-hand side; in a ragged batch
@@ -279,7 +283,6 @@ void launch_finalize(const SiteArgs& a, int kind, int nblk, hipStream_t s);
 // width complex values per site; to_sorted: dst[sorted] = src[caller], else dst[caller] = src[sorted]
 void launch_permute(int nrhs, int nsites, int width, const int* perm, const double2* src, double2* dst,
                     bool to_sorted, hipStream_t s);
-void launch_fill(double2* p, long long n, hipStream_t s);
 void launch_set_state(RhsState* st, int nrhs, double tol, int max_iter, hipStream_t s);
 void launch_grad(const SiteArgs& a, const double2* dainv, double w_qabs, double2* grad, hipStream_t s);
 void launch_adjoint_rhs(const SiteArgs& a, const double2* P_sorted, double w_qabs, double w_qext, hipStream_t s);

@@ -336,49 +336,23 @@ __global__ __launch_bounds__(NT) void k_b2_update(SiteArgs a) {
 
 // ------------------------------------------------------------------ near field
 // ("Near-Field Calculations".)  The extended volume is a lattice box of
-// dims[0] x dims[1] x dims[2] points starting at lattice point org, every
-// point a site of the product's target; its site vectors are in box-scan
-// order.  k_nf_place copies the solution P (caller order) into that vector
-// at the target's sites (every other point is zeroed beforehand).
-__global__ __launch_bounds__(NT) void k_nf_place(int nsites, const int* perm, const int* coords, const double2* P,
-                                                 int ox, int oy, int oz, int nx, int ny, long long n3x,
-                                                 double2* x) {
-    const int q = blockIdx.y;
-    const long long n3 = 3LL * nsites;
-    for (int s = blockIdx.x * NT + threadIdx.x; s < nsites; s += gridDim.x * NT) {
-        const long long i = ((long long)(coords[s * 3 + 2] - oz) * ny + (coords[s * 3 + 1] - oy)) * nx +
-                            (coords[s * 3 + 0] - ox);
-        const double2* src = P + (long long)q * n3 + (long long)perm[s] * 3;
-        double2* dst = x + (long long)q * n3x + i * 3;
-        for (int c = 0; c < 3; ++c) dst[c] = src[c];
-    }
-}
-
-// E_sca = -(off-diagonal product) at every point of the extended volume (v
-// holds that product: the diagonal was zero), and E_inc = e exp(i kd khat . r)
-// with r the point's lattice coordinates.  Either output may be null.
-__global__ __launch_bounds__(NT) void k_nf_out(long long npts, int ox, int oy, int oz, int nx, int ny,
-                                               const double* khat, const double2* e0, double kd, const double2* v,
-                                               double2* einc, double2* esca) {
-    const int q = blockIdx.y;
+// dims[0] x dims[1] x dims[2] points starting at lattice point org.  The
+// product's scatter reads the solution at the target's sites and its gather
+// writes E_sca; E_inc = e exp(i kd khat . r), r the point's lattice
+// coordinates, is this kernel's: one workgroup per x line, a thread per
+// value, so that stores are whole lines (bounded by them).
+__global__ __launch_bounds__(NT) void k_nf_inc(int ox, int oy, int oz, int nx, const double* khat, const double2* e0,
+                                               double kd, double2* einc) {
+    const int y = blockIdx.x, z = blockIdx.y, q = blockIdx.z;
     const double* kh = khat + q * 3;
     const double2* e = e0 + q * 3;
-    const long long base = (long long)q * npts * 3;
-    for (long long i = blockIdx.x * (long long)NT + threadIdx.x; i < npts; i += (long long)gridDim.x * NT) {
-        if (esca)
-            for (int c = 0; c < 3; ++c) {
-                const double2 y = v[base + i * 3 + c];
-                esca[base + i * 3 + c] = double2{-y.x, -y.y};
-            }
-        if (einc) {
-            const long long xy = (long long)nx * ny;
-            const int z = (int)(i / xy), y = (int)((i / nx) % ny), x = (int)(i % nx);
-            const double ph = kd * (kh[0] * (x + ox) + kh[1] * (y + oy) + kh[2] * (z + oz));
-            double sn, cs;
-            sincos(ph, &sn, &cs);
-            const double2 w = {cs, sn};
-            for (int c = 0; c < 3; ++c) einc[base + i * 3 + c] = cmul(e[c], w);
-        }
+    double2* row = einc + (((long long)q * gridDim.y + z) * gridDim.x + y) * nx * 3;
+    for (int idx = threadIdx.x; idx < 3 * nx; idx += NT) {
+        const int x = idx / 3;
+        const double ph = kd * (kh[0] * (x + ox) + kh[1] * (y + oy) + kh[2] * (z + oz));
+        double sn, cs;
+        sincos(ph, &sn, &cs);
+        row[idx] = cmul(e[idx - 3 * x], double2{cs, sn});
     }
 }
 
@@ -846,11 +820,6 @@ __global__ __launch_bounds__(NT) void k_permute(int nrhs, int nsites, int width,
     }
 }
 
-__global__ __launch_bounds__(NT) void k_fill(double2* p, long long n) {
-    for (long long i = blockIdx.x * (long long)NT + threadIdx.x; i < n; i += (long long)gridDim.x * NT)
-        p[i] = double2{0.0, 0.0};
-}
-
 __global__ void k_set_state(RhsState* st, int nrhs, double tol2, int max_iter) {
     const int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= nrhs) return;
@@ -951,17 +920,10 @@ void launch_b2_update(const SiteArgs& a, int site_blocks, hipStream_t s) {
 void launch_qmr_final(const SiteArgs& a, int site_blocks, hipStream_t s) {
     hipLaunchKernelGGL(k_qmr_final, dim3(site_blocks, a.nrhs), dim3(NT), 0, s, a);
 }
-void launch_nf_place(int nsites, const int* perm, const int* coords, const double2* P, int nrhs, const int org[3],
-                     const int dims[3], double2* x, hipStream_t s) {
-    const long long n3x = 3LL * dims[0] * dims[1] * dims[2];
-    hipLaunchKernelGGL(k_nf_place, dim3(blocks_for(nsites, 4096), nrhs), dim3(NT), 0, s, nsites, perm, coords, P,
-                       org[0], org[1], org[2], dims[0], dims[1], n3x, x);
-}
-void launch_nf_out(int nrhs, const int org[3], const int dims[3], const double* khat, const double2* e0, double kd,
-                   const double2* v, double2* einc, double2* esca, hipStream_t s) {
-    const long long npts = (long long)dims[0] * dims[1] * dims[2];
-    hipLaunchKernelGGL(k_nf_out, dim3(blocks_for(npts, 4096), nrhs), dim3(NT), 0, s, npts, org[0], org[1], org[2],
-                       dims[0], dims[1], khat, e0, kd, v, einc, esca);
+void launch_nf_inc(int nrhs, const int org[3], const int dims[3], const double* khat, const double2* e0, double kd,
+                   double2* einc, hipStream_t s) {
+    hipLaunchKernelGGL(k_nf_inc, dim3(dims[1], dims[2], nrhs), dim3(NT), 0, s, org[0], org[1], org[2], dims[0], khat,
+                       e0, kd, einc);
 }
 void launch_field_line(int nrhs, const int org[3], const int dims[3], const double2* E, const double a[3],
                        const double b[3], int n, double2* out, hipStream_t s) {
@@ -995,10 +957,6 @@ void launch_permute(int nrhs, int nsites, int width, const int* perm, const doub
     const long long tot = (long long)nrhs * nsites * width;
     hipLaunchKernelGGL(k_permute, dim3(blocks_for(tot, 4096)), dim3(NT), 0, s, nrhs, nsites, width, perm, src, dst,
                        to_sorted ? 1 : 0);
-}
-
-void launch_fill(double2* p, long long n, hipStream_t s) {
-    hipLaunchKernelGGL(k_fill, dim3(blocks_for(n, 4096)), dim3(NT), 0, s, p, n);
 }
 
 void launch_set_state(RhsState* st, int nrhs, double tol, int max_iter, hipStream_t s) {

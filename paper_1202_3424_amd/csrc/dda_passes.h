@@ -10,6 +10,7 @@
 //   2. forward FFT along y of the z < nz planes (inputs y < ny only)
 //   3. along z for every (x, y): forward FFT of the z < nz inputs, product
 //      with the symmetric 3x3 tensor FFT, inverse FFT, keep z < nz
+//      (of a near-field volume 1-3 cover only the input window of x, y, z)
 //   4. inverse FFT along y of the z < nz planes, keep y < ny
 //   5. inverse FFT along x, gather the occupied sites, add 1/alpha x.
 // Passes 1 and 5 also carry the BiCGSTAB vector updates and the partial sums
@@ -129,6 +130,8 @@ __global__ __launch_bounds__(NT) void k_strided(Geo g, typename V2<T>::t* grid, 
     const int TX = CT ? TXC : TXrt;
     const int Lp = pad_len(L);
     int xt = blockIdx.x, o = blockIdx.y, qx = blockIdx.z;
+    if (!GH && DIR < 0) o += g.i0[2];
+    const int e0 = GH || DIR < 0 ? g.i0[axis] : 0;   // first input
     if constexpr (XG) {
         static_assert(!XG || (GH && VAR == 2 && LC > 0), "XCD order: pass 3, one right-hand side per workgroup");
         if (!xcd_tile(Mx, My, TX, nrhs, xt, o, qx)) return;
@@ -202,7 +205,7 @@ __global__ __launch_bounds__(NT) void k_strided(Geo g, typename V2<T>::t* grid, 
             C v;
             v.x = 0;
             v.y = 0;
-            if (e < lin && line < nval) v = gq[e * estride + line];
+            if (e >= e0 && e < lin && line < nval) v = gq[e * estride + line];
             return v;
         });
         auto store = line_io([&](int line, int e, const C& v) {
@@ -392,7 +395,7 @@ __global__ __launch_bounds__(NT) void k_zfold(Geo g, typename V2<T>::t* grid, co
                 C v;
                 v.x = 0;
                 v.y = 0;
-                if (e < lin && col_ok(xo)) v = gq[e * plane + (long long)kx_of(xo) * 3 + c];
+                if (e >= g.i0[2] && e < lin && col_ok(xo)) v = gq[e * plane + (long long)kx_of(xo) * 3 + c];
                 return v;
             });
             auto store = line_io([&](int line, int e, const C& v) {
@@ -492,6 +495,8 @@ __attribute__((amdgpu_waves_per_eu(GH ? WV : rf_waves<T>(L)))) void k_strided_rf
         o = blockIdx.y;
         xt = blockIdx.x;
     }
+    if (!GH && DIR < 0) o += g.i0[2];
+    const int e0 = GH || DIR < 0 ? g.i0[axis] : 0;   // first input
     if (skip_rhs(st + q, chk)) return;
     if (!ragged_lines(g, q, axis, DIR, o, lin, lout, ghat)) return;
     const int in = threadIdx.x % NIN;
@@ -512,7 +517,7 @@ __attribute__((amdgpu_waves_per_eu(GH ? WV : rf_waves<T>(L)))) void k_strided_rf
 #pragma unroll
         for (int m = 0; m < P; ++m) {
             const int e = t + Q * m;
-            if ((!HIN || 2 * m < P) && e < lin && ln < nval) {
+            if ((!HIN || 2 * m < P) && e >= e0 && e < lin && ln < nval) {
                 v[a][m] = gq[(long long)e * estride + ln];
             } else {
                 v[a][m].x = 0;
@@ -688,7 +693,7 @@ void k_zsq(Geo g, typename V2<T>::t* grid, const double2* tw64, const typename V
     for (int m = 0; m < P; ++m) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            if (2 * m < P && col && t + Q * m < lin) {
+            if (2 * m < P && col && t + Q * m >= g.i0[2] && t + Q * m < lin) {
                 v[a][m] = gc[(long long)m * Q * zs + a];
             } else {
                 v[a][m].x = 0;

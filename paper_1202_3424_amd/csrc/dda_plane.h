@@ -148,6 +148,8 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(WV))) void
         nz = r.n[2];
         gp = (const C*)r.gplane[sizeof(C) == sizeof(float2) ? 1 : 0];
     }
+    // the input window (all of the box but for a near-field volume)
+    const int iy0 = g.i0[1], iy1 = g.rg ? ny : g.i1[1], iz0 = g.i0[2], iz1 = g.rg ? nz : g.i1[2];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const auto* twy = tw_table<T>(g, tw64) + g.ax[1].tw;
     const auto* twz = tw_table<T>(g, tw64) + g.ax[2].tw;
@@ -160,13 +162,13 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(WV))) void
     for (int l0 = wave * LPW; l0 < nlines; l0 += NW * LPW) {
         const int ln = l0 + lane % LPW;
         const int z = ln / 3, c3 = ln % 3;
-        const bool live = ln < nlines;
+        const bool live = ln < nlines, fed = z >= iz0 && z < iz1;
         const C* src = gq + (long long)z * LY * ys + c3;
         C v[1][PY];
 #pragma unroll
         for (int m = 0; m < PY; ++m) {
             const int e = yt + QY * m;
-            if (2 * m < PY && live && e < ny) {
+            if (2 * m < PY && fed && e >= iy0 && e < iy1) {
                 v[0][m] = src[(long long)e * ys];
             } else {
                 v[0][m].x = 0;
@@ -399,7 +401,8 @@ __global__ __launch_bounds__(NT) void k_plane_rt(Geo g, AxisPlan py, AxisPlan pz
     zero.y = 0;
     for (int i = threadIdx.x; i < 3 * nz * My; i += NT) {
         const int c = i % 3, y = i / 3 % My, z = i / (3 * My);
-        A[(z * 3 + c) * Ly + y] = y < ny ? gq[((long long)z * My + y) * Mx * 3 + c] : zero;
+        A[(z * 3 + c) * Ly + y] =
+            z >= g.i0[2] && z < g.i1[2] && y >= g.i0[1] && y < g.i1[1] ? gq[((long long)z * My + y) * Mx * 3 + c] : zero;
     }
     __syncthreads();
     for (int l = 0; l < 3 * nz; l += by) fft_lines<T, -1>(A + l * Ly, twy, min(by, 3 * nz - l), Ly, py);

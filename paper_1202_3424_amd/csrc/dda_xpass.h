@@ -26,7 +26,9 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
     if constexpr (!CT) {
         if (skip_rhs(st, chk)) return;
     }
-    int nx = g.n[0], ny = g.n[1];
+    // the box of the sites (and of the map): the volume's input window
+    int nx = g.i1[0] - g.i0[0], ny = g.i1[1] - g.i0[1];
+    const int xw = g.i0[0];
     const int* map = a.map;
     const int Mx = CT ? LC : g.M[0];
     const int My = g.M[1];
@@ -66,11 +68,11 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
     const long long vb = (long long)q * a.n3;
     const int* mrow = map + ((long long)z * ny + y0) * nx;
     double ss[3] = {0.0, 0.0, 0.0};
-    // forward transform of a line that is zero beyond nx: with 2 nx <= Mx the
+    // forward transform of a line that is zero beyond xw + nx: with twice that <= Mx the
     // first radix pass never reads the upper half, which is then not filled
     // (always so at the compile-time lengths, which are even and >= 2 nx - 1)
     bool hin = false;
-    if constexpr (CT) hin = ct_half_in_ok(LC) && 2 * nx <= Mx;
+    if constexpr (CT) hin = ct_half_in_ok(LC) && 2 * (xw + nx) <= Mx;
     const int ext = hin ? Mx / 2 : Mx;
     const int tin = nl * ext * 3;
     // the site-vector values this mode reads at element i (all of them are
@@ -194,8 +196,8 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
 #pragma unroll
         for (int k = 0; k < NPT; ++k) {
             const int idx = threadIdx.x + k * NTHR;
-            const int e = idx / 3;
-            sk[k] = (idx < tin && e < nx) ? mrow[e] : -1;
+            const int e = idx / 3 - xw;
+            sk[k] = (idx < tin && (unsigned)e < (unsigned)nx) ? mrow[e] : -1;
         }
         // (the status and the map are loaded together: a small launch is a
         // chain of load latencies)
@@ -241,8 +243,8 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
             C val;
             val.x = 0;
             val.y = 0;
-            if (e < nx) {
-                const int s = mrow[yo * nx + e];
+            if ((unsigned)(e - xw) < (unsigned)nx) {
+                const int s = mrow[yo * nx + e - xw];
                 if (s >= 0) {
                     const long long i = elem(s, c);
                     val = to_c<C>(update(i, load_ops(i), true));
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
         }
     }
     __syncthreads();
-    C* gq = grid + ((long long)q * g.npts + ((long long)z * My + y0) * Mx) * 3;
+    C* gq = grid + ((long long)q * g.npts + ((long long)(g.i0[2] + z) * My + g.i0[1] + y0) * Mx) * 3;
     if constexpr (CT) {
         // the last pass writes the grid itself
         auto store = line_io([&](int line, int e, const C& v) { gq[e * 3 + line] = v; });
@@ -336,7 +338,9 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
 #pragma unroll
         for (int k = 0; k < PF; ++k) {
             const int idx = threadIdx.x + k * NTHR;
-            ps[k] = idx < tout ? mrow[idx / 3] : -1;
+            // (a field is gathered at every point, in box-scan order)
+            if (MODE == GA_FIELD) ps[k] = idx < tout ? (z * ny + y0) * nx + idx / 3 : -1;
+            else ps[k] = idx < tout ? mrow[idx / 3] : -1;
         }
         if (skip_rhs(st, chk)) return;   // (as in k_scatter_x)
     }
@@ -376,7 +380,7 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
         return a.rhat[i];
     };
     double2 px[PF], pa[PF];
-    if constexpr (CT && PRE) {
+    if constexpr (CT && PRE && MODE != GA_FIELD) {
         // (clamped to site 0 where there is no site: the value is unused)
 #pragma unroll
         for (int k = 0; k < PF; ++k) pm[k] = mat[ps[k] >= 0 ? ps[k] : 0];
@@ -407,6 +411,10 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
     auto site = [&](int c, int e, int yo, int s, int mt, double2 xo, double2 xa) {
         const long long i = elem(s, c);
         const double2 gv = to_d(lds[(yo * 3 + c) * Lp + e]);
+        if constexpr (MODE == GA_FIELD) {   // the scattered field: no diagonal
+            a.out[i] = double2{-gv.x, -gv.y};
+            return;
+        }
         const double2 d = ai[mt * 3 + c];
         const double2 xin = MODE == GA_CONJ ? cconj(xo) : xo;
         const double2 y = cadd(gv, cmul(d, xin));
@@ -470,7 +478,9 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
         for (int k = 0; k < PF; ++k) {
             const int idx = threadIdx.x + k * NTHR;
             if (idx < tout && ps[k] >= 0) {
-                if constexpr (PRE) {
+                if constexpr (MODE == GA_FIELD) {
+                    site(idx % 3, idx / 3, 0, ps[k], 0, double2{0.0, 0.0}, double2{0.0, 0.0});
+                } else if constexpr (PRE) {
                     site(idx % 3, idx / 3, 0, ps[k], pm[k], px[k], pa[k]);
                 } else {
                     const long long i = elem(ps[k], idx % 3);
@@ -485,6 +495,10 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
             const int rest = idx / 3;
             const int e = rest % nx;
             const int yo = rest / nx;
+            if constexpr (MODE == GA_FIELD) {
+                site(c, e, yo, (z * ny + y0 + yo) * nx + e, 0, double2{0.0, 0.0}, double2{0.0, 0.0});
+                continue;
+            }
             const int s = mrow[yo * nx + e];
             if (s >= 0) {
                 const long long i = elem(s, c);
@@ -492,7 +506,7 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
             }
         }
     }
-    if (MODE != GA_PLAIN) {
+    if constexpr (MODE != GA_PLAIN && MODE != GA_FIELD) {
         double* sh = (double*)(lds + nlines * Lp);
         const int blk = blockIdx.y * bx + blockIdx.x;
         if constexpr (MODE == GA_B3) {
@@ -518,7 +532,7 @@ void scatter_dispatch(int chk, const Geo& g, const SiteArgs& a, typename V2<T>::
     using C = typename V2<T>::t;
     const int L = g.M[0];
     const int XL = x_lines_per_tile(g, a.nrhs, sizeof(T) == 4);
-    dim3 grd((g.n[1] + XL - 1) / XL, g.n[2], a.nrhs);
+    dim3 grd((g.i1[1] - g.i0[1] + XL - 1) / XL, g.i1[2] - g.i0[2], a.nrhs);
     switch (L) {
 #define DDA_CASE(LL)                                                                                            \
     case LL:                                                                                                   \
@@ -597,6 +611,7 @@ void launch_gather_x(int mode, int chk, const Geo& g, const SiteArgs& a, const t
         case GA_B1: gather_dispatch<T, GA_B1>(chk, g, a, grid, tw, s); break;
         case GA_B2: gather_dispatch<T, GA_B2>(chk, g, a, grid, tw, s); break;
         case GA_B3: gather_dispatch<T, GA_B3>(chk, g, a, grid, tw, s); break;
+        case GA_FIELD: gather_dispatch<T, GA_FIELD>(chk, g, a, grid, tw, s); break;
         default: gather_dispatch<T, GA_RES>(chk, g, a, grid, tw, s); break;
     }
 }

@@ -1027,6 +1027,48 @@ def test_nearfield_matches_oracle_everywhere(dda, name, precision):
     assert none is None and torch.equal(Es2, Es)
 
 
+# points of the volume below and above a 4-site box on x, y, z
+NF_WINDOWS = {
+    "plane_48": ((0, 0), (20, 0), (0, 20)),
+    "strided_96": ((10, 2), (30, 14), (5, 39)),
+    "strided_160": ((2, 8), (60, 1), (1, 60)),
+    "runtime": ((17, 0), (0, 18), (14, 3)),
+    "short": ((3, 30), (0, 6), (5, 1)),
+    "y256": ((0, 61), (60, 64), (0, 0)),
+    "z256": ((0, 5), (2, 12), (64, 60)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(NF_WINDOWS))
+@pytest.mark.parametrize("precision", ["fp64", "fp32_matvec"])
+def test_nearfield_input_window(dda, name, precision):
+    """The product of a volume whose sources fill only a window of it, at the
+    window's corners and through every variant of the passes: all variants
+    bitwise equal, and every point within the tolerances of
+    test_nearfield_matches_oracle_everywhere of the oracle's direct sums."""
+    from oracle import nearfield
+    ends = NF_WINDOWS[name]
+    ext = tuple(b / 4 for axis in ends for b in axis)
+    ijk = np.array([[0, 0, 0], [3, 3, 3], [0, 3, 1], [3, 0, 2], [1, 2, 0], [2, 1, 3]], dtype=np.int32)
+    tgt = dda.Target(ijk, 1.5 + 0.1j)
+    kh, e0 = np.array([[0.36, 0.48, 0.8]] * 2), np.array([[0.8, -0.6, 0]] * 2, dtype=complex)
+    P = w.random_vectors(35, (2, len(ijk), 3))
+    ref = None
+    for variant in range(29):
+        opts = dda.Options.for_size_parameter(1.3, precision=precision, kernel_variant=variant)
+        org, dims, Ei, Es = dda.nearfield(tgt, opts, ext, kh, e0, _cuda(P))
+        if ref is None:
+            ref = Es.clone()
+        assert torch.equal(Es, ref), variant
+    assert list(dims) == [4 + b + a for b, a in ends]
+    k = dense.kd_from_size_parameter(1.3, len(ijk))
+    tol = 1e-12 if precision == "fp64" else 2e-5
+    for q in range(2):
+        _, _, ri, rs = nearfield.nearfield(ijk, P[q], k, kh[q], e0[q], ext)
+        assert np.abs(Es[q].cpu().numpy() - rs).max() <= tol * np.abs(rs).max(), q
+        assert np.abs(Ei[q].cpu().numpy() - ri).max() <= 1e-13, q
+
+
 def test_nearfield_solution_satisfies_the_dda_equations(dda):
     """On a GPU solution the total field at the target's sites is the local
     field: |E_inc + E_sca - P / alpha| / |E_inc| over the sites equals the
