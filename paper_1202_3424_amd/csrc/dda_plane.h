@@ -368,17 +368,109 @@ __global__ __launch_bounds__(NTHR) __attribute__((amdgpu_waves_per_eu(WV))) void
 // The same fusion for grids with y and z extents of at most 20, which have no
 // compile-time kernels (targets of up to about ten sites across): the
 // plane of one kx in LDS as y lines (z, c) and as z lines (ky, c), the
-// runtime-planned transforms on each.  Bounded by latency: launches and
-// barriers (18^3, two right-hand sides, FP64: 15 us against 33 as three
-// kernels).
+// runtime-planned transforms on each.  Bounded by latency, so the chain is
+// kept short: a thread keeps its line through all the passes of an axis (one
+// division), each pass reads one LDS buffer and writes the other (one
+// barrier), the first and last pass of an axis read and write the grid or
+// the other axis' order, and the tensor values are loaded at the start.
+// 18^3 in FP64, us for two and for thirty-two right-hand sides: 9.8 and 20;
+// through the general runtime transform, with copies between the axes, 15.9
+// and 24; as three kernels 33 and 235.
 
-// LDS values of the two forms of the plane and the twiddles of both axes
+constexpr int SHORT_MAX = 20;
+// eight wavefronts: one butterfly, or two, of every pass for each thread
+constexpr int SHORT_NT = 512;
+
+// An axis' passes, at most three at these lengths, one word each: radix,
+// product of the radices before, and that product's 10-bit reciprocal (exact
+// quotients of values below SHORT_MAX).  Kernel arguments lie in host
+// memory: few bytes, read at the start.
+struct ShortPlan {
+    int L, tw, nst;
+    unsigned p0, p1, p2;
+};
+inline ShortPlan short_plan(const AxisPlan& ax) {
+    ShortPlan p{};
+    p.L = ax.L;
+    p.tw = ax.tw;
+    p.nst = ax.nst > 0 ? ax.nst : 1;   // (one point: a pass of radix 1)
+    if (p.nst > 3) throw std::invalid_argument("too many passes for a short axis");
+    int ns = 1;
+    for (int i = 0; i < p.nst; ++i) {
+        const int r = ax.nst > 0 ? ax.R[i] : 1;
+        (i == 0 ? p.p0 : i == 1 ? p.p1 : p.p2) = (unsigned)(r | ns << 8 | (1024 + ns - 1) / ns << 16);
+        ns *= r;
+    }
+    return p;
+}
+__device__ __forceinline__ unsigned short_word(const ShortPlan& p, int s) { return s == 0 ? p.p0 : s == 1 ? p.p1 : p.p2; }
+
+// LDS values of one of the two buffers, and with the twiddles of both axes
+constexpr int short_buffer(int LY, int LZ, int nz) {
+    const int a = nz * (LY | 1), b = LY * (LZ | 1);
+    return 3 * (a > b ? a : b);
+}
 constexpr size_t rt_values(int LY, int LZ, int nz) {
-    return (size_t)3 * nz * (LY | 1) + (size_t)3 * LY * (LZ | 1) + ((LY + 1) & ~1) + ((LZ + 1) & ~1);
+    return (size_t)2 * short_buffer(LY, LZ, nz) + ((LY + 1) & ~1) + ((LZ + 1) & ~1);
+}
+
+// One pass of one line (operations and order of fft_pass: bitwise the same):
+// the line's elements lie ss apart at src, results go ds apart to dst;
+// IN: only elements [e0, e1) are inputs, the others zero; OUT: only results
+// e < e1 are stored.  Butterflies jb, jb + jn, ...
+template <typename T, int RR, int DIR, bool IN, bool OUT>
+__device__ __forceinline__ void short_pass(const typename V2<T>::t* src, int ss, typename V2<T>::t* dst, int ds,
+                                           int e0, int e1, const typename V2<T>::t* tw, int L, unsigned w, int jb,
+                                           int jn) {
+    using C = typename V2<T>::t;
+    const int Ns = w >> 8 & 255, inv = w >> 16;
+    const int LR = L / RR;
+    const int tstep = LR * inv >> 10;   // LR / Ns
+    for (int j = jb; j < LR; j += jn) {
+        C v[RR];
+        const unsigned o = __umul24(j, ss);
+#pragma unroll
+        for (int r = 0; r < RR; ++r) {
+            if (IN) {
+                v[r].x = 0;
+                v[r].y = 0;
+                if (j + r * LR >= e0 && j + r * LR < e1) v[r] = src[o + r * LR * ss];
+            } else {
+                v[r] = src[o + r * LR * ss];
+            }
+        }
+        const int k = j - __umul24(Ns, __umul24(j, inv) >> 10);
+        if (Ns > 1) {
+            const int kt = __umul24(k, tstep);
+#pragma unroll
+            for (int r = 1; r < RR; ++r) {
+                C t = tw[r * kt];
+                if (DIR > 0) t.y = -t.y;
+                v[r] = cmul(v[r], t);
+            }
+        }
+        if constexpr (RR > 1) Dft<RR, DIR, C>::run(v);
+        const int b = (j - k) * RR + k;
+        const unsigned d = __umul24(b, ds);
+#pragma unroll
+        for (int q = 0; q < RR; ++q)
+            if (!OUT || b + q * Ns < e1) dst[d + q * Ns * ds] = v[q];
+    }
+}
+template <typename T, int DIR, bool IN, bool OUT>
+__device__ __forceinline__ void short_step(const typename V2<T>::t* src, int ss, typename V2<T>::t* dst, int ds,
+                                           int e0, int e1, const typename V2<T>::t* tw, int L, unsigned w, int jb,
+                                           int jn) {
+    switch (w & 255) {
+#define DDA_R(N) \
+    case N: short_pass<T, N, DIR, IN, OUT>(src, ss, dst, ds, e0, e1, tw, L, w, jb, jn); break;
+        DDA_R(8) DDA_R(5) DDA_R(4) DDA_R(3) DDA_R(2) DDA_R(1)
+#undef DDA_R
+    }
 }
 
 template <typename T>
-__global__ __launch_bounds__(NT) void k_plane_rt(Geo g, AxisPlan py, AxisPlan pz, typename V2<T>::t* grid,
+__global__ __launch_bounds__(SHORT_NT) void k_plane_rt(Geo g, ShortPlan py, ShortPlan pz, typename V2<T>::t* grid,
                                                 const double2* tw64, const typename V2<T>::t* ghat,
                                                 const RhsState* st, int chk) {
     using C = typename V2<T>::t;
@@ -389,72 +481,95 @@ __global__ __launch_bounds__(NT) void k_plane_rt(Geo g, AxisPlan py, AxisPlan pz
     const int Ly = My | 1, Lz = Mz | 1;
     C* twy = (C*)smem;
     C* twz = twy + ((My + 1) & ~1);
-    C* A = twz + ((Mz + 1) & ~1);   // [z][c][Ly]
-    C* B = A + 3 * nz * Ly;         // [ky][c][Lz]
-    load_twiddles<T>(twy, tw64, py);
-    load_twiddles<T>(twz, tw64, pz);
+    C* buf = twz + ((Mz + 1) & ~1);
+    const int other = short_buffer(My, Mz, nz);   // the second buffer's offset
     C* gq = grid + (long long)q * g.npts * 3 + (long long)kx * 3;
-    // lines per call of the runtime transform (its tile bound)
-    const int by = Tile<T>::EMAX / My, bz = Tile<T>::EMAX / Mz;
-    C zero;
-    zero.x = 0;
-    zero.y = 0;
-    for (int i = threadIdx.x; i < 3 * nz * My; i += NT) {
-        const int c = i % 3, y = i / 3 % My, z = i / (3 * My);
-        A[(z * 3 + c) * Ly + y] =
-            z >= g.i0[2] && z < g.i1[2] && y >= g.i0[1] && y < g.i1[1] ? gq[((long long)z * My + y) * Mx * 3 + c] : zero;
-    }
-    __syncthreads();
-    for (int l = 0; l < 3 * nz; l += by) fft_lines<T, -1>(A + l * Ly, twy, min(by, 3 * nz - l), Ly, py);
-    for (int i = threadIdx.x; i < 3 * My * Mz; i += NT) {
-        const int ky = i % My, z = i / My % Mz, c = i / (My * Mz);
-        B[(ky * 3 + c) * Lz + z] = z < nz ? A[(z * 3 + c) * Ly + ky] : zero;
-    }
-    __syncthreads();
-    for (int l = 0; l < 3 * My; l += bz) fft_lines<T, -1>(B + l * Lz, twz, min(bz, 3 * My - l), Lz, pz);
-    const bool ux = kx > Mx / 2;
-    const int fx = ux ? Mx - kx : kx;
-    for (int i = threadIdx.x; i < My * Mz; i += NT) {
-        const int ky = i % My, kz = i / My;
-        const bool uy = ky > My / 2, uz = kz > Mz / 2;
-        const int fy = uy ? My - ky : ky, fz = uz ? Mz - kz : kz;
-        const C* Gp = ghat + (((long long)fz * g.H[1] + fy) * g.H[0] + fx) * 6;
-        C G[6];
-#pragma unroll
-        for (int k = 0; k < 6; ++k) G[k] = Gp[k];
-        // diagonal components are even in every index, ab is odd in a and b
-        if (ux != uy) { G[1].x = -G[1].x; G[1].y = -G[1].y; }
-        if (ux != uz) { G[2].x = -G[2].x; G[2].y = -G[2].y; }
-        if (uy != uz) { G[4].x = -G[4].x; G[4].y = -G[4].y; }
-        C* p = B + ky * 3 * Lz + kz;
-        const C X = p[0], Y = p[Lz], Z = p[2 * Lz];
-        p[0] = passes::trow(G[0], G[1], G[2], X, Y, Z);
-        p[Lz] = passes::trow(G[1], G[3], G[4], X, Y, Z);
-        p[2 * Lz] = passes::trow(G[2], G[4], G[5], X, Y, Z);
-    }
-    __syncthreads();
-    for (int l = 0; l < 3 * My; l += bz) fft_lines<T, 1>(B + l * Lz, twz, min(bz, 3 * My - l), Lz, pz);
-    for (int i = threadIdx.x; i < 3 * My * nz; i += NT) {
-        const int z = i % nz, ky = i / nz % My, c = i / (nz * My);
-        A[(z * 3 + c) * Ly + ky] = B[(ky * 3 + c) * Lz + z];
-    }
-    __syncthreads();
-    for (int l = 0; l < 3 * nz; l += by) fft_lines<T, 1>(A + l * Ly, twy, min(by, 3 * nz - l), Ly, py);
-    for (int i = threadIdx.x; i < 3 * nz * ny; i += NT) {
-        const int c = i % 3, y = i / 3 % ny, z = i / (3 * ny);
-        gq[((long long)z * My + y) * Mx * 3 + c] = A[(z * 3 + c) * Ly + y];
-    }
-}
+    const int ys = Mx * 3;
+    const int tid = threadIdx.x;
+    // this thread's y line (z, c) and z line (ky, c), and its butterflies
+    const int nly = 3 * nz, nlz = 3 * My;
+    const int jny = SHORT_NT / nly, jnz = SHORT_NT / nlz;
+    const int ly = tid % nly, lz = tid % nlz;
+    const int jby = tid / nly < jny ? tid / nly : My, jbz = tid / nlz < jnz ? tid / nlz : Mz;
+    const int zy = ly / 3, cy = ly - 3 * zy, kz = lz / 3, cz = lz - 3 * kz;
+    C* gl = gq + (long long)zy * My * ys + cy;
 
-// The radix sequence the strided passes use on an axis: a compile-time
-// length's, or the runtime plan's.
-inline AxisPlan strided_plan(const AxisPlan& ax) {
-    AxisPlan p = ax;
-    if (ct_plan(ax.L, -1) > 0) {
-        p.nst = ct_plan(ax.L, -1);
-        for (int i = 0; i < p.nst; ++i) p.R[i] = ct_plan(ax.L, i);
+    // tensor values of this thread's point (ky, kz)
+    static_assert(SHORT_NT >= SHORT_MAX * SHORT_MAX, "points of a plane");
+    C G[6];
+    const int p = min(tid, My * Mz - 1);
+    const int h = (p * ((65536 + My - 1) / My)) >> 16, k = p - h * My;
+    const bool ux = kx > Mx / 2, uy = k > My / 2, uz = h > Mz / 2;
+    const C* Gp = ghat + (((long long)(uz ? Mz - h : h) * g.H[1] + (uy ? My - k : k)) * g.H[0] +
+                          (ux ? Mx - kx : kx)) * 6;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) G[c] = Gp[c];
+    // diagonal components are even in every index, ab is odd in a and b
+    if (ux != uy) { G[1].x = -G[1].x; G[1].y = -G[1].y; }
+    if (ux != uz) { G[2].x = -G[2].x; G[2].y = -G[2].y; }
+    if (uy != uz) { G[4].x = -G[4].x; G[4].y = -G[4].y; }
+    for (int i = tid; i < My + Mz; i += SHORT_NT) {
+        const double2 w = tw64[i < My ? py.tw + i : pz.tw + i - My];
+        C* d = i < My ? twy + i : twz + i - My;
+        d->x = (T)w.x;
+        d->y = (T)w.y;
     }
-    return p;
+
+    int at = 0;   // offset of the buffer that holds the data
+    for (int s = 0; s < py.nst; ++s) {
+        const unsigned w = short_word(py, s);
+        C* o = buf + (other - at);
+        const bool last = s == py.nst - 1;   // ... into z lines
+        C* dst = last ? o + cy * Lz + zy : o + ly * Ly;
+        const int ds = last ? 3 * Lz : 1;
+        if (s == 0) {
+            const int e1 = zy >= g.i0[2] && zy < g.i1[2] ? g.i1[1] : 0;
+            short_step<T, -1, true, false>(gl, ys, dst, ds, g.i0[1], e1, twy, My, w, jby, jny);
+        } else {
+            short_step<T, -1, false, false>(buf + at + ly * Ly, 1, dst, ds, 0, 0, twy, My, w, jby, jny);
+        }
+        at = other - at;
+        __syncthreads();
+    }
+    for (int s = 0; s < pz.nst; ++s) {
+        const unsigned w = short_word(pz, s);
+        const C* src = buf + at + lz * Lz;
+        C* dst = buf + (other - at) + lz * Lz;
+        if (s == 0) short_step<T, -1, true, false>(src, 1, dst, 1, 0, nz, twz, Mz, w, jbz, jnz);
+        else short_step<T, -1, false, false>(src, 1, dst, 1, 0, 0, twz, Mz, w, jbz, jnz);
+        at = other - at;
+        __syncthreads();
+    }
+    if (tid < My * Mz) {
+        C* b = buf + at + k * 3 * Lz + h;
+        const C X = b[0], Y = b[Lz], Z = b[2 * Lz];
+        b[0] = passes::trow(G[0], G[1], G[2], X, Y, Z);
+        b[Lz] = passes::trow(G[1], G[3], G[4], X, Y, Z);
+        b[2 * Lz] = passes::trow(G[2], G[4], G[5], X, Y, Z);
+    }
+    __syncthreads();
+    for (int s = 0; s < pz.nst; ++s) {
+        const unsigned w = short_word(pz, s);
+        const C* src = buf + at + lz * Lz;
+        C* o = buf + (other - at);
+        if (s == pz.nst - 1)   // ... z < nz into y lines
+            short_step<T, 1, false, true>(src, 1, o + cz * Ly + kz, 3 * Ly, 0, nz, twz, Mz, w, jbz, jnz);
+        else
+            short_step<T, 1, false, false>(src, 1, o + lz * Lz, 1, 0, 0, twz, Mz, w, jbz, jnz);
+        at = other - at;
+        __syncthreads();
+    }
+    for (int s = 0; s < py.nst; ++s) {
+        const unsigned w = short_word(py, s);
+        const C* src = buf + at + ly * Ly;
+        if (s == py.nst - 1) {   // ... y < ny into the grid
+            short_step<T, 1, false, true>(src, 1, gl, ys, 0, ny, twy, My, w, jby, jny);
+            break;
+        }
+        short_step<T, 1, false, false>(src, 1, buf + (other - at) + ly * Ly, 1, 0, 0, twy, My, w, jby, jny);
+        at = other - at;
+        __syncthreads();
+    }
 }
 
 // ------------------------------------------------------------------ launcher
@@ -489,10 +604,10 @@ bool plane_launch_z(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, co
 // The short-length kernel takes grids of one target with at most 20 points
 // along y and z, the lengths below the shortest compile-time one.  Measured,
 // us for passes 2-4 here and as three kernels: 18 x 18, two right-hand sides
-// 15 and 33, thirty-two 24 and 235; but 20 x 48, whose z pass has a
-// compile-time kernel, 28 and 19.
+// 9.8 and 33, thirty-two 20 and 235; but 20 x 48, whose z pass has a
+// compile-time kernel, 28 (this kernel's first form) and 19.
 template <typename T> bool plane_short(const Geo& g) {
-    return !g.rg && g.M[1] <= 20 && g.M[2] <= 20 &&
+    return !g.rg && g.M[1] <= plane::SHORT_MAX && g.M[2] <= plane::SHORT_MAX &&
            plane::rt_values(g.M[1], g.M[2], g.n[2]) * sizeof(typename V2<T>::t) <= plane::PLANE_LDS;
 }
 
@@ -502,9 +617,9 @@ void launch_plane(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, cons
     bool done = false;
     if (plane_short<T>(g)) {
         hipStream_t stream = s;
-        DDA_LAUNCH((plane::k_plane_rt<T>), dim3(g.M[0], nrhs), dim3(NT),
+        DDA_LAUNCH((plane::k_plane_rt<T>), dim3(g.M[0], nrhs), dim3(plane::SHORT_NT),
                    plane::rt_values(g.M[1], g.M[2], g.n[2]) * sizeof(typename V2<T>::t), stream, g,
-                   plane::strided_plan(g.ax[1]), plane::strided_plan(g.ax[2]), grid, tw, gp, st, chk);
+                   plane::short_plan(g.ax[1]), plane::short_plan(g.ax[2]), grid, tw, gp, st, chk);
         return;
     }
     switch (g.M[1]) {
