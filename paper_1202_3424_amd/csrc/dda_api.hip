@@ -574,6 +574,20 @@ struct Work {
                          out + (size_t)sg.first * t->nmat * 3, s, t->nmat);
     }
 
+    // The incidences to the device and 1/alpha from them: for a few right-hand
+    // sides in one launch that carries them as arguments.  Two copies and
+    // the launch cost a product of a small target 3.5 us of copies and the
+    // gaps between them (389 sites: 26.6 us so and 22.3 in one).
+    void incidence(const double* khv, const double2* e0v, const dda_opts* o) {
+        if (segs.empty() && nrhs <= INC_ARGS) {
+            launch_alpha_inc(nrhs, t->nmat, (const double2*)t->mdev.p, o->m_medium, khv, e0v, kd, o->polarizability,
+                             (double2*)a.ainv, kh, e0, s);
+            return;
+        }
+        upload_incidence(khv, e0v);
+        alpha_table(o->polarizability, o->m_medium, (double2*)a.ainv);
+    }
+
     // the three strided passes: 0 = y forward, 1 = z with the tensor product, 2 = y inverse
     template <typename T>
     void strided_slot(int slot, int chk, int variant) {
@@ -1189,11 +1203,10 @@ dda_status solve_one(dda_ctx* c, dda_target* t, const dda_opts* o, int nrhs, con
     w.b2 = o->solver == DDA_BICGSTAB2;
     w.graphs = false;   // one stream: replays are slower than launches
     w.autotune((o->flags & DDA_FLAG_NO_AUTOTUNE) == 0, o->kernel_variant);
-    w.upload_incidence(kh, e0);
     const bool warm = P0 != nullptr;
     {
         Timed tm(c, T_SETUP, w.s);
-        w.alpha_table(o->polarizability, o->m_medium, (double2*)w.a.ainv);
+        w.incidence(kh.data(), e0.data(), o);
         if (b_caller)
             launch_permute(nrhs, t->nsites, 3, (const int*)t->perm.p, (const double2*)b_caller, w.a.b, true, w.s);
         else
@@ -1841,8 +1854,7 @@ dda_status dda_apply(dda_ctx* c, dda_target* t, const dda_opts* o, int32_t n_rhs
         w.b2 = o->solver == DDA_BICGSTAB2;
         w.graphs = false;   // one stream: replays are slower than launches
         w.autotune((o->flags & DDA_FLAG_NO_AUTOTUNE) == 0, o->kernel_variant);
-        w.upload_incidence(kh, e0);
-        w.alpha_table(o->polarizability, o->m_medium, (double2*)w.a.ainv);
+        w.incidence(kh.data(), e0.data(), o);
         plain_product(w, x, y);
         return DDA_OK;
     });
@@ -1879,8 +1891,7 @@ dda_status dda_apply_noalloc(dda_ctx* c, dda_target* t, const dda_opts* o, int32
         } ne(c);
         Work w(c, c->main, t, n_rhs, kd, fp32, base, L);
         w.autotune(false, o->kernel_variant);   // the tiling tuned for this shape, else the default
-        w.upload_incidence(khv, e0v);
-        w.alpha_table(o->polarizability, o->m_medium, (double2*)w.a.ainv);
+        w.incidence(khv, e0v, o);
         plain_product(w, x, y);
         return DDA_OK;
     });
@@ -1953,8 +1964,7 @@ dda_status dda_grad_eps(dda_ctx* c, dda_target* t, const dda_opts* o, const dda_
         w.b2 = o->solver == DDA_BICGSTAB2;
         w.graphs = false;   // one stream: replays are slower than launches
         w.autotune((o->flags & DDA_FLAG_NO_AUTOTUNE) == 0, o->kernel_variant);
-        w.upload_incidence(kh, e0);
-        w.alpha_table(o->polarizability, o->m_medium, (double2*)w.a.ainv);
+        w.incidence(kh.data(), e0.data(), o);
         double2* dainv = (double2*)c->dainv.ensure((size_t)t->nmat * 3 * sizeof(double2));
         w.alpha_table(o->polarizability + 2, o->m_medium, dainv);
         // P in sorted order, kept for the gradient

@@ -223,6 +223,11 @@ void launch_green(const Geo& g, double kd, double2* work, double2* gh64, float2*
 // 1/alpha (scheme + 2: its derivative in eps) per (right-hand side, material)
 // from the target's distinct refractive indices mats [nmat] and the ambient
 // medium's index
+// (of at most INC_ARGS right-hand sides: the incidences khat and e0 are host
+// arrays, which travel as kernel arguments and are stored to the device too)
+constexpr int INC_ARGS = 8;
+void launch_alpha_inc(int nrhs, int nmat, const double2* mats, double m_medium, const double* khat, const double2* e0,
+                      double kd, int scheme, double2* ainv, double* khat_dev, double2* e0_dev, hipStream_t s);
 void launch_alpha(int nrhs, int nmat, const double2* mats, double m_medium, const double* khat, const double2* e0,
                   double kd, int scheme, double2* ainv, hipStream_t s, int ostride = 0);
 void launch_einc(const SiteArgs& a, const int* coords, const double* khat, const double2* e0, hipStream_t s);
