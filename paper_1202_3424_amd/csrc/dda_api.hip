@@ -206,7 +206,9 @@ struct dda_target {
     double green_kd = -1.0;
     bool have64 = false, have32 = false;
     DevBuf gh64, gh32;
-    DevBuf gp64, gp32;                 // the same in the plane kernel's layout, where it takes this grid
+    // the same in the plane kernel's layout, where it takes this grid (behind
+    // the octant in the same allocation), else null
+    void *gp64 = nullptr, *gp32 = nullptr;
     int lo[3] = {0, 0, 0};             // lattice coordinates of the bounding box's first point
     // near field: the last extended volume (every point a site), keyed by the
     // points added below and above the box on each axis
@@ -719,7 +721,7 @@ struct Work {
         if (sizeof(T) == 4 ? plane32 : plane64) {
             Timed tm(c, T_FFTZ_G, s);
             const dda_target* src = segs.empty() ? t : segs[0].t;
-            const void* gp = plane_short<T>(g) ? ghat(sizeof(T) == 4) : sizeof(T) == 4 ? src->gp32.p : src->gp64.p;
+            const void* gp = plane_short<T>(g) ? ghat(sizeof(T) == 4) : sizeof(T) == 4 ? src->gp32 : src->gp64;
             launch_plane<T>(chk_rest, g, nrhs, gr, tw, (const C*)gp, a.st, s);
         } else {
             {
@@ -768,16 +770,18 @@ void ensure_green(dda_ctx* c, dda_target* t, double kd, bool fp32, bool force) {
     const size_t nh = (size_t)g.H[0] * g.H[1] * g.H[2] * 6;
     if (fresh) t->have64 = t->have32 = false;
     double2* work = (double2*)c->gtmp.ensure(green_work_values(g) * sizeof(double2));
-    double2* g64 = (double2*)t->gh64.ensure(nh * sizeof(double2));
-    float2* g32 = fp32 ? (float2*)t->gh32.ensure(nh * sizeof(float2)) : nullptr;
-    launch_green(g, kd, work, g64, g32, tw, c->stream);
     // the plane kernel's layout, where it takes this grid (with any number of
     // right-hand sides; launch limits are checked with the product)
     const bool p64 = plane_fits<double>(g, 1) && !plane_short<double>(g);
     const bool p32 = fp32 && plane_fits<float>(g, 1) && !plane_short<float>(g);
+    const size_t np = p64 || p32 ? plane_values(g) : 0, nhp = (nh + 15) & ~(size_t)15;   // (rows on cache lines)
+    double2* g64 = (double2*)t->gh64.ensure((nhp + (p64 ? np : 0)) * sizeof(double2));
+    float2* g32 = fp32 ? (float2*)t->gh32.ensure((nhp + (p32 ? np : 0)) * sizeof(float2)) : nullptr;
+    launch_green(g, kd, work, g64, g32, tw, c->stream);
+    if (p64) t->gp64 = g64 + nhp;
+    if (p32) t->gp32 = g32 + nhp;
     if (p64 || p32)
-        launch_green_plane(g, g64, p64 ? (double2*)t->gp64.ensure(plane_values(g) * sizeof(double2)) : nullptr,
-                           p32 ? (float2*)t->gp32.ensure(plane_values(g) * sizeof(float2)) : nullptr, c->stream);
+        launch_green_plane(g, g64, p64 ? (double2*)t->gp64 : nullptr, p32 ? (float2*)t->gp32 : nullptr, c->stream);
     HIPCHK(hipGetLastError());
     t->green_kd = kd;
     t->have64 = true;
@@ -904,8 +908,8 @@ void run_chunk(Work& w, int chunk) {
     key_bytes(key, w.t->gh64.p);
     key_bytes(key, w.t->gh32.p);
     key_bytes(key, w.t->tw.p);
-    key_bytes(key, w.t->gp64.p);
-    key_bytes(key, w.t->gp32.p);
+    key_bytes(key, w.t->gp64);
+    key_bytes(key, w.t->gp32);
     key_bytes(key, w.var);
     key_bytes(key, w.plane64);
     key_bytes(key, w.plane32);
@@ -1326,8 +1330,8 @@ Job make_batch(dda_ctx* c, const std::vector<Job*>& mem) {
         r.kd = j->kd;
         r.ghat[0] = jt->gh64.p;
         r.ghat[1] = jt->gh32.p;
-        r.gplane[0] = jt->gp64.p;
-        r.gplane[1] = jt->gp32.p;
+        r.gplane[0] = jt->gp64;
+        r.gplane[1] = jt->gp32;
         for (int k = 0; k < count; ++k) b.host_rg.push_back(r);
         m.batch_site_blocks = std::max(m.batch_site_blocks, r.site_blocks);
         m.idx.insert(m.idx.end(), j->idx.begin(), j->idx.end());
@@ -1678,8 +1682,7 @@ void free_target(dda_target* t) {
     if (!t) return;
     free_target(t->nf);
     t->nf = nullptr;
-    for (DevBuf* b : {&t->map, &t->perm, &t->mat, &t->coords, &t->tw, &t->tw32, &t->mdev, &t->gh64, &t->gh32, &t->gp64,
-                      &t->gp32})
+    for (DevBuf* b : {&t->map, &t->perm, &t->mat, &t->coords, &t->tw, &t->tw32, &t->mdev, &t->gh64, &t->gh32})
         b->release();
     delete t;
 }
