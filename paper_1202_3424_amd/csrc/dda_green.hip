@@ -71,12 +71,13 @@ __global__ __launch_bounds__(NT) void k_green_x(Geo g, double kd, double2* out, 
     double2* tws = (double2*)smem;
     double2* lds = tws + ((Mx + 1) & ~1);
     load_twiddles<double>(tws, tw64, g.ax[0]);
+    const Divisor dm(Mx), dh(Hx);
     double2 hold[MAXP][3];
 #pragma unroll
     for (int i = 0; i < MAXP; ++i) {
         const int p = threadIdx.x + i * NT;
         if (p < nl * Mx) {
-            const int m = p % Mx, yo = p / Mx;
+            const int yo = dm.quot(p), m = p - yo * Mx;
             double2 v[6];
             // the slots between +(n-1) and -(n-1) hold no separation
             const bool ok = m <= nx - 1 || m >= Mx - (nx - 1);
@@ -98,8 +99,7 @@ __global__ __launch_bounds__(NT) void k_green_x(Geo g, double kd, double2* out, 
         fft_lines<double, -1>(lds, tws, 3 * nl, Lp, g.ax[0]);
         for (int idx = threadIdx.x; idx < nl * Hx * 3; idx += NT) {
             const int c = idx % 3;
-            const int e = idx / 3 % Hx;
-            const int yo = idx / (3 * Hx);
+            const int yo = dh.quot(idx / 3), e = idx / 3 - yo * Hx;
             o[((long long)yo * Hx + e) * 6 + 3 * half + c] = lds[(yo * 3 + c) * Lp + e];
         }
         if (half == 0) {
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(NT) void k_green_x(Geo g, double kd, double2* out, 
             for (int i = 0; i < MAXP; ++i) {
                 const int p = threadIdx.x + i * NT;
                 if (p < nl * Mx) {
-                    const int m = p % Mx, yo = p / Mx;
+                    const int yo = dm.quot(p), m = p - yo * Mx;
 #pragma unroll
                     for (int c = 0; c < 3; ++c) lds[(yo * 3 + c) * Lp + m] = hold[i][c];
                 }

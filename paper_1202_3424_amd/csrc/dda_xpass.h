@@ -235,11 +235,12 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
             lds[(idx % 3) * Lp + idx / 3] = val;
         }
     } else {
+        const Divisor de(ext);
         for (int idx = threadIdx.x; idx < tin; idx += NTHR) {
             const int c = idx % 3;
             const int rest = idx / 3;
-            const int e = rest % ext;
-            const int yo = rest / ext;
+            const int yo = de.quot(rest);
+            const int e = rest - yo * ext;
             C val;
             val.x = 0;
             val.y = 0;
@@ -263,11 +264,12 @@ __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename 
     } else {
         fft_lines<T, -1, NTHR>(lds, tws, nlines, Lp, g.ax[0]);
         const int tot = nl * Mx * 3;
+        const Divisor dm(Mx);
         for (int idx = threadIdx.x; idx < tot; idx += NTHR) {
             const int c = idx % 3;
             const int rest = idx / 3;
-            const int e = rest % Mx;
-            const int yo = rest / Mx;
+            const int yo = dm.quot(rest);
+            const int e = rest - yo * Mx;
             gq[idx] = lds[(yo * 3 + c) * Lp + e];
         }
     }
@@ -348,11 +350,12 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
     // (compile-time lengths: the first pass reads the grid itself)
     if constexpr (!CT) {
         const int tot = nl * Mx * 3;
+        const Divisor dm(Mx);
         for (int idx = threadIdx.x; idx < tot; idx += NTHR) {
             const int c = idx % 3;
             const int rest = idx / 3;
-            const int e = rest % Mx;
-            const int yo = rest / Mx;
+            const int yo = dm.quot(rest);
+            const int e = rest - yo * Mx;
             lds[(yo * 3 + c) * Lp + e] = gq[idx];
         }
     }
@@ -490,11 +493,12 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
             }
         }
     } else {
+        const Divisor dx(nx);
         for (int idx = threadIdx.x; idx < tout; idx += NTHR) {
             const int c = idx % 3;
             const int rest = idx / 3;
-            const int e = rest % nx;
-            const int yo = rest / nx;
+            const int yo = dx.quot(rest);
+            const int e = rest - yo * nx;
             if constexpr (MODE == GA_FIELD) {
                 site(c, e, yo, (z * ny + y0 + yo) * nx + e, 0, double2{0.0, 0.0}, double2{0.0, 0.0});
                 continue;
