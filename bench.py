@@ -241,12 +241,18 @@ def summarize_profiles(tr: str, workload: str, prec: str, unprofiled: str) -> No
 
     L_dom = ub["config"]["fft_grid"][SLOT_OF_PASS[dom] // 2 + 1]
     n_var = CT_VARIANTS[dom] if L_dom in CT_LENGTHS else 1
+    # the plane kernel took the three strided passes: nothing was autotuned
+    plane = "fft_y_fwd" not in ub["matvec"]["passes_calibration_step"]
 
     def per_variant(path, counter, scale):
         fam = sorted((r for r in rows(path) if r["Counter_Name"] == counter and pat.search(r["Kernel_Name"])),
                      key=lambda r: int(r["Dispatch_Id"]))
         out = {}
         v = 0
+        if plane:   # the median launch: converged right-hand sides are skipped only at the end
+            fam = [r for r in fam if "k_plane<" in r["Kernel_Name"]]
+            top = statistics.mode(short(r["Kernel_Name"]) for r in fam)
+            return {0: (top, statistics.median(float(r["Counter_Value"]) for r in fam) * 1024 * scale)}
         while v < n_var and (v + 1) * AUTOTUNE_LAUNCHES <= len(fam):
             grp = fam[v * AUTOTUNE_LAUNCHES:(v + 1) * AUTOTUNE_LAUNCHES]
             names = {short(r["Kernel_Name"]) for r in grp}
@@ -318,7 +324,7 @@ def summarize_profiles(tr: str, workload: str, prec: str, unprofiled: str) -> No
     for name, cal in ub["matvec"]["passes_calibration_step"].items():
         pp = re.compile(PASS_PATTERNS[name])
         L = grid[SLOT_OF_PASS[name] // 2 + 1] if name in SLOT_OF_PASS else None
-        trials = AUTOTUNE_LAUNCHES * (CT_VARIANTS[name] if L in CT_LENGTHS else 1) if L else 0
+        trials = AUTOTUNE_LAUNCHES * (CT_VARIANTS[name] if L in CT_LENGTHS else 1) if L and not plane else 0
         if name == "fft_y_fwd" and grid[2] in CT_LENGTHS:
             # pass 3's candidates are timed behind the chosen forward y pass:
             # one warm-up and twenty launches of it alone, then twenty per
