@@ -1581,6 +1581,30 @@ def test_plane_kernel_order_of_workgroups(dda, nx):
             assert torch.equal(y, ref), (q, precision)
 
 
+@pytest.mark.parametrize("materials", [1, 3])
+def test_incidences_as_arguments_equal_copied_ones(dda, materials):
+    """Up to eight incidences travel as kernel arguments, more are copied to
+    the device: a nine-right-hand-side product and solve, every incidence its
+    own, are bitwise the eight and the one they consist of."""
+    ijk = w.sphere_integer(4.5)
+    n = len(ijk)
+    m = np.array([1.33 + 0.01j, 1.5 + 0.2j, 1.1 + 0.3j])[np.arange(n) % materials]
+    tgt = dda.Target(ijk, m)
+    rng = np.random.default_rng(36)
+    kh = rng.normal(size=(9, 3))
+    kh /= np.linalg.norm(kh, axis=1)[:, None]
+    e0 = np.cross(kh, rng.normal(size=(9, 3))) + 1j * np.cross(kh, rng.normal(size=(9, 3)))
+    opts = dda.Options.for_size_parameter(1.0)
+    xv = _cuda(w.random_vectors(36, (9, n, 3)))
+    y = dda.apply(tgt, opts, kh, e0, xv)
+    P, res = dda.solve(tgt, opts, kh, e0)
+    for a, b in ((0, 8), (8, 9)):
+        assert torch.equal(dda.apply(tgt, opts, kh[a:b], e0[a:b], xv[a:b].contiguous()), y[a:b])
+        Ps, rs = dda.solve(tgt, opts, kh[a:b], e0[a:b])
+        assert torch.equal(Ps, P[a:b])
+        assert [r["qext"] for r in rs] == [r["qext"] for r in res[a:b]]
+
+
 def test_apply_with_overlapping_vectors(dda):
     """x and y of a product that overlap in part (one buffer, y a right-hand
     side further on): the same result as with separate buffers, the caller's
