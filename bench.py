@@ -107,8 +107,7 @@ def kernel_source_digest() -> str:
 # reads its input and rhat and writes its output.  QMR: the scatter reads r,
 # p and the smoothed pair (s, y) and x, and writes p, s, y, x; the gather reads
 # p and writes v.  BiCGstab(2): 3, 6, 6 and 9 vectors in the four scatters,
-# 3 in every gather.  The plain product (near field): its input, and input
-# plus output.
+# 3 in every gather.  The plain product: its input, and input plus output.
 SITE_VECTORS = {"bicgstab": (6, 3), "qmr": (9, 2), "bicgstab2": (6, 3), "plain": (1, 2)}
 
 
@@ -137,6 +136,29 @@ def pass_bytes(tgt, n_sites: int, csize: int, solver: str = "bicgstab", plane: b
         # read the x lines and the solver's site vectors; the box map and
         # materials once
         "fft_x_gather": (Mx * ny * nz * g + sv_gather * site, 4 * nbox + 4 * n_sites),
+    }
+
+
+def field_bytes(vol, tgt, csize: int, plane: bool = False) -> dict:
+    """pass_bytes of the near field's product on a volume ``vol``: its inputs
+    fill only the target's box (the scatter writes, and the forward y pass
+    reads, the target's lines; the z pass reads the target's planes), the
+    scatter reads one vector of the target's sites, the gather writes one of
+    the volume's points and reads no map."""
+    nx, ny, nz = tgt.box
+    vx, vy, vz = vol.box
+    Mx, My, Mz = vol.grid
+    g = 3 * csize
+    lines = Mx * ny * nz * g
+    planes = Mx * My * nz * g
+    octant = (Mx // 2 + 1) * (My // 2 + 1) * (Mz // 2 + 1) * 6 * csize
+    out = Mx * vy * vz * g
+    return {
+        "scatter_fft_x": (lines + 48 * tgt.n_sites, 4 * nx * ny * nz),
+        "fft_y_fwd": (0 if plane else lines + planes, 0),
+        "fft_z_green": (lines + out if plane else planes + Mx * My * vz * g, octant),
+        "fft_y_inv": (0 if plane else Mx * My * vz * g + out, 0),
+        "fft_x_gather": (out + 48 * vx * vy * vz, 0),
     }
 
 
@@ -521,7 +543,7 @@ def nearfield_measurement(dda, np, torch, job, d, reps: int = 10, cpu: bool = Tr
     class Vol:   # the grown volume as the product sees it: every point a site
         box = tuple(int(v) for v in dims)
         grid = tuple(padded(int(v)) for v in dims)
-    bp = pass_bytes(Vol, npts, 16, "plain", plane=tm["fft_y_fwd"][2] == 0)
+    bp = field_bytes(Vol, t, 16, plane=tm["fft_y_fwd"][2] == 0)
     passes = {}
     for name in PASSES:
         pms, nl, _ = tm[name]
@@ -536,7 +558,7 @@ def nearfield_measurement(dda, np, torch, job, d, reps: int = 10, cpu: bool = Tr
            "product_GBps": kern_bytes / (kern_ms * 1e-3) / 1e9, "passes": passes,
            "note": "one call = E_inc and E_sca for both polarizations on every point of the volume, the "
                    "volume's tensor FFT kept from an earlier call (ms_per_call_tensor_rebuilt: built in the "
-                   "call); wall time includes placing P and writing both fields"}
+                   "call); wall time includes writing both fields"}
     if cpu:
         from oracle import dense as odense
         from oracle import nearfield as onf

@@ -388,7 +388,8 @@ dda_status dda_ctx_set_timing_sample(dda_ctx* ctx, int every);
  * right-hand-side count and precision: variants[0] forward y pass,
  * variants[1] z pass with the tensor product, variants[2] inverse y pass
  * (each the value opts->kernel_variant - 1 would force).  All three are -1
- * when no solve with these parameters has been tuned yet.
+ * when no solve with these parameters has been tuned yet, and 0 where one
+ * kernel takes the three passes in LDS (there is nothing to choose).
  * E_INVALID for NULL arguments, n_rhs < 1 or an unknown precision. */
 dda_status dda_ctx_tuned_variants(dda_ctx* ctx, const dda_target* t, int32_t n_rhs, dda_precision precision,
                                   int32_t variants[3]);

@@ -417,7 +417,8 @@ def mueller(f1, f2, e01, e02, phi_deg) -> np.ndarray:
 def tuned_variants(target: "Target", n_rhs: int, precision: str = "fp64") -> tuple:
     """(y forward, z with tensor, y inverse) strided-pass variants the
     autotuner chose for this target, right-hand-side count and precision, or
-    (-1, -1, -1) before any such solve."""
+    (-1, -1, -1) before any such solve; (0, 0, 0) where one kernel takes the
+    three passes."""
     out = (ctypes.c_int32 * 3)()
     _check(_lib.dda_ctx_tuned_variants(target.ctx, target._h, int(n_rhs), _PREC[precision], out),
            "dda_ctx_tuned_variants")
