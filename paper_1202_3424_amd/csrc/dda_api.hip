@@ -442,6 +442,7 @@ struct Work {
     bool fp32;
     bool qmr = false;   // QMR for complex-symmetric A instead of BiCGSTAB
     bool b2 = false;    // BiCGstab(2) instead of BiCGSTAB
+    const AlphaArgs* alpha = nullptr;  // 1/alpha formed in the scatter's launch (plain product)
     const SiteArgs* from = nullptr;   // what the scatter reads, where not a (near field)
     bool graphs = false; // replay captured iteration chunks (batched solves, unless DDA_FLAG_NO_GRAPH)
     SiteArgs a{};
@@ -576,14 +577,29 @@ struct Work {
                          out + (size_t)sg.first * t->nmat * 3, s, t->nmat);
     }
 
+    // 1/alpha with the incidences as kernel arguments, for a few right-hand
+    // sides of one target
+    bool alpha_args(const double* khv, const double2* e0v, const dda_opts* o, AlphaArgs& al) const {
+        if (!segs.empty() || nrhs > INC_ARGS) return false;
+        al = AlphaArgs{};
+        al.n = nrhs * t->nmat;
+        al.nmat = t->nmat;
+        al.scheme = o->polarizability;
+        al.m_medium = o->m_medium;
+        al.kd = kd;
+        al.mats = (const double2*)t->mdev.p;
+        al.out = (double2*)a.ainv;
+        std::copy(khv, khv + 3 * nrhs, al.khat);
+        std::copy(e0v, e0v + 3 * nrhs, al.e0);
+        return true;
+    }
     // The incidences to the device and 1/alpha from them: for a few right-hand
-    // sides in one launch that carries them as arguments.  Two copies and
-    // the launch cost a product of a small target 3.5 us of copies and the
-    // gaps between them (389 sites: 26.6 us so and 22.3 in one).
+    // sides in one launch.  Two copies and the launch cost a product of a
+    // small target 3.5 us of copies and the gaps between them.
     void incidence(const double* khv, const double2* e0v, const dda_opts* o) {
-        if (segs.empty() && nrhs <= INC_ARGS) {
-            launch_alpha_inc(nrhs, t->nmat, (const double2*)t->mdev.p, o->m_medium, khv, e0v, kd, o->polarizability,
-                             (double2*)a.ainv, kh, e0, s);
+        AlphaArgs al;
+        if (alpha_args(khv, e0v, o, al)) {
+            launch_alpha_inc(al, kh, e0, s);
             return;
         }
         upload_incidence(khv, e0v);
@@ -716,7 +732,7 @@ struct Work {
         const double2* tw = (const double2*)t->tw.p;
         {
             Timed tm(c, T_SCATTER, s);
-            launch_scatter_x<T>(sc, chk_sc, g, from ? *from : a, gr, tw, s);
+            launch_scatter_x<T>(sc, chk_sc, g, from ? *from : a, gr, tw, s, alpha);
         }
         if (sizeof(T) == 4 ? plane32 : plane64) {
             Timed tm(c, T_FFTZ_G, s);
@@ -1736,7 +1752,10 @@ dda_target* nf_target(dda_ctx* c, dda_target* t, const int e[6], const int org[3
 // y = A x for the caller's vectors.  The x passes take them in caller order
 // themselves; where x and y overlap in part, through sorted copies in the
 // work vectors (a site's output could overwrite another's input).
-void plain_product(Work& w, const dda_c64* x, dda_c64* y) {
+void plain_product(Work& w, const double* khv, const double2* e0v, const dda_opts* o, const dda_c64* x, dda_c64* y) {
+    AlphaArgs al;
+    if (w.alpha_args(khv, e0v, o, al)) w.alpha = &al;
+    else w.incidence(khv, e0v, o);
     const size_t n = (size_t)w.nrhs * w.a.n3;
     const int* perm = (const int*)w.t->perm.p;
     const bool apart = x + n <= y || y + n <= x;
@@ -1750,6 +1769,7 @@ void plain_product(Work& w, const dda_c64* x, dda_c64* y) {
         w.a.out = w.a.v;
     }
     w.matvec(SC_PLAIN, GA_PLAIN, CHK_NONE, CHK_NONE);
+    w.alpha = nullptr;
     if (!apart) launch_permute(w.nrhs, w.t->nsites, 3, perm, w.a.v, (double2*)y, false, w.s);
     HIPCHK(hipGetLastError());
 }
@@ -1857,8 +1877,7 @@ dda_status dda_apply(dda_ctx* c, dda_target* t, const dda_opts* o, int32_t n_rhs
         w.b2 = o->solver == DDA_BICGSTAB2;
         w.graphs = false;   // one stream: replays are slower than launches
         w.autotune((o->flags & DDA_FLAG_NO_AUTOTUNE) == 0, o->kernel_variant);
-        w.incidence(kh.data(), e0.data(), o);
-        plain_product(w, x, y);
+        plain_product(w, kh.data(), e0.data(), o, x, y);
         return DDA_OK;
     });
 }
@@ -1894,8 +1913,7 @@ dda_status dda_apply_noalloc(dda_ctx* c, dda_target* t, const dda_opts* o, int32
         } ne(c);
         Work w(c, c->main, t, n_rhs, kd, fp32, base, L);
         w.autotune(false, o->kernel_variant);   // the tiling tuned for this shape, else the default
-        w.incidence(khv, e0v, o);
-        plain_product(w, x, y);
+        plain_product(w, khv, e0v, o, x, y);
         return DDA_OK;
     });
 }

@@ -106,6 +106,62 @@ struct SiteArgs {
     const RhsGeo* rg;
 };
 
+// 1/alpha (or its derivative with respect to eps, scheme + 2) per
+// (right-hand side, material): "Dipole Polarizabilities".
+//   LATTDR (Draine & Goodman 1993): 1/alpha = 1/alpha_CM
+//       + (b1 + eps b2 + eps b3 S) (kd)^2 - (2/3) i (kd)^3,
+//       S = sum_mu khat_mu^2 |e_mu|^2, 1/alpha_CM = (4 pi/3)(eps+2)/(eps-1).
+//   GKDLDR (Gutkowicz-Krusin & Draine 2004): S -> khat_mu^2 on axis mu.
+__device__ __forceinline__ void alpha_point(int q, int mt, const double2* mats, double m_medium, const double* kh,
+                                            const double2* e, double kd, int scheme, double2* out, int ostride) {
+    const double b1 = -1.891531, b2 = 0.1648469, b3 = -1.7700004;
+    const double pi = 3.14159265358979323846;
+    // refractive index relative to the ambient medium
+    const double2 m = {mats[mt].x / m_medium, mats[mt].y / m_medium};
+    const double2 eps = cmul(m, m);
+    double S = 0.0;
+    for (int mu = 0; mu < 3; ++mu) S += kh[mu] * kh[mu] * (e[mu].x * e[mu].x + e[mu].y * e[mu].y);
+    const double k2 = kd * kd;
+    const double2 em1 = {eps.x - 1.0, eps.y};
+    const bool deriv = scheme >= 2;
+    const int sch = scheme & 1;
+    for (int mu = 0; mu < 3; ++mu) {
+        const double Smu = sch ? kh[mu] * kh[mu] : S;
+        double2 v;
+        if (!deriv) {
+            const double2 cm = cscale(cdiv(double2{eps.x + 2.0, eps.y}, em1), 4.0 * pi / 3.0);
+            const double2 ldr = cscale(cadd(double2{b1, 0.0}, cscale(eps, b2 + b3 * Smu)), k2);
+            v = cadd(cm, ldr);
+            v.y -= (2.0 / 3.0) * k2 * kd;
+        } else {
+            // d/deps: -4 pi/(eps-1)^2 + (b2 + b3 S) k^2
+            const double2 d = cdiv(double2{-4.0 * pi, 0.0}, cmul(em1, em1));
+            v = cadd(d, double2{(b2 + b3 * Smu) * k2, 0.0});
+        }
+        out[((long long)q * ostride + mt) * 3 + mu] = v;
+    }
+}
+
+// 1/alpha of a few right-hand sides with their incidences as kernel
+// arguments: entry i < n is (right-hand side i / nmat, material i % nmat).
+constexpr int INC_ARGS = 8;
+struct AlphaArgs {
+    int n;
+    int nmat;
+    int scheme;
+    double m_medium;
+    double kd;
+    const double2* mats;
+    double2* out;
+    double khat[INC_ARGS * 3];
+    double2 e0[INC_ARGS * 3];
+};
+__device__ __forceinline__ void alpha_entry(const AlphaArgs& al, int i) {
+    const int q = i / al.nmat;
+    alpha_point(q, i % al.nmat, al.mats, al.m_medium, al.khat + q * 3, al.e0 + q * 3, al.kd, al.scheme, al.out,
+                al.nmat);
+}
+
 // Sites of right-hand side q, its kd, and where its target's sites start in
 // the map / material / coordinate arrays.
 __device__ __forceinline__ long long rhs_n3(const SiteArgs& a, int q) { return a.rg ? 3LL * a.rg[q].nsites : a.n3; }
@@ -165,7 +221,7 @@ int site_blocks_for(long long n3, int nrhs);
 
 template <typename T>
 void launch_scatter_x(int mode, int chk, const Geo& g, const SiteArgs& a, typename V2<T>::t* grid, const double2* tw,
-                      hipStream_t s);
+                      hipStream_t s, const AlphaArgs* alpha = nullptr);
 template <typename T>
 void launch_gather_x(int mode, int chk, const Geo& g, const SiteArgs& a, const typename V2<T>::t* grid,
                      const double2* tw, hipStream_t s);
@@ -223,11 +279,8 @@ void launch_green(const Geo& g, double kd, double2* work, double2* gh64, float2*
 // 1/alpha (scheme + 2: its derivative in eps) per (right-hand side, material)
 // from the target's distinct refractive indices mats [nmat] and the ambient
 // medium's index
-// (of at most INC_ARGS right-hand sides: the incidences khat and e0 are host
-// arrays, which travel as kernel arguments and are stored to the device too)
-constexpr int INC_ARGS = 8;
-void launch_alpha_inc(int nrhs, int nmat, const double2* mats, double m_medium, const double* khat, const double2* e0,
-                      double kd, int scheme, double2* ainv, double* khat_dev, double2* e0_dev, hipStream_t s);
+// (the incidences travel as kernel arguments and are stored to the device too)
+void launch_alpha_inc(const AlphaArgs& al, double* khat_dev, double2* e0_dev, hipStream_t s);
 void launch_alpha(int nrhs, int nmat, const double2* mats, double m_medium, const double* khat, const double2* e0,
                   double kd, int scheme, double2* ainv, hipStream_t s, int ostride = 0);
 void launch_einc(const SiteArgs& a, const int* coords, const double* khat, const double2* e0, hipStream_t s);

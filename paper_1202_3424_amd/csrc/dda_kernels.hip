@@ -26,42 +26,6 @@ __device__ __forceinline__ bool finite2(double2 a) { return isfinite(a.x) && isf
 
 // ------------------------------------------------------------------ setup
 
-// 1/alpha (or its derivative with respect to eps, scheme + 2) per
-// (right-hand side, material): "Dipole Polarizabilities".
-//   LATTDR (Draine & Goodman 1993): 1/alpha = 1/alpha_CM
-//       + (b1 + eps b2 + eps b3 S) (kd)^2 - (2/3) i (kd)^3,
-//       S = sum_mu khat_mu^2 |e_mu|^2, 1/alpha_CM = (4 pi/3)(eps+2)/(eps-1).
-//   GKDLDR (Gutkowicz-Krusin & Draine 2004): S -> khat_mu^2 on axis mu.
-__device__ __forceinline__ void alpha_point(int q, int mt, const double2* mats, double m_medium, const double* kh,
-                                            const double2* e, double kd, int scheme, double2* out, int ostride) {
-    const double b1 = -1.891531, b2 = 0.1648469, b3 = -1.7700004;
-    const double pi = 3.14159265358979323846;
-    // refractive index relative to the ambient medium
-    const double2 m = {mats[mt].x / m_medium, mats[mt].y / m_medium};
-    const double2 eps = cmul(m, m);
-    double S = 0.0;
-    for (int mu = 0; mu < 3; ++mu) S += kh[mu] * kh[mu] * (e[mu].x * e[mu].x + e[mu].y * e[mu].y);
-    const double k2 = kd * kd;
-    const double2 em1 = {eps.x - 1.0, eps.y};
-    const bool deriv = scheme >= 2;
-    const int sch = scheme & 1;
-    for (int mu = 0; mu < 3; ++mu) {
-        const double Smu = sch ? kh[mu] * kh[mu] : S;
-        double2 v;
-        if (!deriv) {
-            const double2 cm = cscale(cdiv(double2{eps.x + 2.0, eps.y}, em1), 4.0 * pi / 3.0);
-            const double2 ldr = cscale(cadd(double2{b1, 0.0}, cscale(eps, b2 + b3 * Smu)), k2);
-            v = cadd(cm, ldr);
-            v.y -= (2.0 / 3.0) * k2 * kd;
-        } else {
-            // d/deps: -4 pi/(eps-1)^2 + (b2 + b3 S) k^2
-            const double2 d = cdiv(double2{-4.0 * pi, 0.0}, cmul(em1, em1));
-            v = cadd(d, double2{(b2 + b3 * Smu) * k2, 0.0});
-        }
-        out[((long long)q * ostride + mt) * 3 + mu] = v;
-    }
-}
-
 __global__ void k_alpha(int nrhs, int nmat, const double2* mats, double m_medium, const double* khat,
                         const double2* e0, double kd, int scheme, double2* out, int ostride) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -69,22 +33,17 @@ __global__ void k_alpha(int nrhs, int nmat, const double2* mats, double m_medium
     const int q = i / nmat;
     alpha_point(q, i % nmat, mats, m_medium, khat + q * 3, e0 + q * 3, kd, scheme, out, ostride);
 }
-struct IncArgs {
-    double khat[INC_ARGS * 3];
-    double2 e0[INC_ARGS * 3];
-};
-__global__ void k_alpha_inc(int nrhs, int nmat, const double2* mats, double m_medium, const IncArgs inc, double kd,
-                            int scheme, double2* out, double* khat, double2* e0) {
+__global__ void k_alpha_inc(const AlphaArgs al, double* khat, double2* e0) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nrhs * nmat) return;
-    const int q = i / nmat;
-    if (i % nmat == 0) {
+    if (i >= al.n) return;
+    const int q = i / al.nmat;
+    if (i % al.nmat == 0) {
         for (int c = 0; c < 3; ++c) {
-            khat[q * 3 + c] = inc.khat[q * 3 + c];
-            e0[q * 3 + c] = inc.e0[q * 3 + c];
+            khat[q * 3 + c] = al.khat[q * 3 + c];
+            e0[q * 3 + c] = al.e0[q * 3 + c];
         }
     }
-    alpha_point(q, i % nmat, mats, m_medium, inc.khat + q * 3, inc.e0 + q * 3, kd, scheme, out, nmat);
+    alpha_entry(al, i);
 }
 
 // E_inc at every site: e exp(i kd khat . r), "Incident Polarization State".
@@ -912,15 +871,8 @@ void launch_alpha(int nrhs, int nmat, const double2* mats, double m_medium, cons
                        ainv, ostride > 0 ? ostride : nmat);
 }
 
-void launch_alpha_inc(int nrhs, int nmat, const double2* mats, double m_medium, const double* khat, const double2* e0,
-                      double kd, int scheme, double2* ainv, double* khat_dev, double2* e0_dev, hipStream_t s) {
-    if (nrhs > INC_ARGS) throw std::invalid_argument("too many incidences for the arguments");
-    IncArgs inc{};
-    std::copy(khat, khat + 3 * nrhs, inc.khat);
-    std::copy(e0, e0 + 3 * nrhs, inc.e0);
-    const int n = nrhs * nmat;
-    hipLaunchKernelGGL(k_alpha_inc, dim3((n + 63) / 64), dim3(64), 0, s, nrhs, nmat, mats, m_medium, inc, kd, scheme,
-                       ainv, khat_dev, e0_dev);
+void launch_alpha_inc(const AlphaArgs& al, double* khat_dev, double2* e0_dev, hipStream_t s) {
+    hipLaunchKernelGGL(k_alpha_inc, dim3((al.n + 63) / 64), dim3(64), 0, s, al, khat_dev, e0_dev);
 }
 
 void launch_einc(const SiteArgs& a, const int* coords, const double* khat, const double2* e0, hipStream_t s) {

@@ -15,13 +15,24 @@ constexpr int xthr(int L) { return L > 128 ? 128 : 64; }
 
 // ------------------------------------------------------------------ pass 1
 
-template <typename T, int MODE, int LC, int NTHR>
+// AL: the plain product's launch also forms the 1/alpha that its gather
+// reads, in a layer of workgroups of its own behind the right-hand sides',
+// instead of a launch before it (389 sites: 22.3 us a product so, 19.4 here).
+struct NoAlpha {};
+template <typename T, int MODE, int LC, int NTHR, typename AL = NoAlpha>
 __global__ __launch_bounds__(NTHR) void k_scatter_x(Geo g, SiteArgs a, typename V2<T>::t* grid, const double2* tw64,
-                                                   int XLrt, int chk) {
+                                                   int XLrt, int chk, const AL al) {
     using C = typename V2<T>::t;
     constexpr bool CT = LC > 0;
     extern __shared__ __align__(16) unsigned char smem[];
     const int q = blockIdx.z;
+    if constexpr (!std::is_same_v<AL, NoAlpha>) {
+        if (q == a.nrhs) {
+            const int b = blockIdx.y * gridDim.x + blockIdx.x;
+            for (int i = b * NTHR + threadIdx.x; i < al.n; i += gridDim.x * gridDim.y * NTHR) alpha_entry(al, i);
+            return;
+        }
+    }
     const RhsState* st = a.st + q;
     if constexpr (!CT) {
         if (skip_rhs(st, chk)) return;
@@ -530,24 +541,24 @@ __global__ __launch_bounds__(NTHR) void k_gather_x(Geo g, SiteArgs a, const type
 
 // ------------------------------------------------------------------ launchers
 
-template <typename T, int MODE>
+template <typename T, int MODE, typename AL = NoAlpha>
 void scatter_dispatch(int chk, const Geo& g, const SiteArgs& a, typename V2<T>::t* grid, const double2* tw,
-                      hipStream_t s) {
+                      hipStream_t s, const AL& al = AL()) {
     using C = typename V2<T>::t;
     const int L = g.M[0];
     const int XL = x_lines_per_tile(g, a.nrhs, sizeof(T) == 4);
-    dim3 grd((g.i1[1] - g.i0[1] + XL - 1) / XL, g.i1[2] - g.i0[2], a.nrhs);
+    dim3 grd((g.i1[1] - g.i0[1] + XL - 1) / XL, g.i1[2] - g.i0[2], a.nrhs + (std::is_same_v<AL, NoAlpha> ? 0 : 1));
     switch (L) {
 #define DDA_CASE(LL)                                                                                            \
     case LL:                                                                                                   \
-        DDA_LAUNCH((k_scatter_x<T, MODE, LL, xthr(LL)>), grd, dim3(xthr(LL)), smem_ct<C>(LL, 3), s, g, a, grid, \
-                           tw, 1, chk);                                                                        \
+        DDA_LAUNCH((k_scatter_x<T, MODE, LL, xthr(LL), AL>), grd, dim3(xthr(LL)), smem_ct<C>(LL, 3), s, g, a, grid, \
+                           tw, 1, chk, al);                                                                        \
         return;
         DDA_CT_LENGTHS(DDA_CASE)
 #undef DDA_CASE
         default:
-            DDA_LAUNCH((k_scatter_x<T, MODE, 0, NT>), grd, dim3(NT), smem_rt<C>(L, 3 * XL), s, g, a, grid,
-                               tw, XL, chk);
+            DDA_LAUNCH((k_scatter_x<T, MODE, 0, NT, AL>), grd, dim3(NT), smem_rt<C>(L, 3 * XL), s, g, a, grid,
+                               tw, XL, chk, al);
     }
 }
 
@@ -587,10 +598,13 @@ void gather_dispatch(int chk, const Geo& g, const SiteArgs& a, const typename V2
 
 template <typename T>
 void launch_scatter_x(int mode, int chk, const Geo& g, const SiteArgs& a, typename V2<T>::t* grid, const double2* tw,
-                      hipStream_t s) {
+                      hipStream_t s, const AlphaArgs* alpha) {
     using namespace passes;
     switch (mode) {
-        case SC_PLAIN: scatter_dispatch<T, SC_PLAIN>(chk, g, a, grid, tw, s); break;
+        case SC_PLAIN:
+            if (alpha) scatter_dispatch<T, SC_PLAIN, AlphaArgs>(chk, g, a, grid, tw, s, *alpha);
+            else scatter_dispatch<T, SC_PLAIN>(chk, g, a, grid, tw, s);
+            break;
         case SC_CONJ: scatter_dispatch<T, SC_CONJ>(chk, g, a, grid, tw, s); break;
         case SC_P: scatter_dispatch<T, SC_P>(chk, g, a, grid, tw, s); break;
         case SC_Q: scatter_dispatch<T, SC_Q>(chk, g, a, grid, tw, s); break;
@@ -622,7 +636,7 @@ void launch_gather_x(int mode, int chk, const Geo& g, const SiteArgs& a, const t
 
 #define DDA_INSTANTIATE_XPASSES(T)                                                                                \
     template void launch_scatter_x<T>(int, int, const Geo&, const SiteArgs&, V2<T>::t*, const double2*,           \
-                                      hipStream_t);                                                              \
+                                      hipStream_t, const AlphaArgs*);                                            \
     template void launch_gather_x<T>(int, int, const Geo&, const SiteArgs&, const V2<T>::t*, const double2*,      \
                                      hipStream_t);
 

@@ -1581,12 +1581,14 @@ def test_plane_kernel_order_of_workgroups(dda, nx):
             assert torch.equal(y, ref), (q, precision)
 
 
+@pytest.mark.parametrize("radius", [4.5, 9.5])
 @pytest.mark.parametrize("materials", [1, 3])
-def test_incidences_as_arguments_equal_copied_ones(dda, materials):
+def test_incidences_as_arguments_equal_copied_ones(dda, materials, radius):
     """Up to eight incidences travel as kernel arguments, more are copied to
     the device: a nine-right-hand-side product and solve, every incidence its
-    own, are bitwise the eight and the one they consist of."""
-    ijk = w.sphere_integer(4.5)
+    own, are bitwise the eight and the one they consist of (runtime-planned and
+    compile-time x lengths)."""
+    ijk = w.sphere_integer(radius)
     n = len(ijk)
     m = np.array([1.33 + 0.01j, 1.5 + 0.2j, 1.1 + 0.3j])[np.arange(n) % materials]
     tgt = dda.Target(ijk, m)
