@@ -1627,3 +1627,69 @@ def test_apply_with_overlapping_vectors(dda):
     assert st == 0
     torch.cuda.synchronize()
     assert torch.equal(buf[1:], ref)
+
+
+# ------------------------------------------------------------------ several materials, many right-hand sides
+
+def _three_materials(n):
+    return np.array([1.33 + 0.01j, 1.6 + 0.2j, 2.0 + 0.5j])[np.arange(n) * 7 % 5 % 3]
+
+
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32_matvec", 2e-5)])
+@pytest.mark.parametrize("box", [(12, 3, 4), (40, 2, 3), (3, 9, 5)])
+def test_products_of_many_right_hand_sides_read_each_sites_material(dda, box, precision, tol):
+    """A launch of more than 16 right-hand sides gathers its operands after
+    the inverse x transform: with three materials, 24 right-hand sides equal
+    the dense matrix's products (and, bitwise, launches of 8 and 16), at
+    compile-time (32, 80) and runtime-planned (6) x lengths."""
+    ijk = w.brick(*box)
+    n = len(ijk)
+    m = _three_materials(n)
+    tgt = dda.Target(ijk, m)
+    kh, e0 = w.incidences_for_orientations(61, 12)
+    opts = dda.Options.for_size_parameter(1.1, precision=precision)
+    xv = w.random_vectors(61, (24, n, 3))
+    y = dda.apply(tgt, opts, kh, e0, _cuda(xv))
+    for a, b in ((0, 8), (8, 24)):
+        assert torch.equal(dda.apply(tgt, opts, kh[a:b], e0[a:b], _cuda(xv[a:b])), y[a:b])
+    for q in (0, 9, 23):
+        ref = (_dense_A(ijk, m, 1.1, kh[q], e0[q], "LATTDR") @ xv[q].reshape(-1)).reshape(n, 3)
+        assert np.abs(y[q].cpu().numpy() - ref).max() <= tol * np.abs(ref).max(), q
+
+
+@pytest.mark.parametrize("solver", ["bicgstab", "qmr", "bicgstab2"])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_matvec"])
+def test_solves_of_many_right_hand_sides_read_each_sites_material(dda, solver, precision):
+    """Twenty right-hand sides on a target of three materials: every P and
+    result is bitwise that of solves of ten, P agrees with the dense
+    solution (the residual's tolerance over the smallest singular value), and a batch whose
+    launches hold twenty right-hand sides of two such targets equals the
+    separate solves."""
+    ijks = []
+    for seed, box in ((63, (12, 11, 13)), (64, (16, 14, 11))):   # both on the 32^3 grid: they share launches
+        keep = np.random.default_rng(seed).random(box) < 0.05
+        keep[0, 0, 0] = keep[-1, -1, -1] = True
+        ijks.append(np.argwhere(keep).astype(np.int32))
+    ms = [_three_materials(len(i)) for i in ijks]
+    ts = [dda.Target(i, m) for i, m in zip(ijks, ms)]
+    opts = dda.Options.for_size_parameter(1.1, tol=1e-9, solver=solver, precision=precision)
+    kh, e0 = w.incidences_for_orientations(62, 10)
+    P, r = dda.solve(ts[0], opts, kh, e0)
+    for a, b in ((0, 10), (10, 20)):
+        Ps, rs = dda.solve(ts[0], opts, kh[a:b], e0[a:b])
+        assert torch.equal(Ps, P[a:b]) and rs == r[a:b]
+    k = dense.kd_from_size_parameter(1.1, len(ijks[0]))
+    for q in (0, 13):
+        A = _dense_A(ijks[0], ms[0], 1.1, kh[q], e0[q], "LATTDR")
+        E = dense.incident_field(ijks[0], k, kh[q], e0[q]).reshape(-1)
+        ref = np.linalg.solve(A, E)
+        err = np.linalg.norm(P[q].cpu().numpy().reshape(-1) - ref)
+        assert r[q]["status"] == 0
+        assert err <= 1.001e-9 * np.linalg.norm(E) / np.linalg.svd(A, compute_uv=False)[-1]
+    rt = np.arange(20) % 2
+    Pb, rb = dda.solve_batched(ts, [opts, opts], rt, kh, e0)
+    for i, t in enumerate(ts):
+        qs = np.flatnonzero(rt == i)
+        Pi, ri = dda.solve(t, opts, kh[qs], e0[qs])
+        for j, q in enumerate(qs):
+            assert torch.equal(Pb[q], Pi[j]) and rb[q] == ri[j]
