@@ -62,25 +62,33 @@ template <typename T> constexpr bool plane_pair(int LY, int LZ) {
 }
 
 // Wavefronts per workgroup: one per group of z columns a wavefront takes at
-// once, at most eight (two per SIMD at the registers the z stage holds).
-// Measured exceptions, both sides in us per launch on this card: FP64 48 x
-// 32, whose 39 KB let four workgroups share a compute unit, two (308 against
-// 346 with three, 128 right-hand sides); FP32 96 x 64 and 96 x 128, twelve at
-// three per SIMD (25.1 against 26.0 and 44.6 against 49.2 with eight, two
-// right-hand sides); FP32 with LZ = 80, eight for the y lines (181 against
-// 193 with five, 80 x 80, twenty right-hand sides).
-template <typename T> constexpr int plane_waves(int LY, int LZ) {
+// once, at most eight (two per SIMD at the registers the z stage holds), with
+// three measured exceptions, which depend on whether the launch has more
+// workgroups than compute units (many) or each has one to itself:
+//   FP64 48 x 32, whose 39 KB let four workgroups share a compute unit, two
+//   if many (128 right-hand sides: 308 us against 346 with three; with two
+//   right-hand sides a product takes a tenth longer with two);
+//   FP32 96 x 64 and 96 x 128, twelve at three per SIMD (two right-hand sides:
+//   25.1 us against 26.0 and 44.6 against 49.2 with eight);
+//   FP32 with LZ = 80, eight for the y lines (80 x 80, twenty right-hand sides:
+//   181 us against 193 with five), but with LY = 32 and 48 only if not many:
+//   256 workgroups 19 us against 22 with two and 23 against 30 with three,
+//   12,288 workgroups of 32 x 80 733 against 327 (537 as three passes).
+template <typename T> constexpr int plane_waves(int LY, int LZ, bool many) {
     const int nz = LY * (LZ / ct_split(LZ)) / 64;   // groups of z columns
-    if (sizeof(T) == 8) return (LZ == 32 && nz == 3) ? 2 : (nz < 8 ? nz : 8);
+    if (sizeof(T) == 8) return (many && LZ == 32 && nz == 3) ? 2 : (nz < 8 ? nz : 8);
     if (nz == 12) return 12;
-    if (LZ == 80) return 8;
+    if (LZ == 80 && (LY >= 64 || !many)) return 8;
     return nz < 8 ? nz : 8;
 }
-// wavefronts per SIMD asked of the compiler: three where it needs no
-// spilling for them (FP32, at most 72 VGPRs of data)
-template <typename T> constexpr int plane_occ(int LY, int LZ) {
-    return sizeof(T) == 4 && (plane_waves<T>(LY, LZ) == 12 || (plane_waves<T>(LY, LZ) <= 4 && z_vgprs<T>(LZ) <= 72)) ? 3 : 2;
+// wavefronts per SIMD asked of the compiler: three where that needs no
+// spilling (FP32, at most 72 VGPRs of data) and whole workgroups of at most
+// six wavefronts fill them (96 x 32, 3,072 workgroups: 155 us at two, 131 at
+// three)
+template <typename T> constexpr int plane_occ(int LZ, int waves) {
+    return sizeof(T) == 4 && (waves == 12 || (waves <= 6 && z_vgprs<T>(LZ) <= 72)) ? 3 : 2;
 }
+constexpr int PLANE_ALONE = 256;   // compute units
 
 // Orders the LDS accesses of one wavefront for the compiler (the hardware
 // executes them in order).
@@ -574,14 +582,22 @@ __global__ __launch_bounds__(SHORT_NT) void k_plane_rt(Geo g, ShortPlan py, Shor
 
 // ------------------------------------------------------------------ launcher
 
+template <typename T, int LY, int LZ, int NW>
+void plane_launch_waves(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, const double2* tw,
+                        const typename V2<T>::t* gp, const RhsState* st, hipStream_t s) {
+    const int ZS = z_stride(LZ, g.n[2]), CS = c_stride(LY, ZS, sizeof(T) == 4);
+    DDA_LAUNCH((k_plane<T, LY, LZ, 64 * NW, plane_occ<T>(LZ, NW)>), dim3(plane_grid(g.M[0], nrhs)), dim3(64 * NW),
+               plane_bytes(LY, LZ, g.n[2], sizeof(T) == 4), s, g, grid, tw, gp, st, chk, nrhs, ZS, CS);
+}
+
 template <typename T, int LY, int LZ>
 bool plane_launch(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, const double2* tw,
                   const typename V2<T>::t* gp, const RhsState* st, hipStream_t s) {
     if constexpr (plane_pair<T>(LY, LZ)) {
-        constexpr int NTHR = 64 * plane_waves<T>(LY, LZ);
-        const int ZS = z_stride(LZ, g.n[2]), CS = c_stride(LY, ZS, sizeof(T) == 4);
-        DDA_LAUNCH((k_plane<T, LY, LZ, NTHR, plane_occ<T>(LY, LZ)>), dim3(plane_grid(g.M[0], nrhs)), dim3(NTHR),
-                   plane_bytes(LY, LZ, g.n[2], sizeof(T) == 4), s, g, grid, tw, gp, st, chk, nrhs, ZS, CS);
+        if ((long long)g.M[0] * nrhs > PLANE_ALONE)
+            plane_launch_waves<T, LY, LZ, plane_waves<T>(LY, LZ, true)>(chk, g, nrhs, grid, tw, gp, st, s);
+        else
+            plane_launch_waves<T, LY, LZ, plane_waves<T>(LY, LZ, false)>(chk, g, nrhs, grid, tw, gp, st, s);
         return true;
     }
     return false;

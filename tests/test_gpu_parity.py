@@ -1693,3 +1693,28 @@ def test_solves_of_many_right_hand_sides_read_each_sites_material(dda, solver, p
         Pi, ri = dda.solve(t, opts, kh[qs], e0[qs])
         for j, q in enumerate(qs):
             assert torch.equal(Pb[q], Pi[j]) and rb[q] == ri[j]
+
+
+# ------------------------------------------------------------------ plane kernel: launch shapes
+
+@pytest.mark.parametrize("precision,ny,nz", [("fp64", 24, 16), ("fp32_matvec", 13, 33), ("fp32_matvec", 16, 40),
+                                             ("fp32_matvec", 24, 38), ("fp32_matvec", 48, 16)])
+@pytest.mark.parametrize("n_rhs", [4, 5])
+def test_plane_kernel_with_one_and_several_workgroups_a_compute_unit(dda, precision, ny, nz, n_rhs):
+    """Launches of 256 and of 320 workgroups (x extent 64), on each side of the
+    line where the plane kernel's wavefront count changes, at the lengths
+    where it does (FP64 48 x 32, FP32 32 x 80, 48 x 80) and at FP32 96 x 32:
+    bitwise the three separate passes."""
+    rng = np.random.default_rng(ny + nz)
+    keep = rng.random((30, ny, nz)) < 0.1
+    keep[0, 0, 0] = keep[-1, -1, -1] = True
+    ijk = np.argwhere(keep).astype(np.int32)
+    tgt = dda.Target(ijk, 1.4 + 0.1j)
+    assert tgt.grid[0] == 64
+    kh, e0 = np.tile([1.0, 0, 0], (n_rhs, 1)), np.tile(np.array([0, 1, 0], complex), (n_rhs, 1))
+    xv = _cuda(w.random_vectors(71, (n_rhs, len(ijk), 3)))
+    opts = dict(precision=precision)
+    y = dda.apply(tgt, dda.Options.for_size_parameter(1.0, **opts), kh, e0, xv)
+    assert dda.tuned_variants(tgt, n_rhs, precision) == (0, 0, 0)
+    ref = dda.apply(tgt, dda.Options.for_size_parameter(1.0, kernel_variant=4, **opts), kh, e0, xv)
+    assert torch.equal(y, ref)
