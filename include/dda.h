@@ -389,7 +389,8 @@ dda_status dda_ctx_set_timing_sample(dda_ctx* ctx, int every);
  * variants[1] z pass with the tensor product, variants[2] inverse y pass
  * (each the value opts->kernel_variant - 1 would force).  All three are -1
  * when no solve with these parameters has been tuned yet, and 0 where one
- * kernel takes the three passes in LDS (there is nothing to choose).
+ * kernel takes the three passes in LDS (there is nothing to choose; on grids
+ * that it takes only with more right-hand sides the variants are fixed).
  * E_INVALID for NULL arguments, n_rhs < 1 or an unknown precision. */
 dda_status dda_ctx_tuned_variants(dda_ctx* ctx, const dda_target* t, int32_t n_rhs, dda_precision precision,
                                   int32_t variants[3]);

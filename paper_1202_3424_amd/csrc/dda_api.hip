@@ -633,8 +633,9 @@ struct Work {
     // near-ties resolve the same way from run to run.
     void autotune(bool enabled, int forced = 0) {
         const Geo& g = t->geo;
-        plane64 = forced <= 0 && plane_fits<double>(g, nrhs);
-        plane32 = forced <= 0 && plane_fits<float>(g, nrhs);
+        const PlaneUse use64 = plane_use<double>(g, nrhs), use32 = plane_use<float>(g, nrhs);
+        plane64 = forced <= 0 && use64 == PLANE_YES;
+        plane32 = forced <= 0 && use32 == PLANE_YES;
         if (forced > 0) {
             for (int slot = 0; slot < 3; ++slot) {
                 const int nv = strided_variants(g.M[slot == 1 ? 2 : 1], slot == 1);
@@ -650,7 +651,9 @@ struct Work {
             return;
         }
         std::array<int, 3> best{0, 0, 0};
-        if (fp32 ? plane32 : plane64) {   // no pass to tune: one plane kernel takes all three
+        if ((fp32 ? use32 : use64) == PLANE_FEW)
+            for (int slot = 0; slot < 3; ++slot) best[slot] = few_variant(slot, fp32);
+        if ((fp32 ? use32 : use64) != PLANE_NO) {   // no pass to tune: one plane kernel takes all three, or fixed variants
             if (enabled) c->tuned[key] = best;
         } else if (enabled) {
             hipEvent_t e0 = take_event(c), e1 = take_event(c);
@@ -786,10 +789,10 @@ void ensure_green(dda_ctx* c, dda_target* t, double kd, bool fp32, bool force) {
     const size_t nh = (size_t)g.H[0] * g.H[1] * g.H[2] * 6;
     if (fresh) t->have64 = t->have32 = false;
     double2* work = (double2*)c->gtmp.ensure(green_work_values(g) * sizeof(double2));
-    // the plane kernel's layout, where it takes this grid (with any number of
-    // right-hand sides; launch limits are checked with the product)
-    const bool p64 = plane_fits<double>(g, 1) && !plane_short<double>(g);
-    const bool p32 = fp32 && plane_fits<float>(g, 1) && !plane_short<float>(g);
+    // the plane kernel's layout, where it can take this grid (whether it does
+    // depends on the right-hand sides of a product)
+    const bool p64 = plane_fits<double>(g) && !plane_short<double>(g);
+    const bool p32 = fp32 && plane_fits<float>(g) && !plane_short<float>(g);
     const size_t np = p64 || p32 ? plane_values(g) : 0, nhp = (nh + 15) & ~(size_t)15;   // (rows on cache lines)
     double2* g64 = (double2*)t->gh64.ensure((nhp + (p64 ? np : 0)) * sizeof(double2));
     float2* g32 = fp32 ? (float2*)t->gh32.ensure((nhp + (p32 ? np : 0)) * sizeof(float2)) : nullptr;

@@ -256,12 +256,21 @@ constexpr bool ragged_variant(int gh, int v) {
 // y and z extents have compiled lengths whose plane fits the LDS.  gp: the
 // tensor octant in that kernel's layout (launch_green_plane; a ragged batch
 // takes each right-hand side's from g.rg).  Bitwise the results of the three
-// launch_strided passes, and faster wherever it fits, so it needs no tuning:
-// 33 us against 48 for 128 x 96 x 64 with two right-hand sides in FP64.
+// launch_strided passes.  plane_use says where it runs, from a scan of every
+// pair of lengths over x extents of 2 to 96 and 1 to 128 right-hand sides: it
+// took 0.64 to 1.06 of the time of a product with three tuned passes from 80
+// workgroups on, and up to 1.39 of it below, in large planes with few
+// workgroups (one workgroup is a chain of all the plane's lines).  With at
+// most 32 of these the passes run instead, in fixed variants (few_variant, at
+// most a tenth slower than tuned ones, whose timing takes longer than such a
+// solve).
 template <typename T>
 void launch_plane(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, const double2* tw,
                   const typename V2<T>::t* gp, const RhsState* st, hipStream_t s);
-template <typename T> bool plane_fits(const Geo& g, int nrhs);
+template <typename T> bool plane_fits(const Geo& g);
+enum PlaneUse { PLANE_NO = 0, PLANE_FEW = 1, PLANE_YES = 2 };
+template <typename T> PlaneUse plane_use(const Geo& g, int nrhs);
+constexpr int few_variant(int slot, bool fp32) { return slot == 1 ? (fp32 ? 3 : 4) : 0; }
 // whether that is the short-length kernel, which reads the octant itself
 template <typename T> bool plane_short(const Geo& g);
 // stored ky of a tensor row in that layout: LY / 2 + 1 and padding up to a

@@ -90,6 +90,18 @@ template <typename T> constexpr int plane_occ(int LZ, int waves) {
 }
 constexpr int PLANE_ALONE = 256;   // compute units
 
+// Planes that few workgroups do not take (plane_use): at most PLANE_MIN of
+// them, an eighth of the compute units, and a chain per workgroup longer than
+// the launches it saves.  A product in a solve here and with the three passes,
+// us: FP64 4 workgroups of 128 x 48 50 and 39, of 96 x 64 49 and 38, 32 of 128
+// x 48 44 and 36; but 16 of 32 x 64 0.98 and 32 of 128 x 32 1.00 of the time.
+// FP32 4 of 128 x 96 74 and 56, 8 of 32 x 96 50 and 43, 32 of 128 x 96 61 and
+// 54; but 40 of 48 x 64 0.94.  With 64 the two are within a tenth.
+constexpr int PLANE_MIN = 32;
+template <typename T> constexpr bool plane_long(int LY, int LZ) {
+    return sizeof(T) == 8 ? LZ > 32 && LY * LZ > 3072 : LZ == 96 || LY * LZ >= 5120;
+}
+
 // Orders the LDS accesses of one wavefront for the compiler (the hardware
 // executes them in order).
 __device__ __forceinline__ void wave_fence() {
@@ -648,19 +660,25 @@ void launch_plane(int chk, const Geo& g, int nrhs, typename V2<T>::t* grid, cons
     if (!done) throw std::invalid_argument("no plane kernel for this grid");
 }
 
-// Whether launch_plane takes this grid: a compiled pair of lengths whose
-// plane, with the occupied z extent, fits the LDS, and a launch within the
-// grid limit.
-template <typename T> bool plane_fits(const Geo& g, int nrhs) {
-    if (plane_short<T>(g)) return nrhs <= 65535;
-    if (!plane::plane_pair<T>(g.M[1], g.M[2]) || 2 * g.n[1] > g.M[1] || 2 * g.n[2] > g.M[2]) return false;
-    return (long long)(g.M[0] + passes::N_XCD) * nrhs * 768 < (1LL << 32);
+// Whether launch_plane can take this grid: a compiled pair of lengths whose
+// plane, with the largest z extent such a grid holds, fits the LDS.
+template <typename T> bool plane_fits(const Geo& g) {
+    return plane_short<T>(g) ||
+           (plane::plane_pair<T>(g.M[1], g.M[2]) && 2 * g.n[1] <= g.M[1] && 2 * g.n[2] <= g.M[2]);
+}
+// Whether it does: a launch within the grid limit, and enough workgroups.
+template <typename T> PlaneUse plane_use(const Geo& g, int nrhs) {
+    if (!plane_fits<T>(g)) return PLANE_NO;
+    if (plane_short<T>(g)) return nrhs <= 65535 ? PLANE_YES : PLANE_NO;
+    if ((long long)(g.M[0] + passes::N_XCD) * nrhs * 768 >= (1LL << 32)) return PLANE_NO;
+    return (long long)g.M[0] * nrhs <= plane::PLANE_MIN && plane::plane_long<T>(g.M[1], g.M[2]) ? PLANE_FEW : PLANE_YES;
 }
 
 #define DDA_INSTANTIATE_PLANE(T)                                                                                \
     template void launch_plane<T>(int, const Geo&, int, V2<T>::t*, const double2*, const V2<T>::t*,              \
                                   const RhsState*, hipStream_t);                                                \
-    template bool plane_fits<T>(const Geo&, int);                                                               \
+    template bool plane_fits<T>(const Geo&);                                                                    \
+    template PlaneUse plane_use<T>(const Geo&, int);                                                            \
     template bool plane_short<T>(const Geo&);
 
 }  // namespace dda

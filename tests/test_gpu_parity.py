@@ -1718,3 +1718,28 @@ def test_plane_kernel_with_one_and_several_workgroups_a_compute_unit(dda, precis
     assert dda.tuned_variants(tgt, n_rhs, precision) == (0, 0, 0)
     ref = dda.apply(tgt, dda.Options.for_size_parameter(1.0, kernel_variant=4, **opts), kh, e0, xv)
     assert torch.equal(y, ref)
+
+
+@pytest.mark.parametrize("precision,box,n_rhs,plane", [
+    ("fp64", (2, 64, 24), 1, False), ("fp64", (16, 64, 24), 1, False), ("fp64", (24, 64, 24), 1, True),
+    ("fp64", (2, 64, 24), 8, False), ("fp64", (2, 64, 24), 9, True), ("fp64", (2, 64, 16), 1, True),
+    ("fp64", (2, 32, 32), 1, False), ("fp64", (2, 16, 32), 1, True), ("fp32_matvec", (2, 64, 48), 1, False),
+    ("fp32_matvec", (2, 16, 48), 8, False), ("fp32_matvec", (2, 16, 48), 9, True),
+    ("fp32_matvec", (2, 24, 40), 1, True), ("fp32_matvec", (2, 48, 24), 1, True)])
+def test_few_workgroups_of_long_planes_take_three_passes(dda, precision, box, n_rhs, plane):
+    """Grids of few workgroups (padded x extent times right-hand sides) whose
+    planes are long: passes 2-4 run as three kernels in fixed variants, at
+    most 32 workgroups; others take the plane kernel.  The products are
+    bitwise those of a named variant."""
+    rng = np.random.default_rng(sum(box))
+    keep = rng.random(box) < 0.1
+    keep[0, 0, 0] = keep[-1, -1, -1] = True
+    ijk = np.argwhere(keep).astype(np.int32)
+    tgt = dda.Target(ijk, 1.4 + 0.1j)
+    assert tgt.grid[0] == {2: 4, 16: 32, 24: 48}[box[0]]
+    kh, e0 = np.tile([1.0, 0, 0], (n_rhs, 1)), np.tile(np.array([0, 1, 0], complex), (n_rhs, 1))
+    xv = _cuda(w.random_vectors(72, (n_rhs, len(ijk), 3)))
+    y = dda.apply(tgt, dda.Options.for_size_parameter(1.0, precision=precision), kh, e0, xv)
+    assert dda.tuned_variants(tgt, n_rhs, precision) == (0, 0 if plane else 4 if precision == "fp64" else 3, 0)
+    ref = dda.apply(tgt, dda.Options.for_size_parameter(1.0, precision=precision, kernel_variant=4), kh, e0, xv)
+    assert torch.equal(y, ref)
