@@ -2078,13 +2078,13 @@ namespace {
 // Work memory and launches of the far field of nrhs solutions P (caller
 // order) over nd directions: one list for all (dstride 0) or a set for each
 // (dstride nd).
-size_t far_bytes(const dda_target* t, int nrhs, int nd) {
-    return far_lines(t->nsites, t->geo.n) ? far_lines_bytes(t->geo.n, nrhs, nd)
+size_t far_bytes(const dda_target* t, int nrhs, int nd, int dstride) {
+    return far_lines(t->nsites, t->geo.n, dstride) ? far_lines_bytes(t->geo.n, nrhs, nd)
                                           : (size_t)nrhs * 3 * t->nsites * sizeof(double2);
 }
 void far_launch(const dda_target* t, int nrhs, const dda_c64* P, const double* dirs, int nd, int dstride, double kd,
                 void* work, double2* f, double* dcs, hipStream_t s) {
-    if (far_lines(t->nsites, t->geo.n)) {
+    if (far_lines(t->nsites, t->geo.n, dstride)) {
         launch_far_lines((const int*)t->map.p, (const int*)t->perm.p, (const double2*)P, 3LL * t->nsites, nrhs, dirs,
                          nd, dstride, kd, t->lo, t->geo.n, work, f, dcs, s);
         return;
@@ -2128,7 +2128,7 @@ dda_status dda_far_field(dda_ctx* c, dda_target* t, const dda_opts* o, int32_t n
         }
         Scope sc(c);
         const double kd = kd_of(o, t->nsites);
-        const size_t pb = (far_bytes(t, n_rhs, n_dir) + 15) & ~(size_t)15, db = dirs.size() * sizeof(double);
+        const size_t pb = (far_bytes(t, n_rhs, n_dir, 0) + 15) & ~(size_t)15, db = dirs.size() * sizeof(double);
         const size_t fb = (size_t)n_rhs * n_dir * 2 * sizeof(double2), cb = (size_t)n_rhs * n_dir * sizeof(double);
         char* buf = (char*)c->ffbuf.ensure(pb + db + fb + cb + 256);
         double2* fdev = (double2*)(buf + pb);
@@ -2198,7 +2198,7 @@ dda_status dda_scattering_averages(dda_ctx* c, dda_target* t, const dda_opts* o,
         const int qg = std::max(1, std::min(n_rhs, (1 << 22) / nd));
         const long long ndt = (long long)nd * qg;
         const size_t n3 = 3 * (size_t)t->nsites;
-        const size_t pb = (far_bytes(t, qg, nd) + 15) & ~(size_t)15, db = (size_t)ndt * 9 * sizeof(double);
+        const size_t pb = (far_bytes(t, qg, nd, nd) + 15) & ~(size_t)15, db = (size_t)ndt * 9 * sizeof(double);
         const size_t fb = (size_t)ndt * 2 * sizeof(double2), cb = (size_t)ndt * sizeof(double);
         const size_t kb = (size_t)n_rhs * 3 * sizeof(double), mb = (size_t)n_theta * sizeof(double);
         char* buf = (char*)c->ffbuf.ensure(pb + db + fb + cb + kb + mb + 256);

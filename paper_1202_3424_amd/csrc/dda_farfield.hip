@@ -173,6 +173,9 @@ constexpr int FF_DIRS = 16;    // directions of a wavefront
 // planes of a workgroup: a constant, so that a sum's order depends on neither
 // the directions nor the right-hand sides of the call
 constexpr int FF_Z = 2;
+// wavefronts of three components up to which a launch takes one component a
+// wavefront instead
+constexpr int FF_SPLIT = 1024;
 
 // Phase factors of a tile of 16 directions: tab[q][tile] holds, in the order
 // the lanes of k_ff_lines read them, (cos, sin)(t h) of lane (direction
@@ -255,7 +258,11 @@ __global__ __launch_bounds__(NT) void k_ff_operands(const int* map, const int* p
 // [nd][9], per right-hand side dstride directions further on.  The matrix
 // instruction (16 x 16 x 4) takes A[direction lane & 15][k = lane >> 4] and
 // B[k][line lane & 15] and gives rows (lane >> 4) + 4 v of column lane & 15.
-// Wavefronts share nothing: each keeps its factors of x in its own LDS.
+// Wavefronts share nothing: each keeps its factors of x in its own LDS.  NC:
+// the components a wavefront takes, all three or one (blockIdx.y then counts
+// the components of each chunk); their sums are separate, so the results are
+// the same.
+template <int NC>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_ff_lines(const double2* fold, const int* kt, int nx, int ny, int nz, int KS,
                                                 const double2* tab, int nd, double* part) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -264,7 +271,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
     if (d0 >= nd) return;
     double2* cst = (double2*)smem + (size_t)wave * KS * 64;   // [KS][lane] (cos, sin) of t h
     const int q = blockIdx.z;
-    const int z0 = blockIdx.y * FF_Z, z1 = min(nz, z0 + FF_Z);
+    const int chunk = NC == 3 ? blockIdx.y : blockIdx.y / 3, c0 = NC == 3 ? 0 : blockIdx.y % 3;
+    const int nchunk = NC == 3 ? gridDim.y : gridDim.y / 3;
+    const int z0 = chunk * FF_Z, z1 = min(nz, z0 + FF_Z);
     const int nyb = (ny + FF_LINES - 1) / FF_LINES;
     tab += ((long long)q * ((nd + FF_DIRS - 1) / FF_DIRS) + d0 / FF_DIRS) * (KS * 64 + (ny + nz) * FF_DIRS);
     for (int ks = 0; ks < KS; ++ks) cst[ks * 64 + lane] = tab[ks * 64 + lane];
@@ -275,15 +284,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
     const int row = lane >> 4, col = lane & 15;
     const double2* fy = tab + KS * 64 + row;
     const double2* fz = fy + ny * FF_DIRS;
-    double2 tot[4][3];
+    double2 tot[4][NC];
 #pragma unroll
     for (int v = 0; v < 4; ++v)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) tot[v][c] = double2{0.0, 0.0};
+        for (int c = 0; c < NC; ++c) tot[v][c] = double2{0.0, 0.0};
     const int nkg = (KS + 3) / 4, nzc = z1 - z0, nt = nyb * nzc;
     // tile i of this wavefront: line block i / nzc of plane z0 + i % nzc
     auto tile_of = [&](int i) { return (z0 + i % nzc) * nyb + i / nzc; };
-    const double2* base = fold + (long long)q * nz * nyb * 3 * KS * 2 * 64 + lane;
+    const double2* base = fold + ((long long)q * nz * nyb * 3 + c0) * KS * 2 * 64 + lane;
     const long long tstride = 3LL * KS * 2 * 64;
     double2 b0 = base[tile_of(0) * tstride], b1 = base[tile_of(0) * tstride + 64];
     for (int i = 0; i < nt; ++i) {
@@ -301,9 +310,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
         // share a SIMD (all six at once, two wavefronts: 136 us against 129 for
         // the ellipsoid)
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
+        for (int c = 0; c < NC; ++c) {
             const double2* B = base + tile * tstride + c * KS * 128;
-            const double2* Bn = c < 2 ? B + KS * 128 : base + tile_of(min(i + 1, nt - 1)) * tstride;
+            const double2* Bn = c < NC - 1 ? B + KS * 128 : base + tile_of(min(i + 1, nt - 1)) * tstride;
             d4 T0 = {0.0, 0.0, 0.0, 0.0}, T1 = {0.0, 0.0, 0.0, 0.0};
             for (int ks = 0; ks < n; ++ks) {
                 const double2 a = cst[ks * 64 + lane];
@@ -329,9 +338,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int d = d0 + row + 4 * v;
-        double* o = part + (((long long)q * gridDim.y + blockIdx.y) * nd + d) * 6;
+        double* o = part + (((long long)q * nchunk + chunk) * nd + d) * 6 + 2 * c0;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
+        for (int c = 0; c < NC; ++c) {
 #pragma unroll
             for (int off = 8; off > 0; off >>= 1) {
                 tot[v][c].x += __shfl_xor(tot[v][c].x, off, 64);
@@ -413,15 +422,25 @@ void launch_farfield_sets(int nsites, const int* coords, const double2* P, int n
     }
 }
 
-// Which form (of the target alone, so that a sum does not depend on the
-// directions or right-hand sides of the call).  The line form's work grows
-// with the rounded box, the sum's with the sites: for 48^3 boxes, 2 x 3,072
-// directions, 297 against 453 us a call at two points a site, 297 against 265
-// at four.  At 4,096 sites (16^3) the two meet: 87 against 96 us for 3,072
-// directions, 59 against 56 for 74.
-bool far_lines(int nsites, const int n[3]) {
+// Which form.  A list of directions (nset 0): of the target alone, so that a
+// direction's sum does not depend on the others of the call; the sets of an
+// average, of nset directions each: of that count too (never of the right-hand
+// sides).  The line form's work grows with the rounded box, the sum's with the
+// sites: for 48^3 boxes, 2 x 3,072 directions, 297 against 453 us a call at two
+// points a site, 297 against 265 at four.  Below 8,192 sites it costs a few us
+// of launches and latency that only many directions win back.  One right-hand
+// side, us a call by lines and by the sum: 16^3, 74 directions 55 and 53, 3,072
+// 89 and 109; 48 x 10 x 10 58 and 54, 89 and 111; 21^3 60 % full 60 and 56, 102
+// and 118; 26^3 60 % full (10,514 sites) 61 and 60, 112 and 136.  Boxes of eight
+// points along x or fewer, half empty when rounded: 8 x 8 x 128 62 and 57, 128
+// and 125.
+bool far_lines(int nsites, const int n[3], int nset) {
     const long long v = 8LL * ((n[0] + 7) / 8) * FF_LINES * ((n[1] + FF_LINES - 1) / FF_LINES) * n[2];
-    return nsites >= 4096 && v <= 3LL * nsites;
+    if (nsites < 4096 || v > 3LL * nsites) return false;
+    const bool half = v < 2LL * nsites;
+    if (nsites >= 8192) return half || n[0] > 8;
+    if (10 * v <= 11LL * nsites) return true;
+    return half ? nset >= 1024 : n[0] > 8 && nset >= 2048;
 }
 namespace {
 struct LineSizes {
@@ -466,8 +485,17 @@ void launch_far_lines(const int* map, const int* perm, const double2* P, long lo
         hipLaunchKernelGGL(k_ff_operands, dim3(nfold + ((nf + NT - 1) / NT) * ((nd + FF_DIRS - 1) / FF_DIRS), nq),
                            dim3(NT), 0, s, map, perm, P + (size_t)q0 * n3, n3, n[0], n[1], n[2], z.KS, fold, kt,
                            nfold, dq, nd, dstride, k, lo[1], lo[2], tab);
-        hipLaunchKernelGGL(k_ff_lines, dim3((nd + per_wg - 1) / per_wg, z.nchunk, nq), dim3(NT), sm, s, fold, kt,
-                           n[0], n[1], n[2], z.KS, tab, nd, part);
+        // one component a wavefront where that still leaves no more wavefronts
+        // than the card holds at once (three per SIMD): a wavefront's tiles are
+        // a chain of load latencies.  One right-hand side of 9,261 sites (21^3),
+        // 74 directions: 17.2 us with three components, 9.1 with one; 722
+        // directions 16.5 and 12.3
+        if ((long long)((nd + FF_DIRS - 1) / FF_DIRS) * z.nchunk * nq <= FF_SPLIT)
+            hipLaunchKernelGGL(k_ff_lines<1>, dim3((nd + per_wg - 1) / per_wg, 3 * z.nchunk, nq), dim3(NT), sm, s, fold,
+                               kt, n[0], n[1], n[2], z.KS, tab, nd, part);
+        else
+            hipLaunchKernelGGL(k_ff_lines<3>, dim3((nd + per_wg - 1) / per_wg, z.nchunk, nq), dim3(NT), sm, s, fold, kt,
+                               n[0], n[1], n[2], z.KS, tab, nd, part);
         hipLaunchKernelGGL(k_ff_project, dim3((nd + NT - 1) / NT, nq), dim3(NT), 0, s, part, z.nchunk, dq, nd, dstride,
                            k, lo[0] + 0.5 * (n[0] - 1), f + (size_t)q0 * nd * 2, dcs + (size_t)q0 * nd);
     }

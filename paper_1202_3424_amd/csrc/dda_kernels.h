@@ -321,10 +321,11 @@ void launch_avg_dirs(int ng, const double* kh, const double* mu, int n_theta, in
 void launch_farfield_sets(int nsites, const int* coords, const double2* P, int nrhs, const double* dirs, int per,
                           double k, const int lo[3], const int n[3], double2* f, double* dcs, hipStream_t s);
 // The same amplitudes by contractions along x on the matrix cores, for boxes
-// that sites fill densely (far_lines): P in caller order, n3 values a
+// that sites fill densely (far_lines; nset: directions of each right-hand
+// side's own set, 0 for one list): P in caller order, n3 values a
 // right-hand side; dirs [nd][9], per right-hand side dstride directions
 // further on (0: one list for all); work: far_lines_bytes
-bool far_lines(int nsites, const int n[3]);
+bool far_lines(int nsites, const int n[3], int nset);
 size_t far_lines_bytes(const int n[3], int nrhs, int nd);
 void launch_far_lines(const int* map, const int* perm, const double2* P, long long n3, int nrhs, const double* dirs,
                       int nd, int dstride, double k, const int lo[3], const int n[3], void* work, double2* f,

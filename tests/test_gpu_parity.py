@@ -1743,3 +1743,63 @@ def test_few_workgroups_of_long_planes_take_three_passes(dda, precision, box, n_
     assert dda.tuned_variants(tgt, n_rhs, precision) == (0, 0 if plane else 4 if precision == "fp64" else 3, 0)
     ref = dda.apply(tgt, dda.Options.for_size_parameter(1.0, precision=precision, kernel_variant=4), kh, e0, xv)
     assert torch.equal(y, ref)
+
+
+# ------------------------------------------------------------------ far field: which form
+
+@pytest.mark.parametrize("box,drop", [((16, 16, 16), 0), ((16, 16, 16), 1), ((8, 16, 32), 0), ((30, 30, 5), 0),
+                                      ((21, 21, 21), 3700), ((24, 24, 24), 5600), ((8, 8, 128), 0), ((8, 8, 128), 8),
+                                      ((32, 32, 16), 10900), ((32, 32, 16), 10930)])
+def test_far_field_forms_about_their_line_match_the_oracle(dda, box, drop):
+    """Boxes on each side of the lines that choose between the contraction
+    along x and the sum over sites (4,096 and 8,192 sites, points of the rounded
+    box per site, short x), over lists and average sets on each side of the
+    counts that matter: amplitudes against the oracle's direct sum (1e-12),
+    averages against the oracle's quadrature (1e-10), and every direction's
+    amplitude the same bits in a list of its own, every right-hand side's in a
+    call of its own."""
+    from oracle import farfield
+    rng = np.random.default_rng(drop + box[0])
+    ijk = w.brick(*box)
+    inner = np.flatnonzero(~np.all((ijk == ijk.min(0)) | (ijk == ijk.max(0)), axis=1))
+    ijk = np.delete(ijk, rng.choice(inner, drop, replace=False), axis=0)
+    n = len(ijk)
+    tgt = dda.Target(ijk, 1.5 + 0.1j)
+    assert tgt.box == box
+    P = w.random_vectors(81, (2, n, 3))
+    opts = dda.Options.for_size_parameter(4.0)
+    k = dense.kd_from_size_parameter(4.0, n)
+    nh, th, ph = w.lab_directions(rng.uniform(0, 180, 83), rng.uniform(0, 360, 83))
+    f, dcs = dda.far_field(tgt, opts, _cuda(P), nh, th, ph)
+    for q in range(2):
+        A = farfield.amplitude_vectors(ijk, P[q], k, nh)
+        ref = np.stack([np.sum(th * A, axis=1), np.sum(ph * A, axis=1)], axis=1)
+        assert np.abs(f[q] - ref).max() <= 1e-12 * np.abs(P[q]).sum() * k ** 3 / np.sqrt(n)
+        f1, _ = dda.far_field(tgt, opts, _cuda(P[q:q + 1]), nh[40:41], th[40:41], ph[40:41])
+        assert np.array_equal(f1[0, 0], f[q, 40])
+    kh, e0 = w.along_x_yz()
+    a = dense.aeff_over_d(n)
+    for nt, nphi in ((5, 3), (20, 60), (32, 64)):
+        av = dda.scattering_averages(tgt, opts, kh, e0, _cuda(P), nt, nphi)
+        one = dda.scattering_averages(tgt, opts, kh[1:], e0[1:], _cuda(P[1:]), nt, nphi)
+        assert one[0] == av[1]
+        qs, g, c2 = farfield.angular_averages(ijk, P[0], k, kh[0], a, nt, nphi)
+        assert abs(av[0]["qsca"] - qs) <= 1e-10 * qs
+        assert abs(av[0]["g"] - g) <= 1e-10 and abs(av[0]["cos2"] - c2) <= 1e-10
+
+
+def test_far_field_lines_of_one_and_three_components_agree(dda):
+    """A launch of few wavefronts takes one component a wavefront, a larger one
+    all three: a 4,096-site target's amplitudes over 3,000 directions (three
+    components) equal, bitwise, those of the same directions 500 at a time."""
+    ijk = w.brick(16, 16, 16)
+    tgt = dda.Target(ijk, 1.5 + 0.1j)
+    rng = np.random.default_rng(82)
+    nh, th, ph = w.lab_directions(rng.uniform(0, 180, 3000), rng.uniform(0, 360, 3000))
+    P = _cuda(w.random_vectors(82, (1, len(ijk), 3)))
+    opts = dda.Options.for_size_parameter(3.0)
+    f, dcs = dda.far_field(tgt, opts, P, nh, th, ph)
+    for d in range(0, 3000, 500):
+        s = slice(d, d + 500)
+        fs, ds = dda.far_field(tgt, opts, P, nh[s], th[s], ph[s])
+        assert np.array_equal(fs[0], f[0, s]) and np.array_equal(ds[0], dcs[0, s])
