@@ -355,9 +355,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) void k_
 }
 
 // A = k^3 times the chunks' sums in order and the phase of the box centre in
-// x, projected on theta and phi.
+// x, projected on theta and phi; f and dcs [q][ostride].
 __global__ __launch_bounds__(NT) void k_ff_project(const double* part, int nchunk, const double* dirs, int nd,
-                                                  int dstride, double k, double xc, double2* f, double* dcs) {
+                                                  int dstride, double k, double xc, int ostride, double2* f,
+                                                  double* dcs) {
     const int d = blockIdx.x * NT + threadIdx.x, q = blockIdx.y;
     if (d >= nd) return;
     const double* dv = dirs + ((long long)q * dstride + d) * 9;
@@ -376,7 +377,7 @@ __global__ __launch_bounds__(NT) void k_ff_project(const double* part, int nchun
         f1 = cadd(f1, double2{dv[3 + c] * A.x, dv[3 + c] * A.y});
         f2 = cadd(f2, double2{dv[6 + c] * A.x, dv[6 + c] * A.y});
     }
-    const long long o = (long long)q * nd + d;
+    const long long o = (long long)q * ostride + d;
     f[o * 2 + 0] = f1;
     f[o * 2 + 1] = f2;
     dcs[o] = (f1.x * f1.x + f1.y * f1.y + f2.x * f2.x + f2.y * f2.y) / (k * k);
@@ -443,22 +444,33 @@ bool far_lines(int nsites, const int n[3], int nset) {
     return half ? nset >= 1024 : n[0] > 8 && nset >= 2048;
 }
 namespace {
+// Work memory is at most FF_WORK, by groups of directions and of right-hand
+// sides, or what one right-hand side's folded operands (at most 3 times its P
+// by the rule above, and its rounding) and FF_DMIN directions take.
+constexpr size_t FF_WORK = (size_t)512 << 20;
+constexpr int FF_DMIN = 4096;
 struct LineSizes {
     int KS, tiles, nchunk, nkg;
+    int nd;                       // directions of a launch
     size_t fold, kt, part, tab;   // bytes: kt of the launch, the others per right-hand side
-    LineSizes(const int n[3], int nd) {
+    LineSizes(const int n[3], int nd_) {
         KS = ((n[0] + 1) / 2 + 3) / 4;
         tiles = n[2] * ((n[1] + FF_LINES - 1) / FF_LINES);
         nchunk = (n[2] + FF_Z - 1) / FF_Z;
         fold = (size_t)tiles * 3 * KS * 2 * 64 * sizeof(double2);
         nkg = (KS + 3) / 4;
         kt = ((size_t)tiles * nkg * sizeof(int) + 255) & ~(size_t)255;
-        part = (size_t)nchunk * nd * 6 * sizeof(double);
-        tab = (size_t)((nd + FF_DIRS - 1) / FF_DIRS) * (KS * 64 + (n[1] + n[2]) * FF_DIRS) * sizeof(double2);
+        const size_t pd = (size_t)nchunk * 6 * sizeof(double);   // part and tab of a direction
+        const size_t td = (size_t)(KS * 4 + n[1] + n[2]) * sizeof(double2);
+        const size_t most = (fold < FF_WORK ? FF_WORK - fold : 0) / (pd + td) / FF_DMIN * FF_DMIN;
+        nd = most >= (size_t)nd_ ? nd_ : (int)(most > FF_DMIN ? most : FF_DMIN);
+        if (nd > nd_) nd = nd_;
+        part = nd * pd;
+        tab = (size_t)((nd + FF_DIRS - 1) / FF_DIRS) * FF_DIRS * td;
     }
-    // right-hand sides of a launch: operands of at most 512 MiB, at least one
+    // right-hand sides of a launch, at least one
     int group(int nrhs) const {
-        const size_t most = ((size_t)512 << 20) / (fold + part + tab);
+        const size_t most = FF_WORK / (fold + part + tab);
         return (int)(most < 1 ? 1 : (most < (size_t)nrhs ? most : (size_t)nrhs));
     }
 };
@@ -478,26 +490,31 @@ void launch_far_lines(const int* map, const int* perm, const double2* P, long lo
     double* part = (double*)((char*)tab + (size_t)grp * z.tab);
     const size_t sm = (size_t)(NT / 64) * z.KS * 64 * sizeof(double2);
     const int nf = z.KS * 64 + (n[1] + n[2]) * FF_DIRS;
-    const int per_wg = FF_DIRS * (NT / 64), nfold = z.tiles * z.nkg * 3;
-    for (int q0 = 0; q0 < nrhs; q0 += grp) {
-        const int nq = nrhs - q0 < grp ? nrhs - q0 : grp;
-        const double* dq = dirs + (size_t)q0 * dstride * 9;
-        hipLaunchKernelGGL(k_ff_operands, dim3(nfold + ((nf + NT - 1) / NT) * ((nd + FF_DIRS - 1) / FF_DIRS), nq),
+    const int per_wg = FF_DIRS * (NT / 64);
+    const int groups = (nd + z.nd - 1) / z.nd;
+    for (int g = 0; g < groups * ((nrhs + grp - 1) / grp); ++g) {
+        const int q0 = g / groups * grp, d0 = g % groups * z.nd;
+        const int nq = nrhs - q0 < grp ? nrhs - q0 : grp, ng = nd - d0 < z.nd ? nd - d0 : z.nd;
+        const double* dq = dirs + ((size_t)q0 * dstride + d0) * 9;
+        // (P is folded with the first directions of its group)
+        const int nfold = d0 == 0 ? z.tiles * z.nkg * 3 : 0;
+        hipLaunchKernelGGL(k_ff_operands, dim3(nfold + ((nf + NT - 1) / NT) * ((ng + FF_DIRS - 1) / FF_DIRS), nq),
                            dim3(NT), 0, s, map, perm, P + (size_t)q0 * n3, n3, n[0], n[1], n[2], z.KS, fold, kt,
-                           nfold, dq, nd, dstride, k, lo[1], lo[2], tab);
+                           nfold, dq, ng, dstride, k, lo[1], lo[2], tab);
         // one component a wavefront where that still leaves no more wavefronts
         // than the card holds at once (three per SIMD): a wavefront's tiles are
         // a chain of load latencies.  One right-hand side of 9,261 sites (21^3),
         // 74 directions: 17.2 us with three components, 9.1 with one; 722
         // directions 16.5 and 12.3
-        if ((long long)((nd + FF_DIRS - 1) / FF_DIRS) * z.nchunk * nq <= FF_SPLIT)
-            hipLaunchKernelGGL(k_ff_lines<1>, dim3((nd + per_wg - 1) / per_wg, 3 * z.nchunk, nq), dim3(NT), sm, s, fold,
-                               kt, n[0], n[1], n[2], z.KS, tab, nd, part);
+        if ((long long)((ng + FF_DIRS - 1) / FF_DIRS) * z.nchunk * nq <= FF_SPLIT)
+            hipLaunchKernelGGL(k_ff_lines<1>, dim3((ng + per_wg - 1) / per_wg, 3 * z.nchunk, nq), dim3(NT), sm, s, fold,
+                               kt, n[0], n[1], n[2], z.KS, tab, ng, part);
         else
-            hipLaunchKernelGGL(k_ff_lines<3>, dim3((nd + per_wg - 1) / per_wg, z.nchunk, nq), dim3(NT), sm, s, fold, kt,
-                               n[0], n[1], n[2], z.KS, tab, nd, part);
-        hipLaunchKernelGGL(k_ff_project, dim3((nd + NT - 1) / NT, nq), dim3(NT), 0, s, part, z.nchunk, dq, nd, dstride,
-                           k, lo[0] + 0.5 * (n[0] - 1), f + (size_t)q0 * nd * 2, dcs + (size_t)q0 * nd);
+            hipLaunchKernelGGL(k_ff_lines<3>, dim3((ng + per_wg - 1) / per_wg, z.nchunk, nq), dim3(NT), sm, s, fold, kt,
+                               n[0], n[1], n[2], z.KS, tab, ng, part);
+        const size_t o = (size_t)q0 * nd + d0;
+        hipLaunchKernelGGL(k_ff_project, dim3((ng + NT - 1) / NT, nq), dim3(NT), 0, s, part, z.nchunk, dq, ng, dstride,
+                           k, lo[0] + 0.5 * (n[0] - 1), nd, f + o * 2, dcs + o);
     }
 }
 

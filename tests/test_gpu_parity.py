@@ -1803,3 +1803,49 @@ def test_far_field_lines_of_one_and_three_components_agree(dda):
         s = slice(d, d + 500)
         fs, ds = dda.far_field(tgt, opts, P, nh[s], th[s], ph[s])
         assert np.array_equal(fs[0], f[0, s]) and np.array_equal(ds[0], dcs[0, s])
+
+
+def test_far_field_work_memory_is_bounded(dda):
+    """65,535 directions on 4.1 million sites: the call works through them in
+    groups, so that its work memory stays within 512 MiB beside its lists
+    (taken on a context of its own, whose work memory starts empty); the
+    amplitudes of directions about the groups' ends are bitwise those of short
+    lists."""
+    import ctypes
+    from paper_1202_3424_amd import _abi
+    lib = _abi.load()
+    ijk = w.brick(160, 160, 160)
+    n, nd = len(ijk), 65535
+    m = np.full(n, 1.5 + 0.1j)
+    ctx, tgt = ctypes.c_void_p(), ctypes.c_void_p()
+    assert lib.dda_ctx_create(0, None, ctypes.byref(ctx)) == 0
+    try:
+        assert lib.dda_target_create(ctx, n, ijk.ctypes.data, m.ctypes.data, ctypes.byref(tgt)) == 0
+        g = torch.Generator(device="cuda")
+        g.manual_seed(83)
+        P = torch.randn((1, n, 3), generator=g, dtype=torch.complex128, device="cuda")
+        rng = np.random.default_rng(83)
+        fr = [np.ascontiguousarray(a) for a in w.lab_directions(rng.uniform(0, 180, nd), rng.uniform(0, 360, nd))]
+        o = dda.Options.for_size_parameter(8.0).c()
+
+        def far(sl):
+            d = [np.ascontiguousarray(a[sl]) for a in fr]
+            f = np.zeros((len(d[0]), 2), dtype=np.complex128)
+            dcs = np.zeros(len(d[0]))
+            assert lib.dda_far_field(ctx, tgt, ctypes.byref(o), 1, P.data_ptr(), len(d[0]), d[0].ctypes.data,
+                                     d[1].ctypes.data, d[2].ctypes.data, f.ctypes.data, dcs.ctypes.data) == 0
+            return f, dcs
+
+        torch.cuda.synchronize()
+        free0 = torch.cuda.mem_get_info()[0]
+        f, dcs = far(slice(0, nd))
+        torch.cuda.synchronize()
+        lists = nd * (9 + 4 + 1) * 8
+        assert free0 - torch.cuda.mem_get_info()[0] <= (512 << 20) + lists + (8 << 20)
+        for d in (0, 4090, 24570, 28668, 32760, 61436, nd - 9):
+            fs, ds = far(slice(d, d + 9))
+            assert np.array_equal(fs, f[d:d + 9]) and np.array_equal(ds, dcs[d:d + 9]), d
+    finally:
+        if tgt:
+            lib.dda_target_destroy(tgt)
+        lib.dda_ctx_destroy(ctx)
