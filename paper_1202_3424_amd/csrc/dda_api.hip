@@ -187,8 +187,9 @@ struct dda_ctx {
     std::vector<Pending> pending;
     double tms[DDA_TIMING_CATEGORIES] = {};
     long long tlaunch[DDA_TIMING_CATEGORIES] = {};
-    // autotuned strided-pass variants per (grid, box, right-hand sides, precision)
-    std::map<std::tuple<int, int, int, int, int, int, int, int>, std::array<int, 3>> tuned;
+    // autotuned strided-pass variants per (grid, box, input window, right-hand
+    // sides, precision): see tuned_key
+    std::map<std::array<int, 14>, std::array<int, 3>> tuned;
     // batched calls: seconds taken with 4, 2 and 1 jobs in flight (< 0: not
     // tried yet), per batch shape (the jobs' grids and right-hand sides)
     std::map<std::string, std::array<double, 3>> sched;
@@ -432,6 +433,14 @@ struct Seg {
     double kd;
 };
 
+// What the autotuner's choice belongs to.  The input window is part of it: the
+// forward passes of a near-field volume do less work than those of a target
+// that fills the same box.
+std::array<int, 14> tuned_key(const Geo& g, int nrhs, bool fp32, bool ragged) {
+    return {g.M[0],  g.M[1],  g.M[2],  g.n[0],  g.n[1],  g.n[2],  g.i0[0],
+            g.i0[1], g.i0[2], g.i1[0], g.i1[1], g.i1[2], nrhs,    (fp32 ? 1 : 0) | (ragged ? 2 : 0)};
+}
+
 struct Work {
     dda_ctx* c;
     Workspace& ws;
@@ -643,8 +652,7 @@ struct Work {
             }
             return;
         }
-        auto key = std::make_tuple(g.M[0], g.M[1], g.M[2], g.n[0], g.n[1], g.n[2], nrhs,
-                                   (fp32 ? 1 : 0) | (a.rg ? 2 : 0));
+        const auto key = tuned_key(g, nrhs, fp32, a.rg != nullptr);
         auto it = c->tuned.find(key);
         if (it != c->tuned.end()) {
             for (int i = 0; i < 3; ++i) var[i] = it->second[i];
@@ -2064,8 +2072,7 @@ dda_status dda_ctx_tuned_variants(dda_ctx* c, const dda_target* t, int32_t n_rhs
         if (n_rhs < 1) invalid("n_rhs must be >= 1");
         if (precision != DDA_FP64 && precision != DDA_FP32_MATVEC) invalid("unknown precision");
         const Geo& g = t->geo;
-        auto key = std::make_tuple(g.M[0], g.M[1], g.M[2], g.n[0], g.n[1], g.n[2], (int)n_rhs,
-                                   precision == DDA_FP32_MATVEC ? 1 : 0);
+        const auto key = tuned_key(g, n_rhs, precision == DDA_FP32_MATVEC, false);
         auto it = c->tuned.find(key);
         for (int i = 0; i < 3; ++i) variants[i] = it == c->tuned.end() ? -1 : it->second[i];
         return DDA_OK;

@@ -1849,3 +1849,21 @@ def test_far_field_work_memory_is_bounded(dda):
         if tgt:
             lib.dda_target_destroy(tgt)
         lib.dda_ctx_destroy(ctx)
+
+
+@pytest.mark.parametrize("precision,edge", [("fp64", 20), ("fp32_matvec", 34)])
+def test_near_field_volume_is_tuned_apart_from_a_target_of_its_box(dda, precision, edge):
+    """The passes of a near-field volume cover its input window: their tuned
+    variants are not those of an ordinary target that fills the same box with
+    the same count of right-hand sides."""
+    small = dda.Target(w.brick(edge, edge, edge), 1.5 + 0.1j)
+    big = dda.Target(np.array([[0, 0, 0]] + [[2 * edge - 1] * 3]), 1.5 + 0.1j)
+    kh, e0 = w.incidences_for_orientations(91, 7)
+    opts = dda.Options.for_size_parameter(1.3, precision=precision)
+    assert dda.tuned_variants(big, 14, precision) == (-1, -1, -1)
+    _, dims, _, _ = dda.nearfield(small, opts, (0.5,) * 6, kh, e0, _cuda(w.random_vectors(91, (14, edge ** 3, 3))))
+    assert tuple(dims) == big.box
+    assert dda.tuned_variants(big, 14, precision) == (-1, -1, -1)
+    dda.apply(big, opts, kh, e0, _cuda(w.random_vectors(92, (14, 2, 3))))
+    v = dda.tuned_variants(big, 14, precision)
+    assert all(0 <= a < 28 for a in v) and v != (0, 0, 0)
