@@ -1867,3 +1867,141 @@ def test_near_field_volume_is_tuned_apart_from_a_target_of_its_box(dda, precisio
     dda.apply(big, opts, kh, e0, _cuda(w.random_vectors(92, (14, 2, 3))))
     v = dda.tuned_variants(big, 14, precision)
     assert all(0 <= a < 28 for a in v) and v != (0, 0, 0)
+
+
+# ------------------------------------------------------------------ grids that the plane kernel does not take
+
+def _sparse_target(dda, box, seed, m=(1.4 + 0.1j,), p=0.02):
+    """About a fiftieth of the box's points, its corners among them."""
+    keep = np.random.default_rng(seed).random(box) < p
+    keep[0, 0, 0] = keep[-1, -1, -1] = True
+    ijk = np.argwhere(keep).astype(np.int32)
+    tgt = dda.Target(ijk, np.asarray(m)[np.arange(len(ijk)) % len(m)])
+    assert tgt.box == tuple(box)
+    return tgt
+
+
+def _launches(dda, fn):
+    """fn() and the launches of each kernel category it made."""
+    dda.set_timing(True)
+    try:
+        out = fn()
+        torch.cuda.synchronize()
+        return out, {k: v[2] for k, v in dda.get_timing().items()}
+    finally:
+        dda.set_timing(False)
+
+
+# boxes whose y and z extents have compile-time lengths without a plane kernel
+# (FP64 80 x 80; FP32 128 x 128)
+NO_PLANE = {"fp64": ((12, 36, 34), (14, 33, 40)), "fp32_matvec": ((12, 60, 52), (14, 64, 63))}
+
+
+@pytest.mark.parametrize("precision,box,n_rhs,plane", [
+    ("fp64", (16, 32, 32), 4, True), ("fp64", (12, 36, 34), 4, False), ("fp64", (3, 7, 9), 2, True),
+    ("fp64", (5, 9, 24), 8, False), ("fp64", (40, 48, 30), 2, True), ("fp64", (40, 30, 48), 2, False),
+    ("fp32_matvec", (16, 40, 40), 4, True), ("fp32_matvec", (12, 60, 52), 4, False),
+    ("fp32_matvec", (30, 60, 40), 2, True), ("fp32_matvec", (3, 70, 5), 2, False)])
+def test_which_grids_take_the_plane_kernel(dda, precision, box, n_rhs, plane):
+    """A product runs the forward y pass as a kernel of its own exactly where
+    the plane kernel does not take its grid (and always where a variant is
+    named), with bitwise the same result."""
+    tgt = _sparse_target(dda, box, 101)
+    kh, e0 = np.tile([1.0, 0, 0], (n_rhs, 1)), np.tile(np.array([0, 1, 0], complex), (n_rhs, 1))
+    xv = _cuda(w.random_vectors(101, (n_rhs, tgt.n_sites, 3)))
+    opts = dda.Options.for_size_parameter(1.0, precision=precision)
+    dda.apply(tgt, opts, kh, e0, xv)   # builds the tensor, tunes
+    y, launches = _launches(dda, lambda: dda.apply(tgt, opts, kh, e0, xv))
+    assert (launches["fft_y_fwd"] == 0) == plane and launches["fft_z_green"] == 1
+    named = dataclasses.replace(opts, kernel_variant=4)
+    ref, launches = _launches(dda, lambda: dda.apply(tgt, named, kh, e0, xv))
+    assert launches["fft_y_fwd"] == 1
+    assert torch.equal(y, ref)
+
+
+@pytest.mark.parametrize("precision", sorted(NO_PLANE))
+@pytest.mark.parametrize("solver", ["bicgstab", "qmr", "bicgstab2"])
+def test_tuned_separate_passes_equal_the_default_ones(dda, solver, precision):
+    """A solve with the autotuned tilings of the three passes equals, bitwise,
+    one with the default tilings, on a grid that runs them."""
+    tgt = _sparse_target(dda, NO_PLANE[precision][0], 102)
+    kh, e0 = w.along_x_yz()
+    opts = dda.Options.for_size_parameter(2.0, solver=solver, precision=precision)
+    (P1, r1), launches = _launches(dda, lambda: dda.solve(tgt, opts, kh, e0))
+    assert launches["fft_y_fwd"] > 0
+    P2, r2 = dda.solve(tgt, dataclasses.replace(opts, autotune=False), kh, e0)
+    assert torch.equal(P1, P2) and r1 == r2
+
+
+@pytest.mark.parametrize("precision", sorted(NO_PLANE))
+@pytest.mark.parametrize("solver", ["bicgstab", "qmr", "bicgstab2"])
+def test_separate_passes_in_shared_launches_and_graphs(dda, solver, precision):
+    """Two targets of different boxes on one padded grid whose passes 2-4 are
+    separate kernels: the batch that shares every launch (each right-hand side
+    its own target's extents and tensor), replayed from graphs several times
+    with other solves between, launched directly, and as separate targets
+    equals, bitwise, the targets solved alone."""
+    ts = [_sparse_target(dda, b, 103 + i, m=(1.4 + 0.1j, 1.7 + 0.3j)) for i, b in enumerate(NO_PLANE[precision])]
+    assert ts[0].grid == ts[1].grid
+    kh, e0 = w.incidences_for_orientations(103, 3)
+    opts = [dda.Options.for_size_parameter(x, tol=tol, solver=solver, precision=precision)
+            for x, tol in ((2.0, 1e-5), (1.6, 1e-6))]
+    rt = np.array([0, 1, 1, 0, 1, 0])
+    alone = []
+    for i, t in enumerate(ts):
+        alone.append(dda.solve(t, opts[i], kh[rt == i], e0[rt == i]))
+
+    def check(P, r):
+        for i in range(2):
+            for j, q in enumerate(np.flatnonzero(rt == i)):
+                assert torch.equal(P[q], alone[i][0][j]) and r[q] == alone[i][1][j], (i, q)
+
+    for _ in range(3):
+        check(*dda.solve_batched(ts, opts, rt, kh, e0))
+        dda.solve(ts[0], opts[0], kh[:2], e0[:2])
+        torch.cuda.synchronize()
+    (P, r), launches = _launches(dda, lambda: dda.solve_batched(
+        ts, [dataclasses.replace(o, graphs=False) for o in opts], rt, kh, e0))
+    assert launches["fft_y_fwd"] > 0
+    check(P, r)
+    check(*dda.solve_batched(ts, [dataclasses.replace(o, share_launches=False) for o in opts], rt, kh, e0))
+
+
+# points of the volume below and above a 4-site box on x, y, z: volumes of 7,
+# 10, 24 and about 131 points (padded 15, 20, 48 and 270)
+NF_RUNTIME_WINDOWS = {
+    "y10_z24": ((1, 2), (2, 4), (8, 12)),
+    "y24_z10": ((0, 0), (8, 12), (6, 0)),
+    "x10_y10_z24": ((6, 0), (0, 6), (20, 0)),
+    "y132": ((0, 3), (64, 64), (0, 3)),
+    "z131": ((3, 0), (2, 1), (64, 63)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(NF_RUNTIME_WINDOWS))
+@pytest.mark.parametrize("precision", ["fp64", "fp32_matvec"])
+def test_nearfield_input_window_through_runtime_planned_passes(dda, name, precision):
+    """Windows of volumes with a y or z extent that has no compile-time length
+    and that run separate passes: every variant of the other axis' pass gives
+    the same bits, within the tolerances of
+    test_nearfield_matches_oracle_everywhere of the oracle's direct sums."""
+    from oracle import nearfield
+    ends = NF_RUNTIME_WINDOWS[name]
+    ext = tuple(b / 4 for axis in ends for b in axis)
+    ijk = np.array([[0, 0, 0], [3, 3, 3], [0, 3, 1], [3, 0, 2], [1, 2, 0], [2, 1, 3]], dtype=np.int32)
+    tgt = dda.Target(ijk, 1.5 + 0.1j)
+    kh, e0 = np.array([[0.36, 0.48, 0.8]] * 2), np.array([[0.8, -0.6, 0]] * 2, dtype=complex)
+    P = w.random_vectors(104, (2, len(ijk), 3))
+    opts = dda.Options.for_size_parameter(1.3, precision=precision)
+    (org, dims, Ei, Es), launches = _launches(dda, lambda: dda.nearfield(tgt, opts, ext, kh, e0, _cuda(P)))
+    assert launches["fft_y_fwd"] > 0
+    assert list(dims) == [4 + b + a for b, a in ends]
+    for variant in range(1, 29):
+        assert torch.equal(dda.nearfield(tgt, dataclasses.replace(opts, kernel_variant=variant), ext, kh, e0,
+                                         _cuda(P))[3], Es), variant
+    k = dense.kd_from_size_parameter(1.3, len(ijk))
+    tol = 1e-12 if precision == "fp64" else 2e-5
+    for q in range(2):
+        _, _, ri, rs = nearfield.nearfield(ijk, P[q], k, kh[q], e0[q], ext)
+        assert np.abs(Es[q].cpu().numpy() - rs).max() <= tol * np.abs(rs).max(), q
+        assert np.abs(Ei[q].cpu().numpy() - ri).max() <= 1e-13, q
