@@ -185,11 +185,14 @@ def load_traffic(kernel: str, workload: str, precision: str, variants, rhs_matve
     return None if v is None else v["bytes_per_rhs_matvec"] * rhs_matvecs_per_launch
 
 
+# one kernel for the three strided passes (compile-time lengths, short lengths)
+PLANE_PATTERN = r"k_plane(_rt)?<"
 # kernel-name patterns of each pass's compile-time family (every variant)
 PASS_PATTERNS = {
     "scatter_fft_x": r"k_scatter_x<",
     "fft_y_fwd": r"k_strided<(double|float), 3, 0, -1,|k_strided_rf<(double|float), 0, -1,",
-    "fft_z_green": r"k_strided<(double|float), 3, 1, -1,|k_strided_rf<(double|float), 1, -1,|k_zfold<|k_zsq<|k_plane<",
+    "fft_z_green": r"k_strided<(double|float), 3, 1, -1,|k_strided_rf<(double|float), 1, -1,|k_zfold<|k_zsq<|"
+                   + PLANE_PATTERN,
     "fft_y_inv": r"k_strided<(double|float), 3, 0, 1,|k_strided_rf<(double|float), 0, 1,",
     "fft_x_gather": r"k_gather_x<",
 }
@@ -272,7 +275,7 @@ def summarize_profiles(tr: str, workload: str, prec: str, unprofiled: str) -> No
         out = {}
         v = 0
         if plane:   # the median launch: converged right-hand sides are skipped only at the end
-            fam = [r for r in fam if "k_plane<" in r["Kernel_Name"]]
+            fam = [r for r in fam if re.search(PLANE_PATTERN, r["Kernel_Name"])]
             top = statistics.mode(short(r["Kernel_Name"]) for r in fam)
             return {0: (top, statistics.median(float(r["Counter_Value"]) for r in fam) * 1024 * scale)}
         while v < n_var and (v + 1) * AUTOTUNE_LAUNCHES <= len(fam):

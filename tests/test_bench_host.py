@@ -103,3 +103,12 @@ def test_launch_groups_follow_the_library_merge_rule():
             job((80, 80, 80), opt(flags=2)), job((80, 80, 80), opt())]
     assert bench.launch_groups(jobs) == [[0], [1, 3], [2, 9], [4], [5], [6], [7], [8]]
     assert bench.launch_groups(jobs[1:2]) == [[0]]
+
+
+def test_pass_patterns_name_every_plane_kernel():
+    """Both plane kernels count as the z pass, and as nothing else."""
+    import re
+    for name in ("void dda::plane::k_plane<double, 96, 64, 512, 2>(dda::Geo, double2*)",
+                 "void dda::plane::k_plane_rt<float>(dda::Geo, dda::plane::ShortPlan)"):
+        assert [p for p, pat in bench.PASS_PATTERNS.items() if re.search(pat, name)] == ["fft_z_green"]
+    assert not re.search(bench.PLANE_PATTERN, "dda::(anonymous namespace)::k_green_plane(dda::Geo)")
