@@ -237,14 +237,17 @@ void launch_strided(int axis, int dir, int chk, const Geo& g, int nrhs, int nc, 
 inline int strided_variants(int L, bool gh) { return ct_length(L) ? (gh ? 28 : 12) : 1; }
 // Fixed choices for FP64 products beside an FP32-matvec solve (residual
 // checks; too few to tune for): slot 0 y forward, 1 z with tensor, 2 y
-// inverse.  Measured on cubes, two right-hand sides, us per launch against
-// variant 0: 128 25, 82, 26 (34, 105, 39); 160 59, 192, 71 (73, 233, 81); 192
-// 97, 422, 96 (153, 532, 173); 256 239, 787, 235 (395, 1276, 400); 384 976,
-// 4483, 1004 (1490, 5297, 1802).
+// inverse.  The fastest at each length, or within a tenth of it, with two
+// right-hand sides and with sixteen.  Measured on cubes, two right-hand sides,
+// us per launch against variant 0: 128 24, 71, 26 (27, 114, 34); 160 47, 146,
+// 57 (65, 197, 80); 192 95, 334, 95 (140, 443, 165); 256 246, 786, 236 (395,
+// 1387, 397); 384 1069, 3757, 1081 (2484, 6434, 2189); 512 4559, 9253, 3575
+// (8026, 13878, 5330).
 constexpr int check_variant(int L, int slot) {
     if (L < 128) return 0;
-    if (slot == 1) return L == 256 ? 25 : 10;
-    return (L == 192 || L > 256) ? 10 : 11;
+    if (slot == 1) return L == 128 ? 10 : L == 256 ? 25 : 6;
+    if (L == 160 || L == 512) return 3;
+    return (L == 192 || L == 384) ? 10 : 11;
 }
 // the variants a ragged batch runs: every y-pass variant, and the pass-3
 // variants that take one right-hand side per workgroup (each right-hand side
