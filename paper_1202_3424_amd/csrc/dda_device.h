@@ -63,7 +63,8 @@ struct RhsState {
     int max_iter;
     int restarts;
     int pad0;        // FP64 residual refinements taken (FP32-matvec mode)
-    // QMR: the smoothing step (w_old, w_new) has not been applied yet.
+    // QMR: x += alpha p of the latest iteration and the smoothing step
+    // (w_old, w_new) after it have not been applied yet.
     // BiCGSTAB: the end of the latest iteration has not been applied to x
     // and r yet (1: x += alpha p + omega s, r = s - omega t; 2: x += alpha p,
     // after a half-step convergence)

@@ -12,9 +12,9 @@
 // the whole grid read and written by every axis.  The arithmetic of each
 // stored value is that of the full transform.
 //
-// 192^3 (n = 96): 186 us (63 + 60 + 63 for x, y and z), 1430 us as
+// 192^3 (n = 96): 178 us (57 + 59 + 62 for x, y and z), 1430 us as
 // whole-grid passes with a kernel each for the samples and the octant; each
-// of the three now moves about 87 MB in and out at 2.8 TB/s and is bounded by
+// of the three now moves about 87 MB in and out at 2.9 TB/s and is bounded by
 // its LDS passes.
 #include <stdexcept>
 
@@ -58,8 +58,8 @@ __device__ __forceinline__ void green_sample(int dx, int dy, int dz, double kd, 
 // XL lines per workgroup, three components at a time in LDS (the other three
 // wait in registers, so that each point is sampled once); at most
 // XL Mx / NT <= MAXP points per thread.  (Sampling only x >= 0 and mirroring
-// the rest into LDS took longer, 75 us against 63 at 192^3: the transform, not
-// the sampling, is the time.)
+// the rest into LDS took longer, 75 us against 63: the transform, not the
+// sampling, is the time.)
 template <int MAXP>
 __global__ __launch_bounds__(NT) void k_green_x(Geo g, double kd, double2* out, const double2* tw64, int XL) {
     extern __shared__ __align__(16) unsigned char smem[];

@@ -190,7 +190,7 @@ enum FinKind {
     FIN_V = 0, FIN_T, FIN_FLUSH, FIN_COLD, FIN_WARM, FIN_RESTART, FIN_QSUM, FIN_RES, FIN_CONJ, FIN_REFINE,
     // QMR: after the product (alpha), after the update (smoothing, beta,
     // status), after the cold / warm start, after an FP64 refinement residual
-    // and after k_qmr_final (clears the pending smoothing step)
+    // and after k_qmr_final (clears the pending x += alpha p and smoothing step)
     FIN_QV, FIN_QUPD, FIN_QCOLD, FIN_QWARM, FIN_QREFINE, FIN_QFINAL,
     // BiCGstab(2): beta after the second product, the minimal-residual
     // coefficients after the fourth, status and beta after the update
@@ -290,8 +290,8 @@ void launch_green(const Geo& g, double kd, double2* work, double2* gh64, float2*
                   hipStream_t s);
 // 1/alpha (scheme + 2: its derivative in eps) per (right-hand side, material)
 // from the target's distinct refractive indices mats [nmat] and the ambient
-// medium's index
-// (the incidences travel as kernel arguments and are stored to the device too)
+// medium's index; launch_alpha_inc: with the incidences as kernel arguments,
+// which it stores to the device too
 void launch_alpha_inc(const AlphaArgs& al, double* khat_dev, double2* e0_dev, hipStream_t s);
 void launch_alpha(int nrhs, int nmat, const double2* mats, double m_medium, const double* khat, const double2* e0,
                   double kd, int scheme, double2* ainv, hipStream_t s, int ostride = 0);
@@ -302,7 +302,7 @@ void launch_init_warm(const SiteArgs& a, int site_blocks, hipStream_t s);
 void launch_bicg_flush(const SiteArgs& a, int site_blocks, hipStream_t s);
 void launch_restart(const SiteArgs& a, int site_blocks, hipStream_t s);
 // QMR: start (cold: r = b, x = 0; warm: r holds b - A x), update, and the
-// pending smoothing step applied to x (x <- the smoothed iterate)
+// pending x += alpha p and smoothing step applied (x <- the smoothed iterate)
 void launch_qmr_init(const SiteArgs& a, bool cold, int site_blocks, hipStream_t s);
 void launch_qmr_update(const SiteArgs& a, int site_blocks, hipStream_t s);
 void launch_qmr_final(const SiteArgs& a, int site_blocks, hipStream_t s);
@@ -334,8 +334,7 @@ void launch_far_lines(const int* map, const int* perm, const double2* P, long lo
                       int nd, int dstride, double k, const int lo[3], const int n[3], void* work, double2* f,
                       double* dcs, hipStream_t s);
 // near field on an extended lattice box (first point org, extents dims):
-// P (caller order) into the box-scan site vector x at the target's sites;
-// E_sca = -v and E_inc at every point (either output may be null); the
+// E_inc at every point (E_sca is the product's gather, GA_FIELD); the
 // trilinear line a..b of n points through E [nrhs][box][3]
 void launch_nf_inc(int nrhs, const int org[3], const int dims[3], const double* khat, const double2* e0, double kd,
                    double2* einc, hipStream_t s);

@@ -9,20 +9,7 @@ namespace dda {
 
 namespace {
 
-template <typename C> __device__ __forceinline__ C to_c(double2 u) {
-    C c;
-    c.x = u.x;
-    c.y = u.y;
-    return c;
-}
-template <typename C> __device__ __forceinline__ double2 to_d(C u) {
-    double2 c;
-    c.x = (double)u.x;
-    c.y = (double)u.y;
-    return c;
-}
 __device__ __forceinline__ bool finite2(double2 a) { return isfinite(a.x) && isfinite(a.y); }
-
 
 // ------------------------------------------------------------------ setup
 

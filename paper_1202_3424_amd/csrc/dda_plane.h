@@ -52,8 +52,9 @@ constexpr size_t plane_bytes(int LY, int LZ, int nz, bool f32) {
 }
 
 // Lengths with a plane kernel: their product at every occupied extent the
-// padding rule gives them (at most L / 2 on each axis).  z: three components of a column to a thread,
-// up to 144 VGPRs of data, which leaves two wavefronts per SIMD.
+// padding rule gives them (at most L / 2 on each axis).  z: three components
+// of a column to a thread, up to 144 VGPRs of data, which leaves two
+// wavefronts per SIMD.
 constexpr bool plane_y(int L) { return L == 32 || L == 48 || L == 64 || L == 80 || L == 96 || L == 128; }
 template <typename T> constexpr bool plane_z(int LZ) { return plane_y(LZ) && z_vgprs<T>(LZ) <= 144; }
 // pairs whose plane fits with the largest occupied z extent, LZ / 2
@@ -116,7 +117,8 @@ __device__ __forceinline__ void wave_fence() {
 // least 192 bytes, an XCD takes one such run of kx and its mirror run (they
 // share tensor rows), every right-hand side in turn; with shorter runs (and
 // extents that do not split so) it takes a contiguous part of the
-// (right-hand side, kx) order.  Measured, us the first way and the second:
+// (right-hand side, kx) order.  Measured, us the first way and the second, the
+// kernel launched back to back:
 // FP64 Mx 32 39.5 and 34.0, 48 42.6 and 40.2, 64 94.6 and 95.7, 96 305 and
 // 312, 128 32.0 and 35.8 (two right-hand sides); FP32 Mx 96 178 and 168.
 template <typename T> __host__ __device__ constexpr bool plane_runs(int Mx) {
@@ -413,11 +415,11 @@ inline ShortPlan short_plan(const AxisPlan& ax) {
     ShortPlan p{};
     p.L = ax.L;
     p.tw = ax.tw;
-    p.nst = ax.nst > 0 ? ax.nst : 1;   // (one point: a pass of radix 1)
+    p.nst = ax.nst;   // (at least one: extents start at 2)
     if (p.nst > 3) throw std::invalid_argument("too many passes for a short axis");
     int ns = 1;
     for (int i = 0; i < p.nst; ++i) {
-        const int r = ax.nst > 0 ? ax.R[i] : 1;
+        const int r = ax.R[i];
         (i == 0 ? p.p0 : i == 1 ? p.p1 : p.p2) = (unsigned)(r | ns << 8 | (1024 + ns - 1) / ns << 16);
         ns *= r;
     }
@@ -469,7 +471,7 @@ __device__ __forceinline__ void short_pass(const typename V2<T>::t* src, int ss,
                 v[r] = cmul(v[r], t);
             }
         }
-        if constexpr (RR > 1) Dft<RR, DIR, C>::run(v);
+        Dft<RR, DIR, C>::run(v);
         const int b = (j - k) * RR + k;
         const unsigned d = __umul24(b, ds);
 #pragma unroll
@@ -484,7 +486,7 @@ __device__ __forceinline__ void short_step(const typename V2<T>::t* src, int ss,
     switch (w & 255) {
 #define DDA_R(N) \
     case N: short_pass<T, N, DIR, IN, OUT>(src, ss, dst, ds, e0, e1, tw, L, w, jb, jn); break;
-        DDA_R(8) DDA_R(5) DDA_R(4) DDA_R(3) DDA_R(2) DDA_R(1)
+        DDA_R(8) DDA_R(5) DDA_R(4) DDA_R(3) DDA_R(2)
 #undef DDA_R
     }
 }

@@ -1695,6 +1695,27 @@ def test_solves_of_many_right_hand_sides_read_each_sites_material(dda, solver, p
             assert torch.equal(Pb[q], Pi[j]) and rb[q] == ri[j]
 
 
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32_matvec", 2e-5)])
+@pytest.mark.parametrize("box", [(12, 3, 4), (40, 2, 3), (3, 9, 5)])
+def test_products_of_many_right_hand_sides_read_each_components_polarizability(dda, box, precision, tol):
+    """GKDLDR's 1/alpha differs from axis to axis: a 24-right-hand-side product
+    of one material takes each component's own, at compile-time (32, 80) and
+    runtime-planned (6) x lengths, as the dense matrix does."""
+    ijk = w.brick(*box)
+    n = len(ijk)
+    m = np.full(n, 2.0 + 0.5j)
+    tgt = dda.Target(ijk, m)
+    kh, e0 = w.incidences_for_orientations(65, 12)
+    opts = dda.Options.for_size_parameter(1.5, precision=precision, polarizability="GKDLDR")
+    xv = w.random_vectors(65, (24, n, 3))
+    y = dda.apply(tgt, opts, kh, e0, _cuda(xv))
+    for a, b in ((0, 8), (8, 24)):
+        assert torch.equal(dda.apply(tgt, opts, kh[a:b], e0[a:b], _cuda(xv[a:b])), y[a:b])
+    for q in (0, 9, 23):
+        ref = (_dense_A(ijk, m, 1.5, kh[q], e0[q], "GKDLDR") @ xv[q].reshape(-1)).reshape(n, 3)
+        assert np.abs(y[q].cpu().numpy() - ref).max() <= tol * np.abs(ref).max(), q
+
+
 # ------------------------------------------------------------------ plane kernel: launch shapes
 
 @pytest.mark.parametrize("precision,ny,nz", [("fp64", 24, 16), ("fp32_matvec", 13, 33), ("fp32_matvec", 16, 40),
