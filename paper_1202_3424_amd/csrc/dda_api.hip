@@ -2327,7 +2327,7 @@ dda_status dda_nearfield(dda_ctx* c, dda_target* t, const dda_opts* o, const dou
         // bounded by the z pass and the volume's traffic.  The 60k-site sphere
         // in a 96^3 volume took 969 us with P placed into a zeroed volume
         // vector, every line transformed and E_sca copied from the product;
-        // so it takes 738.
+        // so it takes 733.
         SiteArgs from = w.a;
         from.nsites = t->nsites;
         from.n3 = 3LL * t->nsites;

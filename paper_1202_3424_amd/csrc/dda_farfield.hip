@@ -446,7 +446,7 @@ bool far_lines(int nsites, const int n[3], int nset) {
 namespace {
 // Work memory is at most FF_WORK, by groups of directions and of right-hand
 // sides, or what one right-hand side's folded operands (at most 3 times its P
-// by the rule above, and its rounding) and FF_DMIN directions take.
+// by the rule above) and FF_DMIN directions take.
 constexpr size_t FF_WORK = (size_t)512 << 20;
 constexpr int FF_DMIN = 4096;
 struct LineSizes {
