@@ -1659,7 +1659,8 @@ def test_products_of_many_right_hand_sides_read_each_sites_material(dda, box, pr
 
 @pytest.mark.parametrize("solver", ["bicgstab", "qmr", "bicgstab2"])
 @pytest.mark.parametrize("precision", ["fp64", "fp32_matvec"])
-def test_solves_of_many_right_hand_sides_read_each_sites_material(dda, solver, precision):
+@pytest.mark.parametrize("scheme", ["LATTDR", "GKDLDR"])
+def test_solves_of_many_right_hand_sides_read_each_sites_material(dda, scheme, solver, precision):
     """Twenty right-hand sides on a target of three materials: every P and
     result is bitwise that of solves of ten, P agrees with the dense
     solution (the residual's tolerance over the smallest singular value), and a batch whose
@@ -1672,7 +1673,7 @@ def test_solves_of_many_right_hand_sides_read_each_sites_material(dda, solver, p
         ijks.append(np.argwhere(keep).astype(np.int32))
     ms = [_three_materials(len(i)) for i in ijks]
     ts = [dda.Target(i, m) for i, m in zip(ijks, ms)]
-    opts = dda.Options.for_size_parameter(1.1, tol=1e-9, solver=solver, precision=precision)
+    opts = dda.Options.for_size_parameter(1.1, tol=1e-9, solver=solver, precision=precision, polarizability=scheme)
     kh, e0 = w.incidences_for_orientations(62, 10)
     P, r = dda.solve(ts[0], opts, kh, e0)
     for a, b in ((0, 10), (10, 20)):
@@ -1680,7 +1681,7 @@ def test_solves_of_many_right_hand_sides_read_each_sites_material(dda, solver, p
         assert torch.equal(Ps, P[a:b]) and rs == r[a:b]
     k = dense.kd_from_size_parameter(1.1, len(ijks[0]))
     for q in (0, 13):
-        A = _dense_A(ijks[0], ms[0], 1.1, kh[q], e0[q], "LATTDR")
+        A = _dense_A(ijks[0], ms[0], 1.1, kh[q], e0[q], scheme)
         E = dense.incident_field(ijks[0], k, kh[q], e0[q]).reshape(-1)
         ref = np.linalg.solve(A, E)
         err = np.linalg.norm(P[q].cpu().numpy().reshape(-1) - ref)
